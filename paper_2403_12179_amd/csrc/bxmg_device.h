@@ -1,0 +1,38 @@
+// Device helpers shared by the kernel sources.
+#pragma once
+#include "bxmg_internal.h"
+
+namespace bxmg {
+
+// Raw-buffer resources (a base, a size in bytes, 32-bit lane offsets).
+constexpr int kBufferDword3 = 0x00020000;  // raw buffer, gfx9 data format
+// A byte offset beyond every box resource (their sizes stay below 2^31 bytes).
+constexpr int kOffPastBox = (int)0x80000000u;
+
+// Fixed-tree block reduction of (max, sum, sum): wave64 butterflies, then
+// the 4 wave results in order.  The result is valid in thread 0.
+__device__ __forceinline__ void block_reduce3(double& mx, double& s2, double& bad, double* sh) {
+    for (int o = 32; o > 0; o >>= 1) {
+        const double a = __shfl_xor(mx, o), b = __shfl_xor(s2, o), c = __shfl_xor(bad, o);
+        mx = fmax(mx, a);
+        s2 = s2 + b;
+        bad = bad + c;
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    if (lane == 0) { sh[3 * wid] = mx; sh[3 * wid + 1] = s2; sh[3 * wid + 2] = bad; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int nw = (blockDim.x + 63) >> 6;
+        mx = sh[0]; s2 = sh[1]; bad = sh[2];
+        for (int w = 1; w < nw; ++w) { mx = fmax(mx, sh[3 * w]); s2 = s2 + sh[3 * w + 1]; bad = bad + sh[3 * w + 2]; }
+    }
+}
+
+__device__ __forceinline__ void acc_norm(double rv, double& mx, double& s2, double& bad) {
+    const double a = fabs(rv);
+    if (!(a <= 1.7976931348623157e308)) bad += 1.0;  // NaN or Inf
+    else mx = fmax(mx, a);
+    s2 = s2 + rv * rv;
+}
+
+}  // namespace bxmg

@@ -78,6 +78,10 @@ struct Level {
     bool push = false;    // producers refresh the face ghosts they mirror
     mutable int flip = 0; // direction of the next sweep over the level's tiles
     bool res = false;     // 32-bit buffer addressing of the boxes
+    // streaming smoother (one-box constant-coefficient levels above the
+    // coarse cycle): blocks per kind and for a zero start
+    bool stream = false;
+    SweepPlan sweep[3][2];
     // level 0 of a solve whose caller boxes were merged: one view per caller
     // box (its valid cells, addressed in the merged storage) and tiles over
     // them, for the layout conversions and the field norm
@@ -117,6 +121,10 @@ struct Hier {
     // FP64 storage: all levels (precision 0) or level 0 only (precision 1)
     std::vector<std::unique_ptr<DevBuf<double>>> u64, f64;
     std::vector<std::unique_ptr<DevBuf<float>>> u32, f32;
+    // second iterate array of the streamed levels, between the pre-sweeps
+    // (u -> a), the prolongation (into a) and the post-sweeps (a -> u)
+    std::vector<std::unique_ptr<DevBuf<double>>> a64;
+    std::vector<std::unique_ptr<DevBuf<float>>> a32;
     DevBuf<double> beta64;
     DevBuf<float> beta32;
     std::vector<std::unique_ptr<FaceSet<double>>> faces64;  // index = level (0 unused)
@@ -178,6 +186,61 @@ struct Tuning {
 static void upload_tiles(const TileSet& t, DevBuf<Tile>& buf, int& n) {
     buf.upload(t.tiles);
     n = (int)t.tiles.size();
+}
+
+// Levels the streaming smoother takes: one box, constant coefficient, 32-bit
+// storage, above the coarse cycle (below it the levels run in one workgroup).
+static void plan_streams(Hier* H, long long& max_tiles) {
+    const size_t nl = H->L.size();
+    H->a64.resize(nl);
+    H->a32.resize(nl);
+    const size_t end = H->coarse_start >= 0 ? (size_t)H->coarse_start : nl - 1;
+    for (size_t l = 0; l < end && !H->var; ++l) {
+        Level& L = *H->L[l];
+        const Level& C = *H->L[l + 1];
+        if (L.boxes.size() != 1 || C.boxes.size() != 1 || !L.push || !L.res) continue;
+        const RBox& B = L.rb[0];
+        const RBox& Q = C.rb[0];
+        int n[3];
+        bool even = true;
+        for (int d = 0; d < 3; ++d) {
+            n[d] = B.hi[d] - B.lo[d] + 1;
+            even = even && n[d] % 2 == 0 && n[d] >= 4 && (B.lo[d] & 1) == 0;
+        }
+        if (!even) continue;
+        const bool f32 = H->precision == 1;
+        bool ok = true;
+        for (int kind = 0; kind < 3; ++kind)
+            for (int zero = 0; zero < 2; ++zero) {
+                SweepPlan& P = L.sweep[kind][zero];
+                P = plan_sweep(n, H->per, kind, zero != 0, f32);
+                ok = ok && P.nt > 0;
+                SweepArgs& A = P.args;
+                A.H = B.H;
+                A.GH = B.H * B.G[1];
+                A.cs = (int)B.cstride;
+                A.cH = Q.H;
+                A.cGH = Q.H * Q.G[1];
+                A.ccs = (int)Q.cstride;
+                A.cpar = (Q.lo[0] + Q.lo[1] + Q.lo[2]) & 1;
+                A.pid = B.pid;
+                A.h = B.h;
+                A.a = B.a;
+                max_tiles = std::max<long long>(max_tiles, P.blocks);
+            }
+        if (!ok) continue;
+        L.stream = true;
+        if (f32) {
+            H->a32[l] = std::make_unique<DevBuf<float>>();
+            H->a32[l]->alloc(L.nelem);
+            HIPCHK(hipMemset(H->a32[l]->p, 0, L.nelem * 4));
+        } else {
+            H->a64[l] = std::make_unique<DevBuf<double>>();
+            H->a64[l]->alloc(L.nelem);
+            HIPCHK(hipMemset(H->a64[l]->p, 0, L.nelem * 8));
+        }
+        H->bytes += (f32 ? 4 : 8) * (size_t)L.nelem;
+    }
 }
 
 // merge: coarse levels run on execution_boxes (solves); the stage calls keep
@@ -298,14 +361,6 @@ static std::unique_ptr<Hier> build_hier(const bxmg_ba_s* ba, int precision, bool
             else H->faces32[l]->table.upload({H->faces32[l]->view(D)});
         }
     }
-    H->partials.alloc(6 * max_tiles + 8);  // two sets: the fused residual's colour-1 and colour-0 norms
-    H->fnorm.alloc(4);
-    H->st.alloc(1);
-    H->flags.alloc(4);
-    HIPCHK(hipMemset(H->flags.p, 0, 4 * sizeof(int)));
-    H->hist.alloc(2 * kHist);
-    H->fn3.alloc(4);
-    H->iters.alloc(1);
     // fused coarse cycle: from the first level l >= 1 below which every level
     // is one box of at most kMaxBottomCells cells
     for (size_t l = 1; l < nl; ++l) {
@@ -314,6 +369,15 @@ static std::unique_ptr<Hier> build_hier(const bxmg_ba_s* ba, int precision, bool
             ok = H->L[m]->boxes.size() == 1 && H->L[m]->dom.cells() <= kMaxBottomCells;
         if (ok) { H->coarse_start = (int)l; break; }
     }
+    plan_streams(H.get(), max_tiles);
+    H->partials.alloc(6 * max_tiles + 8);  // two sets: the fused residual's colour-1 and colour-0 norms
+    H->fnorm.alloc(4);
+    H->st.alloc(1);
+    H->flags.alloc(4);
+    HIPCHK(hipMemset(H->flags.p, 0, 4 * sizeof(int)));
+    H->hist.alloc(2 * kHist);
+    H->fn3.alloc(4);
+    H->iters.alloc(1);
     return H;
 }
 
@@ -336,6 +400,13 @@ template <>
 double* lvl_f<double>(Hier* H, size_t l) { return H->f64[l]->p; }
 template <>
 float* lvl_f<float>(Hier* H, size_t l) { return H->f32[l]->p; }
+
+template <class T>
+T* lvl_a(Hier* H, size_t l);
+template <>
+double* lvl_a<double>(Hier* H, size_t l) { return H->a64[l]->p; }
+template <>
+float* lvl_a<float>(Hier* H, size_t l) { return H->a32[l]->p; }
 
 template <class T>
 const T* lvl_beta(Hier* H, size_t l);
@@ -417,6 +488,13 @@ struct Run {
     // needs the colour-0 residual only
     double* fuse_norms = nullptr;
     bool fused_sweep = false;
+    // on a streamed level 0 the post-sweeps take the norms of the whole
+    // residual instead, in this many partials from stream_norms
+    double* stream_norms = nullptr;
+    int streamed = 0;
+    bool zero_top = false;  // the V-cycle starts from level 0 = 0
+    // whether level l runs the streaming smoother (two sweeps each way)
+    bool streams(size_t l) const { return H->L[l]->stream && nu1 == 2 && nu2 == 2; }
     Grid grid(const Grid& g) const {
         Grid r = g;
         r.active = active;
@@ -527,7 +605,17 @@ void vcycle(Run& R, size_t l) {
     }
     const Level& L = *H->L[l];
     const Level& C = *H->L[l + 1];
-    T* u = lvl_u<T>(H, l);
+    const bool stream = R.streams(l);
+    // the array the prolongation corrects
+    T* u = stream ? lvl_a<T>(H, l) : lvl_u<T>(H, l);
+    if (stream) {
+        const bool zero = l > 0 || R.zero_top;
+        const SweepPlan& P = L.sweep[kSweepRestrict][zero ? 1 : 0];
+        R.pre(l, kStageGS);
+        HIPCHK(launch_sweep<T>(R.s, P, zero, false, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
+                               lvl_f<T>(H, l + 1), nullptr, R.active));
+        R.post(l, kStageGS);
+    } else {
     smooth<T>(R, l, R.nu1);
     if (!L.push) fill_faces<T>(R, l, u);
     R.pre(l, kStageRestrict);
@@ -535,10 +623,11 @@ void vcycle(Run& R, size_t l) {
     x.active = R.active;
     // the coarse correction starts from zero: zeroed by the same launch (the
     // fused coarse cycle zeroes its top level itself)
-    const bool zero_c = (int)l + 1 != H->coarse_start;
+    const bool zero_c = (int)l + 1 != H->coarse_start && !R.streams(l + 1);
     HIPCHK(launch_resid_restrict<T>(R.s, x, u, lvl_f<T>(H, l), lvl_beta<T>(H, l), lvl_fat<T>(H, l),
                                     lvl_f<T>(H, l + 1), zero_c ? lvl_u<T>(H, l + 1) : nullptr));
     R.post(l, kStageRestrict);
+    }
     vcycle<T>(R, l + 1);
     // a small one-box coarse level needs no ghost refresh where the staged
     // prolongation reads the cells its ghosts mirror (on large levels the
@@ -557,7 +646,19 @@ void vcycle(Run& R, size_t l) {
     HIPCHK(launch_prolong<T>(R.s, R.grid(L.walk()), C.d_rb.p, L.cbox.p, lvl_u<T>(H, l + 1), u, R.prolong, R.nu2 > 0,
                              L.stage_values, self, faces));
     R.post(l, kStageProlong);
-    smooth<T>(R, l, R.nu2, true);
+    if (!stream) {
+        smooth<T>(R, l, R.nu2, true);
+        return;
+    }
+    const bool norm = R.stream_norms && l == 0;
+    const int kind = norm ? kSweepNorm : kSweepPlain;
+    const SweepPlan& P = L.sweep[kind][0];
+    R.pre(l, kStageGS);
+    // (the solve's other level-0 passes read its face ghosts)
+    HIPCHK(launch_sweep<T>(R.s, P, false, true, l == 0, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
+                           R.stream_norms, R.active));
+    R.post(l, kStageGS);
+    if (norm) R.streamed = P.blocks;
 }
 
 // Coefficient setup: cell beta at level 0 (exchange + even reflection), then
@@ -1110,6 +1211,7 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
     double* pn = K.p[1].p;
     HIPCHK(launch_zero<double>(R.s, pc, n));  // beta = 0 reads it: keep it finite
     HIPCHK(launch_zero<double>(R.s, pn, n));
+    R.zero_top = true;
     Run R0 = R;  // the same, with launches that run whatever the stop flag says
     R0.active = nullptr;
     auto stop_test = [&]() {
@@ -1121,11 +1223,11 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
     // correction first (the direction pass clears it on the way otherwise)
     auto precondition = [&](bool zero) {
         if (fp32) {
-            if (zero) HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, n, R.active));
+            if (zero && !R.streams(0)) HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, n, R.active));
             vcycle<float>(R, 0);
             fill_faces<float>(R, 0, H->u32[0]->p);
         } else {
-            if (zero) HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, n, R.active));
+            if (zero && !R.streams(0)) HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, n, R.active));
             vcycle<double>(R, 0);
             fill_faces<double>(R, 0, H->u64[0]->p);
         }
@@ -1300,6 +1402,13 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         double* const norms1 = H->partials.p + 3 * (size_t)L0.ntcol;
         const int* first_nz = guess_nz;  // for the first residual only
         auto check = [&](bool fused) {  // residual of the current iterate, then the stop test
+            if (R.streamed) {  // the post-sweeps took all of its norms
+                HIPCHK(launch_norm_final(R.s, H->partials.p, R.streamed, H->fnorm.p));
+                HIPCHK(launch_batch_check(R.s, H->flags.p + 1, 1, H->fnorm.p, H->st.p, H->flags.p, H->hist.p,
+                                          H->hist.p + kHist, H->flags.p + 2));
+                R.streamed = 0;
+                return;
+            }
             if (!L0.push) fill_faces<double>(R, 0, u);
             R.pre(0, kStageResid);
             if (fused) {
@@ -1322,12 +1431,15 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         auto cycle = [&]() {  // returns whether its last level-0 sweep took the colour-1 norms
             if (P.precision == 0) {
                 R.fuse_norms = fusable ? norms1 : nullptr;
+                R.stream_norms = H->partials.p;
                 R.fused_sweep = false;
                 vcycle<double>(R, 0);
                 R.fuse_norms = nullptr;
+                R.stream_norms = nullptr;
                 return R.fused_sweep;
             } else {
-                HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, L0.nelem, R.active));
+                R.zero_top = true;
+                if (!R.streams(0)) HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, L0.nelem, R.active));
                 vcycle<float>(R, 0);
                 HIPCHK(launch_add_f32(R.s, R.grid(L0.walk()), u, H->u32[0]->p));
                 return false;
@@ -1447,7 +1559,8 @@ void hier_vcycle_from_zero(bxmg_ctx ctx, Hier* H, const bxmg_solve_params& P) {
     R.prof = &ctx->prof;
     R.lds_coarse = ctx->lds_coarse != 0;
     const Level& L0 = *H->L[0];
-    HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, L0.nelem));
+    R.zero_top = true;
+    if (!R.streams(0)) HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, L0.nelem));
     vcycle<double>(R, 0);
     ctx->prof.harvest();
 }

@@ -215,6 +215,41 @@ template <class T>
 hipError_t launch_gs(hipStream_t s, const Grid& g, T* u, const T* f, const T* beta, const FaceArrays<T>* fat,
                      int colour, double* norm_partials = nullptr);
 
+// The streaming smoother (bxmg_sweep.hip): two red-black sweeps of a one-box
+// constant-coefficient level, f and u read once, in blocks of XM pairs x TY
+// rows x ZC planes.
+enum SweepKind {
+    kSweepRestrict = 0,  // then the residual, restricted into the coarse level's f
+    kSweepPlain = 1,
+    kSweepNorm = 2,      // then the residual's norms, per block (FP64)
+};
+struct SweepArgs {
+    int n[3];          // cells of the level (even)
+    int per[3];
+    int H, GH, cs;     // its storage: half-row pitch, plane pitch, colour stride (elements)
+    int RM, RY;        // columns of a block with its halo: pairs, rows
+    int hm, hy;        // the halo: pairs, rows (0: the block spans the domain there)
+    int XM, TY, ZC;    // what a block owns
+    int nbx, nby, nbz;
+    int cH, cGH, ccs, cpar;  // the coarse level's storage; parity of its lower corner
+    int pid;           // problem slot of active[]
+    double h, a;
+};
+struct SweepPlan {
+    int nt = 0;        // threads per block: 256, 512 or 1024 (0: the level is not streamed)
+    int blocks = 0;
+    SweepArgs args{};
+};
+// The blocks of a level of n cells (storage and coarse fields of args unset).
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32);
+// uin (not read when zero: the sweeps start from u = 0) -> uout, another
+// array.  post: the sweeps after a prolongation that left colour 0 to them
+// (launch_prolong, only_c1); push: write uout's face ghosts too.  cf: the
+// coarse f (kSweepRestrict); partials: 3 per block (kSweepNorm).
+template <class T>
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, bool push, int kind, const T* uin,
+                        T* uout, const T* f, T* cf, double* partials, const int* active);
+
 // r = f - L u on both colours, optional store of r (R = T, or float for the
 // mixed-precision cast), partial norms (max|r|, sum r^2, bad count) at
 // 3 * (tile index).  colour0_only (FP64, buffer-addressed, no store): the

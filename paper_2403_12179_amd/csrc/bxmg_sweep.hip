@@ -1,0 +1,468 @@
+// Streaming smoother: two red-black sweeps of a one-box, constant-coefficient
+// level in one pass over its data, with the residual that follows them.
+//
+// One half-sweep per launch moves 1.5 arrays per half-sweep, 6 for the two
+// sweeps of a V(2,2) cycle and 2 more for the residual after them.  Here a
+// block owns a column of the domain (XM pairs x TY rows x ZC planes) and
+// walks it in z, plane by plane; each thread holds one x-pair (2m, 2m+1) of
+// one row.  At the step that loads plane q, the four half-sweeps and the
+// residual work on the planes behind it:
+//
+//   stage 1  colour 0 of plane q-1      stage 3  colour 0 of plane q-3
+//   stage 2  colour 1 of plane q-2      stage 4  colour 1 of plane q-4
+//   stage 5  the residual of plane q-5
+//
+// Every stage's z neighbours and own cells are in the thread's registers
+// (its column's last few planes); of its x and y neighbours one is the
+// thread's own other cell and three come from LDS, written there one step
+// earlier by the stage before (one barrier per step).  So u and f are read
+// once and u written once.  A block recomputes a halo around its own columns
+// (one layer per stage), reading u of one array and writing another: blocks
+// need nothing of each other.  The arithmetic of a cell, and the order of
+// its sums, are those of the one-colour kernel, so the results are bitwise
+// those of one launch per half-sweep: a ghost beyond a Dirichlet face holds
+// minus the cell's own value before the update (reading own registers), and
+// periodic columns wrap.
+//
+// Measured on the 256^3 FP64 Dirichlet level 0: two sweeps, residual and
+// restriction 183 us, against 4 x 50 + 66 us one launch each; a step's time
+// is split between LDS traffic (18 reads and 6 writes of a value per thread)
+// and FP64 issue (about 85 instructions per thread), which overlap little,
+// as a block's waves run the same phase of a step together.  The 256^3 solve
+// went from 8.73 to 7.78 ms, the 192^3 heat step from 4.50 to 4.00 ms.
+#include <hip/hip_runtime.h>
+#include <type_traits>
+
+#include <algorithm>
+
+#include "bxmg_device.h"
+
+namespace bxmg {
+
+namespace {
+
+// a / b for a loop-invariant b whose reciprocal is held in two parts,
+// 1/b = yh + yl: the estimate fma(a, yh, a yl) is within half an ulp and a
+// rounding of a/b, and the correction by its exact remainder then gives the
+// correctly rounded quotient (Markstein 1990) -- the IEEE division's bits,
+// in 4 dependent instructions instead of about 12.  (An infinite a gives NaN;
+// both end the solve as non-finite.)
+template <class T>
+struct Recip {
+    T b, yh, yl;
+    __device__ __forceinline__ explicit Recip(T d) : b(d), yh(T(1) / d), yl(fma_(-d, yh, T(1)) * yh) {}
+    static __device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
+    static __device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+    __device__ __forceinline__ T div(T a) const {
+        const T q = fma_(a, yh, a * yl);
+        return fma_(fma_(-q, b, a), yh, q);
+    }
+};
+
+// Barrier between LDS writers and readers of one step; global loads in
+// flight (the planes ahead) and stores are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <class T>
+struct Raw;
+template <>
+struct Raw<double> {
+    static __device__ __forceinline__ double ld(__amdgpu_buffer_rsrc_t r, int v, int s) {
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
+    }
+    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, int v, int s, double x) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, v, s, 0);
+    }
+};
+template <>
+struct Raw<float> {
+    static __device__ __forceinline__ float ld(__amdgpu_buffer_rsrc_t r, int v, int s) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
+    }
+    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, int v, int s, float x) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, v, s, 0);
+    }
+};
+
+}  // namespace
+
+// KIND (SweepKind): what follows the sweeps.  ZERO: they start from u = 0,
+// which is not read.  POST: the sweeps after a prolongation, which leaves
+// colour 0 to them: colour 0's old values, read only beside Dirichlet faces,
+// are minus the ghosts there.  PUSH: write the face ghosts of uout too.
+// NT: threads per block (columns of a block, halo included, at most NT).
+template <class T, int NT, bool ZERO, int KIND, bool POST, bool PUSH>
+__global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__ uin, T* __restrict__ uout,
+                                             const T* __restrict__ f, T* __restrict__ cf,
+                                             double* __restrict__ partials, const int* __restrict__ active) {
+    using std::integral_constant;
+    constexpr bool REST = KIND == kSweepRestrict, NORM = KIND == kSweepNorm;
+    constexpr bool RES = REST || NORM;
+    // LDS half planes (one colour of one plane of the block's columns)
+    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bS = 12, nBuf = REST ? 14 : RES ? 12 : 10;
+    __shared__ T lds[nBuf * NT];
+    if (active && !active[A.pid]) return;
+    const int tid = threadIdx.x;
+    // block -> (bx, by, bz), neighbouring blocks on one XCD
+    int blk = blockIdx.x;
+    {
+        const int nb = gridDim.x;
+        if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
+    }
+    const int bx = blk % A.nbx, byz = blk / A.nbx;
+    const int by = byz % A.nby, bz = byz / A.nby;
+    const int nm = A.n[0] >> 1, n1 = A.n[1], n2 = A.n[2];
+    const int ty = tid / A.RM, tm = tid - ty * A.RM;
+    // the thread's column: pair m of row y (raw: before periodic wrapping)
+    const int mr = bx * A.XM - A.hm + tm, yr = by * A.TY - A.hy + ty;
+    int m = mr, y = yr;
+    bool in = ty < A.RY;
+    if (A.per[0]) { m %= nm; m += m < 0 ? nm : 0; } else in = in && m >= 0 && m < nm;
+    if (A.per[1]) { y %= n1; y += y < 0 ? n1 : 0; } else in = in && y >= 0 && y < n1;
+    const bool own = in && tm >= A.hm && tm < A.hm + A.XM && mr < nm && ty >= A.hy && ty < A.hy + A.TY && yr < n1;
+    const bool perz = A.per[2] != 0;
+    // Dirichlet faces the column lies on
+    const bool fxl = in && !A.per[0] && m == 0, fxr = in && !A.per[0] && m == nm - 1;
+    const bool fyl = in && !A.per[1] && y == 0, fyr = in && !A.per[1] && y == n1 - 1;
+    const bool edge_xy = __ballot(fxl || fxr || fyl || fyr) != 0;
+    const int z0 = bz * A.ZC, zlim = min(z0 + A.ZC, n2);
+    // first plane loaded: the halo below, rounded to an even plane so that a
+    // step's plane parity is known at compile time
+    constexpr int kHalo = (RES ? 5 : 4) - (ZERO ? 1 : 0), kFirst = (kHalo + 1) & ~1;
+    const int zs = perz ? z0 - kFirst : max(0, z0 - kFirst);
+    const int zend = zlim + (REST ? 6 : RES ? 5 : 4);  // one past the last step
+    const int zmax = min(zlim + (RES ? 4 : 3), perz ? zlim + 4 : n2 - 1);  // last plane with values in use
+    // cells of the pair: in a plane of parity p, the colour-c cell is at
+    // x = 2m + o, o = (c + y + p) & 1; "A" offsets belong to o = yo, "B" ones
+    // to o = 1 - yo
+    const int yo = y & 1;
+    // LDS slots of the x neighbours of the pair's cells and of the rows beside
+    // (a neighbour outside the block's columns is never used by an own cell)
+    const bool wx = A.per[0] && A.hm == 0, wy = A.per[1] && A.hy == 0;
+    const int sl = tm > 0 ? tid - 1 : wx ? tid + A.RM - 1 : tid;
+    const int sr = tm < A.RM - 1 ? tid + 1 : wx ? tid - (A.RM - 1) : tid;
+    const int sdn = !in ? tid : ty > 0 ? tid - A.RM : wy ? tid + (A.RY - 1) * A.RM : tid;
+    const int sup = !in ? tid : ty < A.RY - 1 ? tid + A.RM : wy ? tid - (A.RY - 1) * A.RM : tid;
+    const int sxA = !in ? tid : yo ? sr : sl;
+    const int sxB = !in ? tid : yo ? sl : sr;
+    // the pair's cell on a Dirichlet x face, if any
+    const bool fxA = yo ? fxr : fxl, fxB = yo ? fxl : fxr;
+    const int es = (int)sizeof(T);
+    const int row = (y + 1) * A.H + m, co = A.cs * es, pl = A.GH * es;
+    const int vA = in ? (row + yo) * es : kOffPastBox, vB = in ? (row + 1 - yo) * es : kOffPastBox;
+    const int wA = own ? vA : kOffPastBox, wB = own ? vB : kOffPastBox;  // stores past the box are dropped
+    // POST: offset (from the plane's start) of an x or y ghost of the colour-0
+    // cell in planes of even and odd parity; past the box: none
+    int gA = kOffPastBox, gB = kOffPastBox;
+    if constexpr (POST) {
+        const int gy = fyl ? row - A.H : fyr ? row + A.H : 0;
+        const bool fy = fyl || fyr;
+        gA = fxA ? ((y + 1) * A.H + (yo ? nm : 0)) * es : fy ? (gy + yo) * es : kOffPastBox;
+        gB = fxB ? ((y + 1) * A.H + (yo ? 0 : nm)) * es : fy ? (gy + 1 - yo) * es : kOffPastBox;
+    }
+    const T h2 = (T)(A.h * A.h), ih2 = (T)(1.0 / (A.h * A.h));
+    const T sb = T(6) + (T)(A.a * (A.h * A.h));
+    const Recip<T> rsb(sb);
+    const int bytes = 2 * A.cs * es;
+    const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
+    const auto Rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, bytes, kBufferDword3);
+    const auto Ro = __builtin_amdgcn_make_buffer_rsrc((void*)uout, (short)0, bytes, kBufferDword3);
+
+    // the column's registers, indexed by plane modulo 8 (only a few of each
+    // are live): values of colour 0 (r) and 1 (b) after 0..4 half-sweeps
+    T r0[8], b0[8], r1[8], b2[8], r3[8], b4[8], fr[8], fb[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        r0[k] = T(0); b0[k] = T(0); r1[k] = T(0); b2[k] = T(0);
+        r3[k] = T(0); b4[k] = T(0); fr[k] = T(0); fb[k] = T(0);
+    }
+    T sprev = T(0), half = T(0);  // restriction: this row's pair sum, the even plane's sum of four
+    double mx = 0.0, s2 = 0.0, bad = 0.0;
+
+    // loads of plane q into ring slot PH (plane parity PH & 1)
+    auto load = [&](auto ph, int q) {
+        constexpr int PH = decltype(ph)::value;
+        int z = min(q, zmax);  // planes past the last one in use: any values
+        if (perz) {            // (twice: the halo may be wider than the domain)
+            z += z < 0 ? n2 : 0;
+            z += z < 0 ? n2 : 0;
+            z -= z >= n2 ? n2 : 0;
+            z -= z >= n2 ? n2 : 0;
+        }
+        const int zo = (z + 1) * pl;
+        const int vr = (PH & 1) ? vB : vA, vb = (PH & 1) ? vA : vB;
+        fr[PH] = Raw<T>::ld(Rf, vr, zo);
+        fb[PH] = Raw<T>::ld(Rf, vb, zo + co);
+        if constexpr (!ZERO) {
+            b0[PH] = Raw<T>::ld(Ru, vb, zo + co);
+            // colour 0's old value is read only through Dirichlet ghosts
+            const bool ez = !perz && (z == 0 || z == n2 - 1);
+            if (edge_xy || ez) {
+                if constexpr (POST) {
+                    const int g = (PH & 1) ? gB : gA;
+                    T v = Raw<T>::ld(Ru, g, zo + co);
+                    if (ez) {
+                        const T vz = Raw<T>::ld(Ru, vr, zo + co + (z == 0 ? -pl : pl));
+                        v = g == kOffPastBox ? vz : v;
+                    }
+                    r0[PH] = -v;
+                } else {
+                    r0[PH] = Raw<T>::ld(Ru, vr, zo);
+                }
+            }
+        }
+    };
+
+    auto step = [&](auto ph, auto edge, int q) {
+        constexpr int PH = decltype(ph)::value;
+        constexpr bool EDGE = decltype(edge)::value;
+#define RS(d) ((PH - (d) + 16) & 7)   /* ring slot of plane q - d */
+#define ISA(d, c) ((((c) + PH - (d)) & 1) == 0)  /* its colour-c cell is at o = yo */
+        struct Three { T x, d, u; };
+        auto near = [&](int buf, bool isA) {
+            const T* hp = lds + buf * NT;
+            return Three{hp[isA ? sxA : sxB], hp[sdn], hp[sup]};
+        };
+        // neighbour sum of the colour-c cell of plane q - D: own_o = the
+        // pair's other cell; oldv = the cell's own value before the update
+        // (x- + x+ commutes, so the own cell's side does not matter)
+        auto sum = [&](auto dd, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
+            constexpr int D = decltype(dd)::value;
+            if constexpr (EDGE) {
+                const T g = -oldv;
+                n.x = (isA ? fxA : fxB) ? g : n.x;
+                n.d = fyl ? g : n.d;
+                n.u = fyr ? g : n.u;
+                zm = !perz && q == D ? g : zm;
+                zp = !perz && q == D + n2 - 1 ? g : zp;
+            }
+            return ((own_o + n.x) + (n.d + n.u)) + (zm + zp);
+        };
+        // every LDS value of the step, written in earlier steps
+        Three t1{}, t2, t3, t4, t5r{}, t5b{};
+        T spart = T(0);
+        if constexpr (!ZERO) t1 = near(bB0 + ((PH - 1) & 1), ISA(1, 0));
+        t2 = near(bR1 + ((PH - 1) & 1), ISA(2, 1));
+        t3 = near(bB2 + ((PH - 1) & 1), ISA(3, 0));
+        t4 = near(bR3 + ((PH - 1) & 3), ISA(4, 1));
+        if constexpr (RES) {
+            t5r = near(bB4 + ((PH - 1) & 1), ISA(5, 0));
+            t5b = near(bR3 + ((PH - 2) & 3), ISA(5, 1));
+        }
+        if constexpr (REST) spart = lds[(bS + ((PH - 1) & 1)) * NT + sup];
+        // plane q enters: colour 1 for stage 1's neighbours
+        if constexpr (!ZERO) lds[(bB0 + (PH & 1)) * NT + tid] = b0[RS(0)];
+        {  // stage 1
+            T su = T(0);
+            if constexpr (!ZERO)
+                su = sum(integral_constant<int, 1>(), ISA(1, 0), b0[RS(1)], t1, b0[RS(2)], b0[RS(0)], r0[RS(1)]);
+            r1[RS(1)] = rsb.div(su - h2 * fr[RS(1)]);
+            lds[(bR1 + (PH & 1)) * NT + tid] = r1[RS(1)];
+        }
+        {  // stage 2
+            const T su = sum(integral_constant<int, 2>(), ISA(2, 1), r1[RS(2)], t2, r1[RS(3)], r1[RS(1)],
+                             ZERO ? T(0) : b0[RS(2)]);
+            b2[RS(2)] = rsb.div(su - h2 * fb[RS(2)]);
+            lds[(bB2 + (PH & 1)) * NT + tid] = b2[RS(2)];
+        }
+        {  // stage 3
+            const T su = sum(integral_constant<int, 3>(), ISA(3, 0), b2[RS(3)], t3, b2[RS(4)], b2[RS(2)], r1[RS(3)]);
+            r3[RS(3)] = rsb.div(su - h2 * fr[RS(3)]);
+            lds[(bR3 + (PH & 3)) * NT + tid] = r3[RS(3)];
+        }
+        {  // stage 4
+            const T su = sum(integral_constant<int, 4>(), ISA(4, 1), r3[RS(4)], t4, r3[RS(5)], r3[RS(3)], b2[RS(4)]);
+            b4[RS(4)] = rsb.div(su - h2 * fb[RS(4)]);
+            if constexpr (RES) lds[(bB4 + (PH & 1)) * NT + tid] = b4[RS(4)];
+        }
+        {  // plane q-4 is final
+            const int p = q - 4;
+            const bool mine = p >= z0 && p < zlim;
+            const int zo = (p + 1) * pl;
+            const int vr = (PH & 1) ? wB : wA, vb = (PH & 1) ? wA : wB;
+            Raw<T>::st(Ro, mine ? vr : kOffPastBox, zo, r3[RS(4)]);
+            Raw<T>::st(Ro, mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
+        }
+        if constexpr (RES) {  // stage 5
+            const T sur =
+                sum(integral_constant<int, 5>(), ISA(5, 0), b4[RS(5)], t5r, b4[RS(6)], b4[RS(4)], r3[RS(5)]);
+            const T rr = fr[RS(5)] - (sur - sb * r3[RS(5)]) * ih2;
+            const T sub =
+                sum(integral_constant<int, 5>(), ISA(5, 1), r3[RS(5)], t5b, r3[RS(6)], r3[RS(4)], b4[RS(5)]);
+            const T rb = fb[RS(5)] - (sub - sb * b4[RS(5)]) * ih2;
+            if constexpr (NORM) {
+                const int p = q - 5;
+                if (own && p >= z0 && p < zlim) {
+                    acc_norm((double)rr, mx, s2, bad);
+                    acc_norm((double)rb, mx, s2, bad);
+                }
+            } else {
+                // the four residuals of this row pair in plane q-6 (the
+                // partner's sum arrived with the last barrier), then this
+                // row's sum for the next step
+                const T four = sprev + spart;
+                if constexpr (((PH - 6) & 1) == 0) {
+                    half = four;
+                } else {
+                    const int p = q - 6;
+                    if (own && !(y & 1) && p >= z0 && p < zlim) {
+                        const int J = y >> 1, K = p >> 1;
+                        const int c = (m + J + K + A.cpar) & 1;
+                        cf[(long long)c * A.ccs + (long long)(K + 1) * A.cGH + (J + 1) * A.cH + ((m + 1) >> 1)] =
+                            (half + four) * T(0.125);
+                    }
+                }
+                sprev = rr + rb;  // even x + odd x: which colour is which commutes
+                lds[(bS + (PH & 1)) * NT + tid] = sprev;
+            }
+        }
+        if constexpr (PUSH) {  // the face ghosts that mirror plane q-4's cells
+            const int p = q - 4;
+            const bool fz = p == 0 || p == n2 - 1;
+            if (own && p >= z0 && p < zlim && (fz || m == 0 || m == nm - 1 || y == 0 || y == n1 - 1)) {
+                const int zo = (p + 1) * pl, rb = (y + 1) * A.H;
+                auto ghost = [&](bool per, T v, int c, int image, int below, int zi, int zb) {
+                    // the periodic image (same colour) or the ghost beyond (the other colour)
+                    if (per) Raw<T>::st(Ro, image * es, zi + (c ? co : 0), v);
+                    else Raw<T>::st(Ro, below * es, zb + (c ? 0 : co), -v);
+                };
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const T v = c ? b4[RS(4)] : r3[RS(4)];
+                    const int o = (c + y + PH) & 1, xs = m + o;  // slot of x = 2m + o in its row
+                    if (m == 0 && o == 0) ghost(A.per[0], v, c, rb + nm, rb, zo, zo);
+                    if (m == nm - 1 && o == 1) ghost(A.per[0], v, c, rb, rb + nm, zo, zo);
+                    if (y == 0) ghost(A.per[1], v, c, (n1 + 1) * A.H + xs, xs, zo, zo);
+                    if (y == n1 - 1) ghost(A.per[1], v, c, xs, (n1 + 1) * A.H + xs, zo, zo);
+                    if (p == 0) ghost(perz, v, c, rb + xs, rb + xs, (n2 + 1) * pl, 0);
+                    if (p == n2 - 1) ghost(perz, v, c, rb + xs, rb + xs, 0, (n2 + 1) * pl);
+                }
+            }
+        }
+#undef RS
+#undef ISA
+    };
+
+    load(integral_constant<int, 0>(), zs);
+    load(integral_constant<int, 1>(), zs + 1);
+    for (int qb = zs;; qb += 8) {
+#define BXMG_STEP(PH)                                                                          \
+    {                                                                                          \
+        const int q = qb + PH;                                                                 \
+        if (q >= zend) break;                                                                  \
+        load(integral_constant<int, (PH + 2) & 7>(), q + 2);                                   \
+        if (edge_xy || (!perz && (q <= 5 || q >= n2))) step(integral_constant<int, PH>(), std::true_type(), q); \
+        else step(integral_constant<int, PH>(), std::false_type(), q);                         \
+        lds_barrier();                                                                         \
+    }
+        BXMG_STEP(0) BXMG_STEP(1) BXMG_STEP(2) BXMG_STEP(3)
+        BXMG_STEP(4) BXMG_STEP(5) BXMG_STEP(6) BXMG_STEP(7)
+#undef BXMG_STEP
+    }
+    if constexpr (NORM) {
+        double* sh = (double*)lds;  // every LDS read ended with the last barrier
+        block_reduce3(mx, s2, bad, sh);
+        if (tid == 0) {
+            partials[3 * (size_t)blk] = mx;
+            partials[3 * (size_t)blk + 1] = s2;
+            partials[3 * (size_t)blk + 2] = bad;
+        }
+    }
+}
+
+// Blocks of a level: every split of its rows and planes into blocks of at
+// most 1024 columns is priced as (rounds of blocks over the 256 CUs) x (steps
+// of a block) x (time of a step), a step being latency-bound with few waves
+// on a CU and issue-bound with many; the cheapest is taken.
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32) {
+    SweepPlan best;
+    const int halo = (kind == kSweepPlain ? 4 : 5) - (zero ? 1 : 0);
+    const int lead = ((halo + 1) & ~1) + (kind == kSweepRestrict ? 6 : kind == kSweepNorm ? 5 : 4);
+    const int nm = n[0] / 2;
+    // (the FP64 forms keep up to 168 registers a thread: at most 12 waves)
+    const int ntmax = f32 ? 1024 : 768;
+    double cost = 1e30;
+    auto split = [](int cells, int pieces, int unit) {  // the size of equal pieces, a multiple of unit
+        const int u = cells / unit, q = (u + pieces - 1) / pieces;
+        return q * unit;
+    };
+    for (int px = 1; px <= nm; ++px) {
+        const int XM = split(nm, px, 1);
+        if (XM < 8 && px > 1) break;
+        const bool wx = XM == nm;
+        const int hm = wx ? 0 : (halo + 1) / 2, RM = XM + 2 * hm;
+        if (RM > ntmax) continue;
+        for (int py = 1; py <= n[1] / 2; ++py) {
+            const int TY = split(n[1], py, 2);
+            const bool wy = TY == n[1];
+            const int hy = wy ? 0 : halo, RY = TY + 2 * hy;
+            const int cols = RM * RY;
+            if (cols > ntmax) continue;
+            const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : cols <= 768 ? 768 : 1024;
+            const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
+            const int fit = nt == 256 ? 5 : nt == 512 ? 2 : 1;  // blocks a CU holds (registers)
+            for (int pz = 1; pz <= n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
+                const int ZC = split(n[2], pz, 2);
+                const int nbz = (n[2] + ZC - 1) / ZC;
+                const long long blocks = (long long)nbx * nby * nbz;
+                const long long per_cu = (blocks + 255) / 256;
+                const long long rounds = (per_cu + fit - 1) / fit;
+                const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
+                const double step = std::max(1000.0, 300.0 + (f32 ? 110.0 : 130.0) * waves);
+                const double c = rounds * (ZC + lead) * step + 1e-3 * blocks;
+                if (c < cost) {
+                    cost = c;
+                    best.nt = nt;
+                    best.blocks = (int)blocks;
+                    SweepArgs& A = best.args;
+                    A.RM = RM; A.RY = RY; A.hm = hm; A.hy = hy;
+                    A.XM = XM; A.TY = TY; A.ZC = ZC;
+                    A.nbx = nbx; A.nby = nby; A.nbz = nbz;
+                }
+                if (ZC == 2) break;
+            }
+            if (TY == 2) break;
+        }
+    }
+    for (int d = 0; d < 3; ++d) { best.args.n[d] = n[d]; best.args.per[d] = per[d]; }
+    return best;
+}
+
+template <class T>
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, bool push, int kind, const T* uin,
+                        T* uout, const T* f, T* cf, double* partials, const int* active) {
+    const dim3 G((unsigned)P.blocks);
+#define BXMG_SW(NT, ZERO, KIND, POST, PUSH)                                                                     \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, PUSH>), G, dim3(NT), 0, s, P.args, uin, uout, f, cf, \
+                       partials, active)
+#define BXMG_SWN(ZERO, KIND, POST, PUSH)               \
+    if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST, PUSH); \
+    else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST, PUSH); \
+    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST, PUSH); \
+    else if constexpr (sizeof(T) == 4) BXMG_SW(1024, ZERO, KIND, POST, PUSH); \
+    else return hipErrorInvalidValue
+    if (kind == kSweepRestrict && !post && !push) {
+        if (zero) { BXMG_SWN(true, kSweepRestrict, false, false); }
+        else { BXMG_SWN(false, kSweepRestrict, false, false); }
+    } else if (kind == kSweepNorm && post && push && std::is_same<T, double>::value) {
+        if constexpr (std::is_same<T, double>::value) { BXMG_SWN(false, kSweepNorm, true, true); }
+    } else if (kind == kSweepPlain && post) {
+        if (push) { BXMG_SWN(false, kSweepPlain, true, true); } else { BXMG_SWN(false, kSweepPlain, true, false); }
+    } else {
+        return hipErrorInvalidValue;
+    }
+#undef BXMG_SWN
+#undef BXMG_SW
+    return hipGetLastError();
+}
+template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, bool, int, const double*, double*,
+                                         const double*, double*, double*, const int*);
+template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, bool, int, const float*, float*,
+                                        const float*, float*, double*, const int*);
+
+}  // namespace bxmg
