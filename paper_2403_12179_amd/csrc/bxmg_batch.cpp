@@ -365,8 +365,8 @@ struct bxmg_batch_s {
     DevVec<CoarseCycle<double>> cc64;
     DevVec<CoarseCycle<float>> cc32;
     int ncc = 0;
-    int cc_lds = 0;  // dynamic LDS of the coarse-cycle launch
-    bool cc_all_lds = false;  // every member's coarse levels fit in LDS
+    int cc_lds = 0, cc_bottom = 0;  // dynamic LDS of the two forms of the coarse cycle
+    bool cc_fast = false;  // every member takes the register and LDS form
     bool use_graph = true;
     int stable = 0;         // launches since the running set last changed
     bool inflight = false;  // cycles launched and not yet collected
@@ -592,22 +592,26 @@ void rebuild(bxmg_batch_s* b) {
             }
         }
     // fused coarse cycles (dynamic LDS: the largest need of a member)
-    b->cc_lds = 0;
-    b->cc_all_lds = true;
+    b->cc_lds = b->cc_bottom = 0;
+    b->cc_fast = b->ctx->lds_coarse != 0;
+    auto layout = [&](auto& cc) {
+        const int fast = coarse_fast_layout(cc);
+        b->cc_fast = b->cc_fast && fast > 0;
+        b->cc_lds = std::max(b->cc_lds, fast);
+        b->cc_bottom = std::max(b->cc_bottom, coarse_bottom_lds(cc));
+    };
     if (b->prec == 0) {
         std::vector<CoarseCycle<double>> cc;
         for (int s : b->members) {
             cc.push_back(coarse_desc<double>(b, *b->slots[s], b->u64.p, b->f64.p, b->fa64.p));
-            b->cc_lds = std::max(b->cc_lds, coarse_lds_layout<double>(cc.back(), b->ctx->lds_coarse));
-            b->cc_all_lds = b->cc_all_lds && cc.back().lds;
+            layout(cc.back());
         }
         b->cc64.assign(cc);
     } else {
         std::vector<CoarseCycle<float>> cc;
         for (int s : b->members) {
             cc.push_back(coarse_desc<float>(b, *b->slots[s], b->u32.p, b->f32.p, b->fa32.p));
-            b->cc_lds = std::max(b->cc_lds, coarse_lds_layout<float>(cc.back(), b->ctx->lds_coarse));
-            b->cc_all_lds = b->cc_all_lds && cc.back().lds;
+            layout(cc.back());
         }
         b->cc32.assign(cc);
     }
@@ -693,7 +697,8 @@ void b_vcycle(bxmg_batch_s* b, hipStream_t s) {
         // (cells and the face ghosts mirroring them)
         HIPCHK(launch_resid_restrict<T>(s, level_xgrid(b, l), u, f, arena_beta<T>(b, l), level_fat<T>(b, l), f, u));
     }
-    HIPCHK(launch_coarse_cycle<T>(s, coarse_descs<T>(b), b->ncc, b->active.p, b->var, b->cc_lds, b->cc_all_lds));
+    if (b->cc_fast) HIPCHK(launch_coarse_fast<T>(s, coarse_descs<T>(b), b->ncc, b->active.p, b->var, b->cc_lds));
+    else HIPCHK(launch_coarse_cycle<T>(s, coarse_descs<T>(b), b->ncc, b->active.p, b->var, b->cc_bottom));
     for (int l = b->lmax - 1; l >= 0; --l) {
         BLevel& B = b->lev[l];
         // small one-box coarse levels: the staged prolongation reads the

@@ -9,6 +9,24 @@ constexpr int kBufferDword3 = 0x00020000;  // raw buffer, gfx9 data format
 // A byte offset beyond every box resource (their sizes stay below 2^31 bytes).
 constexpr int kOffPastBox = (int)0x80000000u;
 
+// a / b for a loop-invariant b whose reciprocal is held in two parts,
+// 1/b = yh + yl: the estimate fma(a, yh, a yl) is within half an ulp and a
+// rounding of a/b, and the correction by its exact remainder then gives the
+// correctly rounded quotient (Markstein 1990) -- the IEEE division's bits,
+// in 4 dependent instructions instead of about 12.  (An infinite a gives NaN;
+// both end the solve as non-finite.)
+template <class T>
+struct Recip {
+    T b, yh, yl;
+    __device__ __forceinline__ explicit Recip(T d) : b(d), yh(T(1) / d), yl(fma_(-d, yh, T(1)) * yh) {}
+    static __device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
+    static __device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+    __device__ __forceinline__ T div(T a) const {
+        const T q = fma_(a, yh, a * yl);
+        return fma_(fma_(-q, b, a), yh, q);
+    }
+};
+
 // Fixed-tree block reduction of (max, sum, sum): wave64 butterflies, then
 // the 4 wave results in order.  The result is valid in thread 0.
 __device__ __forceinline__ void block_reduce3(double& mx, double& s2, double& bad, double* sh) {

@@ -134,7 +134,6 @@ struct Hier {
     DevBuf<CoarseCycle<float>> cc32;
     CoarseCycle<double> cc64_host{};   // ... and what they hold
     CoarseCycle<float> cc32_host{};
-    int cc64_lds = 0, cc32_lds = 0;    // dynamic LDS of the coarse-cycle launch
     DevBuf<double> partials;  // 3 per tile of the largest tiled launch, + 3
     DevBuf<double> fnorm;     // 3
     // the solve's stop test on the device (the batch engine's, one slot):
@@ -565,28 +564,21 @@ CoarseCycle<float>& cc_host<float>(Hier* H) { return H->cc32_host; }
 
 // the fused coarse cycle; its descriptor is uploaded when the settings change
 template <class T>
-int& cc_lds(Hier* H);
-template <>
-int& cc_lds<double>(Hier* H) { return H->cc64_lds; }
-template <>
-int& cc_lds<float>(Hier* H) { return H->cc32_lds; }
-
-template <class T>
 void coarse_cycle(Run& R) {
     Hier* H = R.H;
     static_assert(std::is_trivially_copyable<CoarseCycle<T>>::value, "descriptor must be plain data");
     DevBuf<CoarseCycle<T>>& buf = cc_buf<T>(H);
     CoarseCycle<T>& host = cc_host<T>(H);
     CoarseCycle<T> cc = coarse_desc<T>(H, R.nu1, R.nu2, R.prolong, R.bottom_rtol);
-    const int lds = coarse_lds_layout<T>(cc, R.lds_coarse);
+    const int fast = R.lds_coarse ? coarse_fast_layout<T>(cc) : 0;
     if (!buf.p || std::memcmp(&cc, &host, sizeof cc) != 0) {
         if (!buf.p) buf.alloc(1);
         host = cc;  // lives as long as the hierarchy: safe source for the async copy
-        cc_lds<T>(H) = lds;
         HIPCHK(hipMemcpyAsync(buf.p, &host, sizeof host, hipMemcpyHostToDevice, R.s));
     }
-    // (the kernel zeroes the top level's correction itself)
-    HIPCHK(launch_coarse_cycle<T>(R.s, buf.p, 1, R.active, H->var, cc_lds<T>(H), host.lds != 0));
+    // (the kernels zero the top level's correction themselves)
+    if (fast) HIPCHK(launch_coarse_fast<T>(R.s, buf.p, 1, R.active, H->var, fast));
+    else HIPCHK(launch_coarse_cycle<T>(R.s, buf.p, 1, R.active, H->var, coarse_bottom_lds<T>(cc)));
 }
 
 template <class T>

@@ -157,18 +157,29 @@ struct CoarseLevel {
 
 constexpr int kMaxCoarseLevels = 8;
 
+// What k_coarse_fast needs of them (coarse_fast_layout fills it).
+template <class T>
+struct CoarseGeom {
+    double h[kMaxCoarseLevels];
+    double a, rtol;
+    const T* c[kMaxCoarseLevels][3];  // face coefficients (nullptr: constant)
+    T* u;                             // the top level's storage ...
+    const T* f;
+    int* iters;
+    int n[kMaxCoarseLevels][3];
+    int per[3];
+    int nlev, nu1, nu2, prolong, pid;
+    int H, GH, cs, par;               // ... its pitches, colour stride and corner parity
+};
+
 // The levels of the fused coarse cycle, finest first; the last is the bottom.
 template <class T>
 struct CoarseCycle {
+    CoarseGeom<T> g;
     int nlev;
     int nu1, nu2, prolong;
     int per[3];
     int pid;  // problem slot (checked against the active flags of a batch)
-    // lds != 0: u and f of level m live at byte offsets lds_u[m], lds_f[m] of
-    // the workgroup's dynamic LDS; the bottom CG's vectors at bot_off
-    int lds;
-    int lds_u[kMaxCoarseLevels], lds_f[kMaxCoarseLevels];
-    int bot_off;
     double rtol;
     int* iters;
     CoarseLevel<T> L[kMaxCoarseLevels];
@@ -351,18 +362,22 @@ hipError_t launch_bottom(hipStream_t s, T* u, const T* f, FaceArrays<T> fa, bool
                          double rtol, int* iters_out);
 
 // the fused coarse V-cycle, one workgroup per descriptor cc[0..n); with
-// active != nullptr a descriptor whose problem slot is inactive is skipped;
-// lds_bytes: dynamic LDS per workgroup (the largest descriptor's need);
-// levels_lds: every descriptor has cc.lds set -- the levels then live in
-// LDS, otherwise all of them run from device memory (same values either way).
-// The cycle zeroes its top level's u itself.
+// active != nullptr a descriptor whose problem slot is inactive is skipped.
+// The cycle zeroes its top level's u itself.  launch_coarse_fast keeps the
+// levels in registers and LDS (bxmg_coarse.hip; lds_bytes: the largest of
+// coarse_fast_layout over the descriptors, all of them non-zero);
+// launch_coarse_cycle works on device memory (lds_bytes: the largest of
+// coarse_bottom_lds).
+template <class T>
+hipError_t launch_coarse_fast(hipStream_t s, const CoarseCycle<T>* cc, int n, const int* active, bool var,
+                              int lds_bytes);
+template <class T>
+int coarse_fast_layout(CoarseCycle<T>& cc);
 template <class T>
 hipError_t launch_coarse_cycle(hipStream_t s, const CoarseCycle<T>* cc, int n, const int* active, bool var,
-                               int lds_bytes, bool levels_lds);
-// LDS layout of a coarse cycle (sets cc.lds, offsets, bot_off); returns the
-// bytes it needs.  Levels go to LDS when everything fits in lds_limit_bytes().
+                               int lds_bytes);
 template <class T>
-int coarse_lds_layout(CoarseCycle<T>& cc, bool allow_levels);
+int coarse_bottom_lds(const CoarseCycle<T>& cc);
 
 // ---------------------------------------------------------------- batches
 constexpr int kStatusNoConv = -4;     // = BXMG_ENOCONV

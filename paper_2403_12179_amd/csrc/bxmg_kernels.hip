@@ -2086,27 +2086,17 @@ __global__ void __launch_bounds__(kBotThreads) k_bottom(T* __restrict__ u, const
 // of the coarse level, prolongation, post-smoothing), each a block-strided
 // loop closed by a barrier.  Launch latency, not bandwidth, bounds these
 // levels, so one launch replaces some 20 per level.
-// Level storage of the fused coarse cycle, by 32-bit element offsets (the
-// levels hold at most kMaxBottomCells cells): LDS through an address-space-3
-// pointer, so the compiler emits LDS instructions rather than flat ones, or
-// device memory.
-template <class T, bool LDS>
-struct LvMem;
+// This form works on device memory: the fallback where the levels are asked
+// to stay there.
 template <class T>
-struct LvMem<T, true> {
-    __attribute__((address_space(3))) T* p;
-    __device__ __forceinline__ T ld(int e) const { return p[e]; }
-    __device__ __forceinline__ void st(int e, T v) const { p[e] = v; }
-};
-template <class T>
-struct LvMem<T, false> {
+struct LvMem {
     T* p;
     __device__ __forceinline__ T ld(int e) const { return p[e]; }
     __device__ __forceinline__ void st(int e, T v) const { p[e] = v; }
 };
 
-template <class T, bool LDS>
-__device__ void blk_fill(const LvMem<T, LDS>& u, const GhostCopy* __restrict__ list, long long n) {
+template <class T>
+__device__ void blk_fill(const LvMem<T>& u, const GhostCopy* __restrict__ list, long long n) {
     for (int g = threadIdx.x; g < (int)n; g += blockDim.x) {
         const GhostCopy pc = list[g];
         const T v = u.ld((int)(pc.src & 0x7fffffffu));
@@ -2215,18 +2205,15 @@ __device__ __forceinline__ void blk_push(const M& U, const RBox& B, int i, int j
         }
 }
 
-// A level of the coarse cycle: its descriptor and its u and f (LDS or device
-// memory), with generic pointers for the bottom solver.
-template <class T, bool LDS>
+// A level of the coarse cycle: its descriptor and its u and f.
+template <class T>
 struct LevelData {
     const CoarseLevel<T>& L;
-    LvMem<T, LDS> u, f;
-    T* ug;
-    T* fg;
+    LvMem<T> u, f;
 };
 
-template <class T, int MODE, bool LDS>
-__device__ void blk_gs(const LevelData<T, LDS>& D, int colour) {
+template <class T, int MODE>
+__device__ void blk_gs(const LevelData<T>& D, int colour) {
     const RBox& B = D.L.box;
     const BoxCells bc = box_cells(B);
     const T h2 = (T)(D.L.h * D.L.h);
@@ -2246,8 +2233,8 @@ __device__ void blk_gs(const LevelData<T, LDS>& D, int colour) {
     __syncthreads();
 }
 
-template <class T, int MODE, bool LDS>
-__device__ void blk_smooth(const LevelData<T, LDS>& D, int nsweeps) {
+template <class T, int MODE>
+__device__ void blk_smooth(const LevelData<T>& D, int nsweeps) {
     for (int s = 0; s < nsweeps; ++s)
         for (int c = 0; c < 2; ++c) {
             if (!D.L.push) blk_fill(D.u, D.L.face[c ^ 1], D.L.nface[c ^ 1]);
@@ -2255,8 +2242,8 @@ __device__ void blk_smooth(const LevelData<T, LDS>& D, int nsweeps) {
         }
 }
 
-template <class T, int MODE, bool LDS>
-__device__ void blk_resid_restrict(const LevelData<T, LDS>& F, const LevelData<T, LDS>& C) {
+template <class T, int MODE>
+__device__ void blk_resid_restrict(const LevelData<T>& F, const LevelData<T>& C) {
     const RBox& B = F.L.box;
     const int cnx = (B.hi[0] - B.lo[0] + 1) >> 1, cny = (B.hi[1] - B.lo[1] + 1) >> 1, cnz = (B.hi[2] - B.lo[2] + 1) >> 1;
     const int n = cnx * cny * cnz;
@@ -2286,30 +2273,14 @@ __device__ void blk_resid_restrict(const LevelData<T, LDS>& F, const LevelData<T
     __syncthreads();
 }
 
-template <class T, bool LDS>
-__device__ void blk_zero(const LvMem<T, LDS>& u, long long n) {
+template <class T>
+__device__ void blk_zero(const LvMem<T>& u, long long n) {
     for (int g = threadIdx.x; g < (int)n; g += blockDim.x) u.st(g, T(0));
     __syncthreads();
 }
 
-// four elements per thread and step, loaded before any is stored (a copy
-// from device memory waits for one load's latency per step, not per element)
-template <class T, bool LD, bool LS>
-__device__ void blk_copy(const LvMem<T, LD>& dst, const LvMem<T, LS>& src, long long n) {
-    const int bs = blockDim.x, ni = (int)n;
-    for (int g0 = threadIdx.x; g0 < ni; g0 += 4 * bs) {
-        T v[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) v[m] = g0 + m * bs < ni ? src.ld(g0 + m * bs) : T(0);
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-            if (g0 + m * bs < ni) dst.st(g0 + m * bs, v[m]);
-    }
-    __syncthreads();
-}
-
-template <class T, bool LDS>
-__device__ void blk_prolong(const LevelData<T, LDS>& C, const LevelData<T, LDS>& F, int order) {
+template <class T>
+__device__ void blk_prolong(const LevelData<T>& C, const LevelData<T>& F, int order) {
     const RBox& B = F.L.box;
     const RBox& Q = C.L.box;
     const BoxCells bc = box_cells(B);
@@ -2340,32 +2311,15 @@ __device__ void blk_prolong(const LevelData<T, LDS>& C, const LevelData<T, LDS>&
     __syncthreads();
 }
 
-// The fused coarse V-cycle of one problem per workgroup.  LDS: the levels'
-// u and f live in LDS for the whole cycle (they are scratch below the top
-// level); the top level's f is read at the start and its u, the correction,
-// written back at the end.  Otherwise they stay in device memory.  Either
-// way the cycle starts by zeroing the top level's u.
-template <class T, int MODE, bool LDS>
+// The fused coarse V-cycle of one problem per workgroup.
+template <class T, int MODE>
 __global__ void __launch_bounds__(kBotThreads) k_coarse_cycle(const CoarseCycle<T>* __restrict__ ccs,
                                                              const int* __restrict__ active) {
-    typedef __attribute__((address_space(3))) T lds_T;
     const CoarseCycle<T>& cc = ccs[blockIdx.x];
     if (active && !active[cc.pid]) return;
     const int nl = cc.nlev;
-    auto lev = [&](int m) {
-        if constexpr (LDS) {
-            T* ug = (T*)(bxmg_lds + cc.lds_u[m]);
-            T* fg = (T*)(bxmg_lds + cc.lds_f[m]);
-            return LevelData<T, true>{cc.L[m], {(lds_T*)ug}, {(lds_T*)fg}, ug, fg};
-        } else {
-            return LevelData<T, false>{cc.L[m], {cc.L[m].u}, {cc.L[m].f}, cc.L[m].u, cc.L[m].f};
-        }
-    };
-    {
-        const auto top = lev(0);
-        blk_zero(top.u, cc.L[0].nelem);
-        if constexpr (LDS) blk_copy(top.f, LvMem<T, false>{cc.L[0].f}, cc.L[0].nelem);
-    }
+    auto lev = [&](int m) { return LevelData<T>{cc.L[m], {cc.L[m].u}, {cc.L[m].f}}; };
+    blk_zero(lev(0).u, cc.L[0].nelem);
     for (int l = 0; l + 1 < nl; ++l) {
         const auto F = lev(l), C = lev(l + 1);
         blk_smooth<T, MODE>(F, cc.nu1);
@@ -2388,11 +2342,11 @@ __global__ void __launch_bounds__(kBotThreads) k_coarse_cycle(const CoarseCycle<
         G.nboxes = 1;
         G.a = Lb.box.a;
         const int N = G.n[0] * G.n[1] * G.n[2];
-        BottomLds S(bxmg_lds + cc.bot_off, N, (G.n[0] + 2) * (G.n[1] + 2) * (G.n[2] + 2));
+        BottomLds S(bxmg_lds, N, (G.n[0] + 2) * (G.n[1] + 2) * (G.n[2] + 2));
         if (N <= kWaveBottomCells) {
-            if (threadIdx.x < 64) bottom_cg_wave<T, MODE == 2>(Db.ug, Db.fg, Lb.fa, &Lb.box, G, Lb.h, cc.rtol, cc.iters, S);
+            if (threadIdx.x < 64) bottom_cg_wave<T, MODE == 2>(Db.u.p, Db.f.p, Lb.fa, &Lb.box, G, Lb.h, cc.rtol, cc.iters, S);
         } else {
-            bottom_cg<T, MODE == 2>(Db.ug, Db.fg, Lb.fa, &Lb.box, G, Lb.h, cc.rtol, cc.iters, S);
+            bottom_cg<T, MODE == 2>(Db.u.p, Db.f.p, Lb.fa, &Lb.box, G, Lb.h, cc.rtol, cc.iters, S);
         }
         __syncthreads();
     }
@@ -2402,7 +2356,6 @@ __global__ void __launch_bounds__(kBotThreads) k_coarse_cycle(const CoarseCycle<
         blk_prolong(C, F, cc.prolong);
         blk_smooth<T, MODE>(F, cc.nu2);
     }
-    if constexpr (LDS) blk_copy(LvMem<T, false>{cc.L[0].u}, lev(0).u, cc.L[0].nelem);
 }
 
 // ================================================================ launchers
@@ -2421,29 +2374,13 @@ int lds_limit_bytes() {
 }
 
 template <class T>
-int coarse_lds_layout(CoarseCycle<T>& cc, bool allow_levels) {
+int coarse_bottom_lds(const CoarseCycle<T>& cc) {
     const RBox& B = cc.L[cc.nlev - 1].box;
     const int n0 = B.hi[0] - B.lo[0] + 1, n1 = B.hi[1] - B.lo[1] + 1, n2 = B.hi[2] - B.lo[2] + 1;
-    const size_t bot = bottom_lds_bytes(n0 * n1 * n2, (n0 + 2) * (n1 + 2) * (n2 + 2));
-    auto a16 = [](size_t x) { return (x + 15) / 16 * 16; };
-    size_t off = 0;
-    for (int m = 0; m < cc.nlev; ++m) {
-        cc.lds_u[m] = (int)off;
-        off += a16((size_t)cc.L[m].nelem * sizeof(T));
-        cc.lds_f[m] = (int)off;
-        off += a16((size_t)cc.L[m].nelem * sizeof(T));
-    }
-    if (allow_levels && off + bot <= (size_t)lds_limit_bytes()) {
-        cc.lds = 1;
-        cc.bot_off = (int)off;
-        return (int)(off + bot);
-    }
-    cc.lds = 0;
-    cc.bot_off = 0;
-    return (int)bot;
+    return (int)bottom_lds_bytes(n0 * n1 * n2, (n0 + 2) * (n1 + 2) * (n2 + 2));
 }
-template int coarse_lds_layout<double>(CoarseCycle<double>&, bool);
-template int coarse_lds_layout<float>(CoarseCycle<float>&, bool);
+template int coarse_bottom_lds<double>(const CoarseCycle<double>&);
+template int coarse_bottom_lds<float>(const CoarseCycle<float>&);
 
 // Lets a one-workgroup kernel take the device's whole LDS as dynamic LDS.
 static bool allow_lds(const void* fn) {
@@ -2774,28 +2711,21 @@ template hipError_t launch_bottom<float>(hipStream_t, float*, const float*, Face
 
 template <class T>
 hipError_t launch_coarse_cycle(hipStream_t s, const CoarseCycle<T>* cc, int n, const int* active, bool var,
-                               int lds_bytes, bool levels_lds) {
+                               int lds_bytes) {
     if (n <= 0) return hipSuccess;
-#define BXMG_CC(MODE, LDS)                                                                                 \
+#define BXMG_CC(MODE)                                                                                      \
     do {                                                                                                   \
-        static const bool once = allow_lds((const void*)k_coarse_cycle<T, MODE, LDS>);                     \
+        static const bool once = allow_lds((const void*)k_coarse_cycle<T, MODE>);                          \
         (void)once;                                                                                        \
-        hipLaunchKernelGGL((k_coarse_cycle<T, MODE, LDS>), dim3(n), dim3(kBotThreads), lds_bytes, s, cc, active); \
+        hipLaunchKernelGGL((k_coarse_cycle<T, MODE>), dim3(n), dim3(kBotThreads), lds_bytes, s, cc, active); \
     } while (0)
-    if (var) {
-        if (levels_lds) BXMG_CC(2, true);
-        else BXMG_CC(2, false);
-    } else {
-        if (levels_lds) BXMG_CC(0, true);
-        else BXMG_CC(0, false);
-    }
+    if (var) BXMG_CC(2);
+    else BXMG_CC(0);
 #undef BXMG_CC
     return hipGetLastError();
 }
-template hipError_t launch_coarse_cycle<double>(hipStream_t, const CoarseCycle<double>*, int, const int*, bool, int,
-                                                bool);
-template hipError_t launch_coarse_cycle<float>(hipStream_t, const CoarseCycle<float>*, int, const int*, bool, int,
-                                               bool);
+template hipError_t launch_coarse_cycle<double>(hipStream_t, const CoarseCycle<double>*, int, const int*, bool, int);
+template hipError_t launch_coarse_cycle<float>(hipStream_t, const CoarseCycle<float>*, int, const int*, bool, int);
 
 // ------------------------------------------------------------ batch kernels
 // One block per segment: a fixed-tree reduction over the segment's tiles, in

@@ -41,24 +41,6 @@ namespace bxmg {
 
 namespace {
 
-// a / b for a loop-invariant b whose reciprocal is held in two parts,
-// 1/b = yh + yl: the estimate fma(a, yh, a yl) is within half an ulp and a
-// rounding of a/b, and the correction by its exact remainder then gives the
-// correctly rounded quotient (Markstein 1990) -- the IEEE division's bits,
-// in 4 dependent instructions instead of about 12.  (An infinite a gives NaN;
-// both end the solve as non-finite.)
-template <class T>
-struct Recip {
-    T b, yh, yl;
-    __device__ __forceinline__ explicit Recip(T d) : b(d), yh(T(1) / d), yl(fma_(-d, yh, T(1)) * yh) {}
-    static __device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
-    static __device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
-    __device__ __forceinline__ T div(T a) const {
-        const T q = fma_(a, yh, a * yl);
-        return fma_(fma_(-q, b, a), yh, q);
-    }
-};
-
 // Barrier between LDS writers and readers of one step; global loads in
 // flight (the planes ahead) and stores are not waited for.
 __device__ __forceinline__ void lds_barrier() {

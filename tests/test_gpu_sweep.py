@@ -32,7 +32,6 @@ def solve(bx, n, lo, per, knob, **par):
     rhs = bx.MultiFab(ba, ctx=ctx).set_val(0.0).from_global(f)
     res = bx.mlmg_solve(phi, rhs, **par)
     out = phi.to_global()
-    ctx.close()
     return out, res
 
 
