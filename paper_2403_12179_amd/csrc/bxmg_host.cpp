@@ -604,7 +604,7 @@ void vcycle(Run& R, size_t l) {
         const bool zero = l > 0 || R.zero_top;
         const SweepPlan& P = L.sweep[kSweepRestrict][zero ? 1 : 0];
         R.pre(l, kStageGS);
-        HIPCHK(launch_sweep<T>(R.s, P, zero, false, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
+        HIPCHK(launch_sweep<T>(R.s, P, zero, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
                                lvl_f<T>(H, l + 1), nullptr, R.active));
         R.post(l, kStageGS);
     } else {
@@ -646,8 +646,7 @@ void vcycle(Run& R, size_t l) {
     const int kind = norm ? kSweepNorm : kSweepPlain;
     const SweepPlan& P = L.sweep[kind][0];
     R.pre(l, kStageGS);
-    // (the solve's other level-0 passes read its face ghosts)
-    HIPCHK(launch_sweep<T>(R.s, P, false, true, l == 0, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
+    HIPCHK(launch_sweep<T>(R.s, P, false, true, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
                            R.stream_norms, R.active));
     R.post(l, kStageGS);
     if (norm) R.streamed = P.blocks;

@@ -255,10 +255,10 @@ struct SweepPlan {
 SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32);
 // uin (not read when zero: the sweeps start from u = 0) -> uout, another
 // array.  post: the sweeps after a prolongation that left colour 0 to them
-// (launch_prolong, only_c1); push: write uout's face ghosts too.  cf: the
-// coarse f (kSweepRestrict); partials: 3 per block (kSweepNorm).
+// (launch_prolong, only_c1).  uout's ghosts are not written.  cf: the coarse f
+// (kSweepRestrict); partials: 3 per block (kSweepNorm).
 template <class T>
-hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, bool push, int kind, const T* uin,
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin,
                         T* uout, const T* f, T* cf, double* partials, const int* active);
 
 // r = f - L u on both colours, optional store of r (R = T, or float for the

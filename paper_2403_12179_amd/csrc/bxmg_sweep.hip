@@ -76,9 +76,10 @@ struct Raw<float> {
 // KIND (SweepKind): what follows the sweeps.  ZERO: they start from u = 0,
 // which is not read.  POST: the sweeps after a prolongation, which leaves
 // colour 0 to them: colour 0's old values, read only beside Dirichlet faces,
-// are minus the ghosts there.  PUSH: write the face ghosts of uout too.
+// are minus the ghosts there.  uout's ghosts are left alone: no streamed level
+// reads them.
 // NT: threads per block (columns of a block, halo included, at most NT).
-template <class T, int NT, bool ZERO, int KIND, bool POST, bool PUSH>
+template <class T, int NT, bool ZERO, int KIND, bool POST>
 __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__ uin, T* __restrict__ uout,
                                              const T* __restrict__ f, T* __restrict__ cf,
                                              double* __restrict__ partials, const int* __restrict__ active) {
@@ -164,7 +165,8 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         r3[k] = T(0); b4[k] = T(0); fr[k] = T(0); fb[k] = T(0);
     }
     T sprev = T(0), half = T(0);  // restriction: this row's pair sum, the even plane's sum of four
-    double mx = 0.0, s2 = 0.0, bad = 0.0;
+    double mx = 0.0, s2 = 0.0;
+    int nbad = 0;  // non-finite residuals
 
     // loads of plane q into ring slot PH (plane parity PH & 1)
     auto load = [&](auto ph, int q) {
@@ -185,14 +187,9 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
             // colour 0's old value is read only through Dirichlet ghosts
             const bool ez = !perz && (z == 0 || z == n2 - 1);
             if (edge_xy || ez) {
-                if constexpr (POST) {
-                    const int g = (PH & 1) ? gB : gA;
-                    T v = Raw<T>::ld(Ru, g, zo + co);
-                    if (ez) {
-                        const T vz = Raw<T>::ld(Ru, vr, zo + co + (z == 0 ? -pl : pl));
-                        v = g == kOffPastBox ? vz : v;
-                    }
-                    r0[PH] = -v;
+                if constexpr (POST) {  // the ghost itself (offsets from the plane below)
+                    const int g = (PH & 1) ? gB : gA, gz = z == 0 ? vr : vr + 2 * pl;
+                    r0[PH] = Raw<T>::ld(Ru, ez && g == kOffPastBox ? gz : g + pl, zo + co - pl);
                 } else {
                     r0[PH] = Raw<T>::ld(Ru, vr, zo);
                 }
@@ -216,7 +213,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         auto sum = [&](auto dd, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
             constexpr int D = decltype(dd)::value;
             if constexpr (EDGE) {
-                const T g = -oldv;
+                const T g = POST && D == 1 ? oldv : -oldv;  // (stage 1 after a prolongation: the ghost's value)
                 n.x = (isA ? fxA : fxB) ? g : n.x;
                 n.d = fyl ? g : n.d;
                 n.u = fyr ? g : n.u;
@@ -279,9 +276,14 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
             const T rb = fb[RS(5)] - (sub - sb * b4[RS(5)]) * ih2;
             if constexpr (NORM) {
                 const int p = q - 5;
-                if (own && p >= z0 && p < zlim) {
-                    acc_norm((double)rr, mx, s2, bad);
-                    acc_norm((double)rb, mx, s2, bad);
+                const bool mine = own && p >= z0 && p < zlim;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {  // acc_norm, without branches: 0 adds nothing
+                    const double v = mine ? (double)(c ? rb : rr) : 0.0, a = fabs(v);
+                    const bool fine = a <= 1.7976931348623157e308;
+                    mx = fmax(mx, fine ? a : 0.0);
+                    nbad += fine ? 0 : 1;
+                    s2 = s2 + v * v;
                 }
             } else {
                 // the four residuals of this row pair in plane q-6 (the
@@ -301,29 +303,6 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
                 }
                 sprev = rr + rb;  // even x + odd x: which colour is which commutes
                 lds[(bS + (PH & 1)) * NT + tid] = sprev;
-            }
-        }
-        if constexpr (PUSH) {  // the face ghosts that mirror plane q-4's cells
-            const int p = q - 4;
-            const bool fz = p == 0 || p == n2 - 1;
-            if (own && p >= z0 && p < zlim && (fz || m == 0 || m == nm - 1 || y == 0 || y == n1 - 1)) {
-                const int zo = (p + 1) * pl, rb = (y + 1) * A.H;
-                auto ghost = [&](bool per, T v, int c, int image, int below, int zi, int zb) {
-                    // the periodic image (same colour) or the ghost beyond (the other colour)
-                    if (per) Raw<T>::st(Ro, image * es, zi + (c ? co : 0), v);
-                    else Raw<T>::st(Ro, below * es, zb + (c ? 0 : co), -v);
-                };
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const T v = c ? b4[RS(4)] : r3[RS(4)];
-                    const int o = (c + y + PH) & 1, xs = m + o;  // slot of x = 2m + o in its row
-                    if (m == 0 && o == 0) ghost(A.per[0], v, c, rb + nm, rb, zo, zo);
-                    if (m == nm - 1 && o == 1) ghost(A.per[0], v, c, rb, rb + nm, zo, zo);
-                    if (y == 0) ghost(A.per[1], v, c, (n1 + 1) * A.H + xs, xs, zo, zo);
-                    if (y == n1 - 1) ghost(A.per[1], v, c, xs, (n1 + 1) * A.H + xs, zo, zo);
-                    if (p == 0) ghost(perz, v, c, rb + xs, rb + xs, (n2 + 1) * pl, 0);
-                    if (p == n2 - 1) ghost(perz, v, c, rb + xs, rb + xs, 0, (n2 + 1) * pl);
-                }
             }
         }
 #undef RS
@@ -348,6 +327,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
     }
     if constexpr (NORM) {
         double* sh = (double*)lds;  // every LDS read ended with the last barrier
+        double bad = (double)nbad;
         block_reduce3(mx, s2, bad, sh);
         if (tid == 0) {
             partials[3 * (size_t)blk] = mx;
@@ -416,25 +396,24 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
 }
 
 template <class T>
-hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, bool push, int kind, const T* uin,
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin,
                         T* uout, const T* f, T* cf, double* partials, const int* active) {
     const dim3 G((unsigned)P.blocks);
-#define BXMG_SW(NT, ZERO, KIND, POST, PUSH)                                                                     \
-    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, PUSH>), G, dim3(NT), 0, s, P.args, uin, uout, f, cf, \
-                       partials, active)
-#define BXMG_SWN(ZERO, KIND, POST, PUSH)               \
-    if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST, PUSH); \
-    else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST, PUSH); \
-    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST, PUSH); \
-    else if constexpr (sizeof(T) == 4) BXMG_SW(1024, ZERO, KIND, POST, PUSH); \
+#define BXMG_SW(NT, ZERO, KIND, POST)                                                                     \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST>), G, dim3(NT), 0, s, P.args, uin, uout, f, cf, partials, \
+                       active)
+#define BXMG_SWN(ZERO, KIND, POST)                   \
+    if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST); \
+    else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST); \
+    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST); \
+    else if constexpr (sizeof(T) == 4) BXMG_SW(1024, ZERO, KIND, POST); \
     else return hipErrorInvalidValue
-    if (kind == kSweepRestrict && !post && !push) {
-        if (zero) { BXMG_SWN(true, kSweepRestrict, false, false); }
-        else { BXMG_SWN(false, kSweepRestrict, false, false); }
-    } else if (kind == kSweepNorm && post && push && std::is_same<T, double>::value) {
-        if constexpr (std::is_same<T, double>::value) { BXMG_SWN(false, kSweepNorm, true, true); }
+    if (kind == kSweepRestrict && !post) {
+        if (zero) { BXMG_SWN(true, kSweepRestrict, false); } else { BXMG_SWN(false, kSweepRestrict, false); }
+    } else if (kind == kSweepNorm && post && std::is_same<T, double>::value) {
+        if constexpr (std::is_same<T, double>::value) { BXMG_SWN(false, kSweepNorm, true); }
     } else if (kind == kSweepPlain && post) {
-        if (push) { BXMG_SWN(false, kSweepPlain, true, true); } else { BXMG_SWN(false, kSweepPlain, true, false); }
+        BXMG_SWN(false, kSweepPlain, true);
     } else {
         return hipErrorInvalidValue;
     }
@@ -442,9 +421,9 @@ hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post,
 #undef BXMG_SW
     return hipGetLastError();
 }
-template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, bool, int, const double*, double*,
+template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, int, const double*, double*,
                                          const double*, double*, double*, const int*);
-template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, bool, int, const float*, float*,
+template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, int, const float*, float*,
                                         const float*, float*, double*, const int*);
 
 }  // namespace bxmg
