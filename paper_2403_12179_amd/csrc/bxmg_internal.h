@@ -247,8 +247,8 @@ struct SweepArgs {
     double h, a;
 };
 struct SweepPlan {
-    int nt = 0;        // threads per block: 256, 512 or 1024 (0: the level is not streamed)
-    int blocks = 0;
+    int nt = 0;  // the kernel's form: up to 256, 512, 768 or 1024 threads (0: the level is not streamed)
+    int threads = 0, blocks = 0;
     SweepArgs args{};
 };
 // The blocks of a level of n cells (storage and coarse fields of args unset).

@@ -24,12 +24,17 @@
 // minus the cell's own value before the update (reading own registers), and
 // periodic columns wrap.
 //
+// A block's wait for ghosts and its selects between a ghost and a cell are
+// compiled for the walls it touches (none, an x face alone, any).
+//
 // Measured on the 256^3 FP64 Dirichlet level 0: two sweeps, residual and
-// restriction 183 us, against 4 x 50 + 66 us one launch each; a step's time
-// is split between LDS traffic (18 reads and 6 writes of a value per thread)
-// and FP64 issue (about 85 instructions per thread), which overlap little,
-// as a block's waves run the same phase of a step together.  The 256^3 solve
-// went from 8.73 to 7.78 ms, the 192^3 heat step from 4.50 to 4.00 ms.
+// restriction 181 us, against 4 x 50 + 66 us one launch each; two sweeps and
+// the norms 186, two sweeps from zero 114.  The arrays alone take 52 to 66 us
+// at the copy rate; loads, stores, LDS traffic (18 reads and 6 writes of a
+// value per thread and step) and FP64 issue (about 85 instructions) overlap
+// only in part, as a block's waves run the same phase of a step together.
+// The 256^3 solve went from 8.77 to 6.06 ms, the 192^3 heat step from 4.47 to
+// 3.37 ms.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -112,7 +117,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
     // Dirichlet faces the column lies on
     const bool fxl = in && !A.per[0] && m == 0, fxr = in && !A.per[0] && m == nm - 1;
     const bool fyl = in && !A.per[1] && y == 0, fyr = in && !A.per[1] && y == n1 - 1;
-    const bool edge_xy = __ballot(fxl || fxr || fyl || fyr) != 0;
+    const bool edge_y = __ballot(fyl || fyr) != 0, edge_xy = edge_y || __ballot(fxl || fxr) != 0;
     const int z0 = bz * A.ZC, zlim = min(z0 + A.ZC, n2);
     // first plane loaded: the halo below, rounded to an even plane so that a
     // step's plane parity is known at compile time
@@ -197,9 +202,9 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         }
     };
 
+    // EDGE: 0 inside, 1 beside a Dirichlet x face, 2 beside any
     auto step = [&](auto ph, auto edge, int q) {
-        constexpr int PH = decltype(ph)::value;
-        constexpr bool EDGE = decltype(edge)::value;
+        constexpr int PH = decltype(ph)::value, EDGE = decltype(edge)::value;
 #define RS(d) ((PH - (d) + 16) & 7)   /* ring slot of plane q - d */
 #define ISA(d, c) ((((c) + PH - (d)) & 1) == 0)  /* its colour-c cell is at o = yo */
         struct Three { T x, d, u; };
@@ -212,13 +217,15 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         // (x- + x+ commutes, so the own cell's side does not matter)
         auto sum = [&](auto dd, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
             constexpr int D = decltype(dd)::value;
-            if constexpr (EDGE) {
+            if constexpr (EDGE > 0) {
                 const T g = POST && D == 1 ? oldv : -oldv;  // (stage 1 after a prolongation: the ghost's value)
                 n.x = (isA ? fxA : fxB) ? g : n.x;
-                n.d = fyl ? g : n.d;
-                n.u = fyr ? g : n.u;
-                zm = !perz && q == D ? g : zm;
-                zp = !perz && q == D + n2 - 1 ? g : zp;
+                if constexpr (EDGE > 1) {
+                    n.d = fyl ? g : n.d;
+                    n.u = fyr ? g : n.u;
+                    zm = !perz && q == D ? g : zm;
+                    zp = !perz && q == D + n2 - 1 ? g : zp;
+                }
             }
             return ((own_o + n.x) + (n.d + n.u)) + (zm + zp);
         };
@@ -317,8 +324,10 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         const int q = qb + PH;                                                                 \
         if (q >= zend) break;                                                                  \
         load(integral_constant<int, (PH + 2) & 7>(), q + 2);                                   \
-        if (edge_xy || (!perz && (q <= 5 || q >= n2))) step(integral_constant<int, PH>(), std::true_type(), q); \
-        else step(integral_constant<int, PH>(), std::false_type(), q);                         \
+        if (edge_y || (!perz && (q <= 5 || q >= n2)))                                          \
+            step(integral_constant<int, PH>(), integral_constant<int, 2>(), q);                \
+        else if (edge_xy) step(integral_constant<int, PH>(), integral_constant<int, 1>(), q);  \
+        else step(integral_constant<int, PH>(), integral_constant<int, 0>(), q);               \
         lds_barrier();                                                                         \
     }
         BXMG_STEP(0) BXMG_STEP(1) BXMG_STEP(2) BXMG_STEP(3)
@@ -380,6 +389,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
                 if (c < cost) {
                     cost = c;
                     best.nt = nt;
+                    best.threads = (cols + 63) / 64 * 64;
                     best.blocks = (int)blocks;
                     SweepArgs& A = best.args;
                     A.RM = RM; A.RY = RY; A.hm = hm; A.hy = hy;
@@ -400,7 +410,7 @@ hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post,
                         T* uout, const T* f, T* cf, double* partials, const int* active) {
     const dim3 G((unsigned)P.blocks);
 #define BXMG_SW(NT, ZERO, KIND, POST)                                                                     \
-    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST>), G, dim3(NT), 0, s, P.args, uin, uout, f, cf, partials, \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST>), G, dim3(P.threads), 0, s, P.args, uin, uout, f, cf, partials, \
                        active)
 #define BXMG_SWN(ZERO, KIND, POST)                   \
     if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST); \
