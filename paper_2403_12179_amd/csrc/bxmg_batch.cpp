@@ -300,6 +300,14 @@ struct BLevel {
     DevVec<FaceArrays<double>> fat64;  // by slot
     DevVec<FaceArrays<float>> fat32;
     int flip = 0;
+    // streaming smoother (every member's level is one box, FP32, constant
+    // coefficient): the launches before and after the coarse levels, and above
+    // level 0 the boxes in the second iterate array
+    bool stream = false;
+    DevVec<SweepArgs> pre, post;
+    DevVec<int2> pre_at, post_at;
+    int npre = 0, npost = 0, pre_threads = 0, post_threads = 0;
+    DevVec<RBox> rb2;
 };
 
 struct Done {
@@ -471,6 +479,120 @@ CoarseCycle<T> coarse_desc(const bxmg_batch_s* b, const Problem& p, T* u, T* f, 
     return cc;
 }
 
+// --------------------------------------------------- streaming smoother
+// The blocks of a launch: the jobs' blocks dealt to the 8 XCDs (block b runs
+// on XCD b % 8) in runs of one job, so that neighbours share an L2, each run to
+// the XCD with the least work, longest jobs first; unused places are -1.
+std::vector<int2> deal_blocks(const std::vector<SweepArgs>& jobs) {
+    std::vector<int> order(jobs.size());
+    double total = 0.0;
+    for (size_t q = 0; q < jobs.size(); ++q) {
+        order[q] = (int)q;
+        total += (double)jobs[q].nbx * jobs[q].nby * jobs[q].nbz * (jobs[q].ZC + 10);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return jobs[x].ZC > jobs[y].ZC; });
+    std::array<std::vector<int2>, 8> xcd;
+    std::array<double, 8> load{};
+    for (int q : order) {
+        const SweepArgs& A = jobs[q];
+        const int blocks = A.nbx * A.nby * A.nbz;
+        const int run = std::max(1, (int)(total / 64.0 / (A.ZC + 10)));
+        for (int k = 0; k < blocks;) {
+            const size_t x = std::min_element(load.begin(), load.end()) - load.begin();
+            const int end = std::min(blocks, k + run);
+            load[x] += (double)(end - k) * (A.ZC + 10);
+            for (; k < end; ++k) xcd[x].push_back(int2{q, k});
+        }
+    }
+    size_t len = 0;
+    for (const auto& v : xcd) len = std::max(len, v.size());
+    std::vector<int2> at(8 * len, int2{-1, 0});
+    for (size_t x = 0; x < 8; ++x)
+        for (size_t k = 0; k < xcd[x].size(); ++k) at[8 * k + x] = xcd[x][k];
+    return at;
+}
+
+// Levels whose pre- and post-sweeps are one launch each over all problems.
+// The sweeps write another array than they read.  Level 0 needs none: the
+// pre-sweeps start from zero, and the post-sweeps add their result to the
+// FP64 iterate.  Above it the pre-sweeps' array, which the prolongation
+// corrects, lies in the ranges that the level has in the FP64 arena and that
+// a mixed-precision batch otherwise leaves idle; FP64 batches have no such
+// range and keep one launch per half-sweep.  64 periodic problems of 32^3 to
+// 128^3 (52 million cells): the level-0 sweeps, restriction, zeroing and the
+// update of the iterate took 8 x 91 + 372 us a cycle and take 216 + 415; the
+// batch went from 23.0 to 17.0 ms.  With blocks in problem order and an equal
+// share of the chip planned for every problem it took 19.2: a launch ends with
+// its longest blocks, and the largest problems set it.
+void plan_streams(bxmg_batch_s* b) {
+    for (BLevel& B : b->lev) B.stream = false;
+    if (b->prec != 1 || b->var || b->P.nu1 != 2 || b->P.nu2 != 2) return;
+    double cells = 0.0;
+    for (int s : b->members) cells += (double)b->slots[s]->plan->dom.cells();
+    for (int l = b->lmax - 1; l >= 0; --l) {
+        BLevel& B = b->lev[l];
+        if (!B.res || !b->lev[l + 1].res || !B.push || !B.one_box) continue;
+        // (a level below that is not streamed is zeroed by the residual launch above it)
+        if (l + 1 < b->lmax && !b->lev[l + 1].stream) continue;
+        std::map<const GeoPlan*, std::array<SweepPlan, 2>> plans;
+        std::vector<SweepArgs> job[2];
+        std::vector<RBox> rb2;
+        int threads[2] = {0, 0};
+        bool ok = true;
+        for (int s : b->members) {
+            const Problem& p = *b->slots[s];
+            const GeoPlan& G = *p.plan;
+            if (l >= (int)G.L.size()) continue;
+            RBox r2 = G.L[l].rb[0];
+            r2.base = 2 * (r2.base + p.off);
+            r2.pid = s;
+            for (int q = 0; q < 6; ++q)
+                if (r2.nb[q] >= 0) r2.nb[q] = (int)rb2.size();
+            rb2.push_back(r2);
+            if (l >= G.cs) continue;
+            if (G.L[l + 1].rb.size() != 1) { ok = false; break; }
+            auto it = plans.find(&G);
+            if (it == plans.end()) {
+                // the problem's share of the chip
+                const int cus = std::max(1, (int)std::lround(256.0 * (double)G.dom.cells() / cells));
+                std::array<SweepPlan, 2> P;
+                for (int k = 0; k < 2; ++k)
+                    P[k] = plan_sweep_level(G.L[l].rb[0], G.L[l + 1].rb[0], G.per,
+                                            k == 0 ? kSweepRestrict : l ? kSweepPlain : kSweepAdd, k == 0, true, cus,
+                                            kSweepJobThreads);
+                it = plans.emplace(&G, P).first;
+            }
+            for (int k = 0; k < 2; ++k) {
+                const SweepPlan& P = it->second[k];
+                if (P.nt == 0) ok = false;
+                SweepArgs A = P.args;
+                const long long at0 = p.off + G.L[l].off;
+                const long long second = l ? 2 * at0 : at0;
+                A.pid = s;
+                A.f = at0;
+                A.cf = p.off + G.L[l + 1].off;
+                A.acc = at0;
+                A.uin = second;
+                A.uout = k ? at0 : second;
+                job[k].push_back(A);
+                threads[k] = std::max(threads[k], P.threads);
+            }
+        }
+        if (!ok) continue;
+        B.stream = true;
+        const std::vector<int2> pre = deal_blocks(job[0]), post = deal_blocks(job[1]);
+        B.pre.assign(job[0]);
+        B.post.assign(job[1]);
+        B.pre_at.assign(pre);
+        B.post_at.assign(post);
+        B.npre = (int)pre.size();
+        B.npost = (int)post.size();
+        B.pre_threads = threads[0];
+        B.post_threads = threads[1];
+        if (l) B.rb2.assign(rb2);
+    }
+}
+
 // ------------------------------------------------------------- rebuild
 void destroy_graph(bxmg_batch_s* b) {
     if (b->exec) { (void)hipGraphExecDestroy(b->exec); b->exec = nullptr; }
@@ -558,6 +680,7 @@ void rebuild(bxmg_batch_s* b) {
         B.fullc.assign(fullc);
         B.nfullc = (int)fullc.size();
     }
+    plan_streams(b);
     b->tstart.assign(tstart);
     b->segslot.assign(segslot);
     b->nseg = (int)segslot.size();
@@ -681,6 +804,22 @@ void b_smooth(bxmg_batch_s* b, hipStream_t s, size_t l, int nsweeps) {
         }
 }
 
+// The streamed levels' second iterate array (plan_streams).
+float* second_array(bxmg_batch_s* b, int l) { return l ? reinterpret_cast<float*>(b->u64.p) : b->u32.p; }
+
+void b_sweep_pre(bxmg_batch_s* b, hipStream_t s, int l) {
+    BLevel& B = b->lev[l];
+    float* a = second_array(b, l);
+    HIPCHK(launch_sweep_jobs(s, B.pre.p(), B.pre_at.p(), B.npre, B.pre_threads, kSweepRestrict, a, a, b->f32.p,
+                             b->f32.p, nullptr, b->active.p));
+}
+
+void b_sweep_post(bxmg_batch_s* b, hipStream_t s, int l) {
+    BLevel& B = b->lev[l];
+    HIPCHK(launch_sweep_jobs(s, B.post.p(), B.post_at.p(), B.npost, B.post_threads, l ? kSweepPlain : kSweepAdd,
+                             second_array(b, l), b->u32.p, b->f32.p, nullptr, b->u64.p, b->active.p));
+}
+
 template <class T>
 void b_vcycle(bxmg_batch_s* b, hipStream_t s) {
     T* u = arena_u<T>(b);
@@ -688,6 +827,10 @@ void b_vcycle(bxmg_batch_s* b, hipStream_t s) {
     const bool f32 = sizeof(T) == 4;
     for (int l = 0; l < b->lmax; ++l) {
         BLevel& B = b->lev[l];
+        if (B.stream) {
+            b_sweep_pre(b, s, l);
+            continue;
+        }
         b_smooth<T>(b, s, l, b->P.nu1);
         if (!B.push) {
             HIPCHK(launch_fill_sets(s, u, f32, B.face[0].p(), B.nface, B.mface, b->active.p));
@@ -703,12 +846,19 @@ void b_vcycle(bxmg_batch_s* b, hipStream_t s) {
         BLevel& B = b->lev[l];
         // small one-box coarse levels: the staged prolongation reads the
         // cells their ghosts mirror, so no ghost refresh before it
-        const Grid g = level_grid(b, l);
+        Grid g = level_grid(b, l);
         const bool self = B.coarse_self && prolong_staged(g.push, b->P.nu2 > 0, B.stage_values);
         if (!self) HIPCHK(launch_fill_sets(s, u, f32, B.fullc.p(), B.nfullc, B.mfullc, b->active.p));
-        HIPCHK(launch_prolong<T>(s, g, b->lev[l + 1].rb.p(), B.cbox.p(), u, u, b->P.prolong, b->P.nu2 > 0,
+        T* uf = u;
+        if constexpr (std::is_same<T, float>::value)
+            if (B.stream && l > 0) {
+                g.boxes = B.rb2.p();
+                uf = second_array(b, l);
+            }
+        HIPCHK(launch_prolong<T>(s, g, b->lev[l + 1].rb.p(), B.cbox.p(), u, uf, b->P.prolong, b->P.nu2 > 0,
                                  B.stage_values, self));
-        b_smooth<T>(b, s, l, b->P.nu2);
+        if (B.stream) b_sweep_post(b, s, l);
+        else b_smooth<T>(b, s, l, b->P.nu2);
     }
 }
 
@@ -728,6 +878,10 @@ void enqueue_cycle(bxmg_batch_s* b, hipStream_t s) {
     if (b->prec == 0) {
         b_vcycle<double>(b, s);
     } else {
+        if (b->lev[0].stream) {  // (its pre-sweeps start from zero, its post-sweeps add)
+            b_vcycle<float>(b, s);
+            return;
+        }
         HIPCHK(launch_zero_ranges<float>(s, b->u32.p, b->z0.p(), b->nz0, b->z0max, b->active.p));
         b_vcycle<float>(b, s);
         HIPCHK(launch_add_f32(s, level_grid(b, 0), b->u64.p, b->u32.p));

@@ -81,7 +81,7 @@ struct Level {
     // streaming smoother (one-box constant-coefficient levels above the
     // coarse cycle): blocks per kind and for a zero start
     bool stream = false;
-    SweepPlan sweep[3][2];
+    SweepPlan sweep[4][2];
     // level 0 of a solve whose caller boxes were merged: one view per caller
     // box (its valid cells, addressed in the merged storage) and tiles over
     // them, for the layout conversions and the field norm
@@ -198,33 +198,13 @@ static void plan_streams(Hier* H, long long& max_tiles) {
         Level& L = *H->L[l];
         const Level& C = *H->L[l + 1];
         if (L.boxes.size() != 1 || C.boxes.size() != 1 || !L.push || !L.res) continue;
-        const RBox& B = L.rb[0];
-        const RBox& Q = C.rb[0];
-        int n[3];
-        bool even = true;
-        for (int d = 0; d < 3; ++d) {
-            n[d] = B.hi[d] - B.lo[d] + 1;
-            even = even && n[d] % 2 == 0 && n[d] >= 4 && (B.lo[d] & 1) == 0;
-        }
-        if (!even) continue;
         const bool f32 = H->precision == 1;
         bool ok = true;
-        for (int kind = 0; kind < 3; ++kind)
+        for (int kind = 0; kind < 4; ++kind)
             for (int zero = 0; zero < 2; ++zero) {
                 SweepPlan& P = L.sweep[kind][zero];
-                P = plan_sweep(n, H->per, kind, zero != 0, f32);
+                P = plan_sweep_level(L.rb[0], C.rb[0], H->per, kind, zero != 0, f32);
                 ok = ok && P.nt > 0;
-                SweepArgs& A = P.args;
-                A.H = B.H;
-                A.GH = B.H * B.G[1];
-                A.cs = (int)B.cstride;
-                A.cH = Q.H;
-                A.cGH = Q.H * Q.G[1];
-                A.ccs = (int)Q.cstride;
-                A.cpar = (Q.lo[0] + Q.lo[1] + Q.lo[2]) & 1;
-                A.pid = B.pid;
-                A.h = B.h;
-                A.a = B.a;
                 max_tiles = std::max<long long>(max_tiles, P.blocks);
             }
         if (!ok) continue;
@@ -490,6 +470,7 @@ struct Run {
     // on a streamed level 0 the post-sweeps take the norms of the whole
     // residual instead, in this many partials from stream_norms
     double* stream_norms = nullptr;
+    double* stream_add = nullptr;  // ... or add the FP32 result to this instead of storing it
     int streamed = 0;
     bool zero_top = false;  // the V-cycle starts from level 0 = 0
     // whether level l runs the streaming smoother (two sweeps each way)
@@ -605,7 +586,7 @@ void vcycle(Run& R, size_t l) {
         const SweepPlan& P = L.sweep[kSweepRestrict][zero ? 1 : 0];
         R.pre(l, kStageGS);
         HIPCHK(launch_sweep<T>(R.s, P, zero, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
-                               lvl_f<T>(H, l + 1), nullptr, R.active));
+                               lvl_f<T>(H, l + 1), nullptr, nullptr, R.active));
         R.post(l, kStageGS);
     } else {
     smooth<T>(R, l, R.nu1);
@@ -643,11 +624,11 @@ void vcycle(Run& R, size_t l) {
         return;
     }
     const bool norm = R.stream_norms && l == 0;
-    const int kind = norm ? kSweepNorm : kSweepPlain;
+    const int kind = norm ? kSweepNorm : R.stream_add && l == 0 ? kSweepAdd : kSweepPlain;
     const SweepPlan& P = L.sweep[kind][0];
     R.pre(l, kStageGS);
     HIPCHK(launch_sweep<T>(R.s, P, false, true, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
-                           R.stream_norms, R.active));
+                           R.stream_add, R.stream_norms, R.active));
     R.post(l, kStageGS);
     if (norm) R.streamed = P.blocks;
 }
@@ -1430,7 +1411,12 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
                 return R.fused_sweep;
             } else {
                 R.zero_top = true;
-                if (!R.streams(0)) HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, L0.nelem, R.active));
+                if (R.streams(0)) {
+                    R.stream_add = u;
+                    vcycle<float>(R, 0);
+                    return false;
+                }
+                HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, L0.nelem, R.active));
                 vcycle<float>(R, 0);
                 HIPCHK(launch_add_f32(R.s, R.grid(L0.walk()), u, H->u32[0]->p));
                 return false;

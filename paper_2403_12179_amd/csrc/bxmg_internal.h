@@ -233,6 +233,7 @@ enum SweepKind {
     kSweepRestrict = 0,  // then the residual, restricted into the coarse level's f
     kSweepPlain = 1,
     kSweepNorm = 2,      // then the residual's norms, per block (FP64)
+    kSweepAdd = 3,       // the FP32 result added to an FP64 array of the same layout
 };
 struct SweepArgs {
     int n[3];          // cells of the level (even)
@@ -245,21 +246,36 @@ struct SweepArgs {
     int cH, cGH, ccs, cpar;  // the coarse level's storage; parity of its lower corner
     int pid;           // problem slot of active[]
     double h, a;
+    long long uin, uout, f, cf, acc;  // launch_sweep_jobs: element offsets of the arrays
 };
 struct SweepPlan {
     int nt = 0;  // the kernel's form: up to 256, 512, 768 or 1024 threads (0: the level is not streamed)
     int threads = 0, blocks = 0;
     SweepArgs args{};
 };
-// The blocks of a level of n cells (storage and coarse fields of args unset).
-SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32);
+// The blocks of a level of n cells (storage and coarse fields of args unset),
+// for cus compute units, at most ntmax threads each.
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int cus = 256,
+                     int ntmax = 1024);
+// The same for the one-box level B over the one-box level Q, all of args set;
+// nt = 0 if the level cannot be streamed.
+SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32,
+                           int cus = 256, int ntmax = 1024);
 // uin (not read when zero: the sweeps start from u = 0) -> uout, another
 // array.  post: the sweeps after a prolongation that left colour 0 to them
 // (launch_prolong, only_c1).  uout's ghosts are not written.  cf: the coarse f
-// (kSweepRestrict); partials: 3 per block (kSweepNorm).
+// (kSweepRestrict); acc: what the result is added to, its face ghosts
+// refreshed (kSweepAdd); partials: 3 per block (kSweepNorm).
 template <class T>
-hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin,
-                        T* uout, const T* f, T* cf, double* partials, const int* active);
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
+                        const T* f, T* cf, double* acc, double* partials, const int* active);
+// FP32 over many levels in one launch of blocks of threads threads: block b
+// works block where[b].y of the level jobs[where[b].x], planned for at most
+// kSweepJobThreads threads.  kSweepRestrict (from zero), kSweepPlain, kSweepAdd.
+constexpr int kSweepJobThreads = 512;
+hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* where, int blocks, int threads,
+                             int kind, const float* uin, float* uout, const float* f, float* cf, double* acc,
+                             const int* active);
 
 // r = f - L u on both colours, optional store of r (R = T, or float for the
 // mixed-precision cast), partial norms (max|r|, sum r^2, bad count) at

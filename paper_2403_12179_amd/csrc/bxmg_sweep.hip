@@ -34,7 +34,9 @@
 // value per thread and step) and FP64 issue (about 85 instructions) overlap
 // only in part, as a block's waves run the same phase of a step together.
 // The 256^3 solve went from 8.77 to 6.06 ms, the 192^3 heat step from 4.47 to
-// 3.37 ms.
+// 3.37 ms.  Adding an FP32 correction to the FP64 iterate (kSweepAdd) takes
+// 415 us over the 52 million cells of 64 problems, 240 of which are its bytes
+// at the copy rate.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -84,23 +86,40 @@ struct Raw<float> {
 // are minus the ghosts there.  uout's ghosts are left alone: no streamed level
 // reads them.
 // NT: threads per block (columns of a block, halo included, at most NT).
-template <class T, int NT, bool ZERO, int KIND, bool POST>
-__global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__ uin, T* __restrict__ uout,
-                                             const T* __restrict__ f, T* __restrict__ cf,
-                                             double* __restrict__ partials, const int* __restrict__ active) {
+// kSweepAdd: the result is added to acc (and its face ghosts refreshed)
+// instead of being stored.  JOBS: many levels in one launch; block b works
+// block where[b].y of job where[b].x (none: -1).
+template <class T, int NT, bool ZERO, int KIND, bool POST, bool JOBS>
+__global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __restrict__ jobs,
+                                             const int2* __restrict__ where, const T* __restrict__ uin,
+                                             T* __restrict__ uout, const T* __restrict__ f, T* __restrict__ cf,
+                                             double* __restrict__ acc, double* __restrict__ partials,
+                                             const int* __restrict__ active) {
     using std::integral_constant;
-    constexpr bool REST = KIND == kSweepRestrict, NORM = KIND == kSweepNorm;
+    constexpr bool REST = KIND == kSweepRestrict, NORM = KIND == kSweepNorm, ADD = KIND == kSweepAdd;
     constexpr bool RES = REST || NORM;
     // LDS half planes (one colour of one plane of the block's columns)
     constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bS = 12, nBuf = REST ? 14 : RES ? 12 : 10;
     __shared__ T lds[nBuf * NT];
-    if (active && !active[A.pid]) return;
     const int tid = threadIdx.x;
     // block -> (bx, by, bz), neighbouring blocks on one XCD
-    int blk = blockIdx.x;
-    {
+    int blk = blockIdx.x, job = 0;
+    if constexpr (JOBS) {
+        job = where[blk].x;
+        blk = where[blk].y;
+        if (job < 0) return;
+    } else {
         const int nb = gridDim.x;
         if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
+    }
+    const SweepArgs A = JOBS ? jobs[job] : A0;
+    if (active && !active[A.pid]) return;
+    if constexpr (JOBS) {
+        uin += A.uin;
+        uout += A.uout;
+        f += A.f;
+        cf += A.cf;
+        acc += A.acc;
     }
     const int bx = blk % A.nbx, byz = blk / A.nbx;
     const int by = byz % A.nby, bz = byz / A.nby;
@@ -160,6 +179,12 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
     const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
     const auto Rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, bytes, kBufferDword3);
     const auto Ro = __builtin_amdgcn_make_buffer_rsrc((void*)uout, (short)0, bytes, kBufferDword3);
+    // kSweepAdd: the same cells of acc, loaded with the plane four ahead (a
+    // load after a step's stores would wait for them)
+    const auto Ra = __builtin_amdgcn_make_buffer_rsrc((void*)(ADD ? (const void*)acc : (const void*)f), (short)0,
+                                                      2 * A.cs * 8, kBufferDword3);
+    const int aA = own ? (row + yo) * 8 : kOffPastBox, aB = own ? (row + 1 - yo) * 8 : kOffPastBox;
+    double a0[4] = {}, a1[4] = {};  // indexed by plane modulo 4
 
     // the column's registers, indexed by plane modulo 8 (only a few of each
     // are live): values of colour 0 (r) and 1 (b) after 0..4 half-sweeps
@@ -187,6 +212,12 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
         const int vr = (PH & 1) ? vB : vA, vb = (PH & 1) ? vA : vB;
         fr[PH] = Raw<T>::ld(Rf, vr, zo);
         fb[PH] = Raw<T>::ld(Rf, vb, zo + co);
+        if constexpr (ADD) {
+            const bool mine = q - 4 >= z0 && q - 4 < zlim;
+            const int zd = (q - 3) * A.GH * 8;
+            a0[PH & 3] = Raw<double>::ld(Ra, !mine ? kOffPastBox : (PH & 1) ? aB : aA, zd);
+            a1[PH & 3] = Raw<double>::ld(Ra, !mine ? kOffPastBox : (PH & 1) ? aA : aB, zd + A.cs * 8);
+        }
         if constexpr (!ZERO) {
             b0[PH] = Raw<T>::ld(Ru, vb, zo + co);
             // colour 0's old value is read only through Dirichlet ghosts
@@ -271,8 +302,37 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
             const bool mine = p >= z0 && p < zlim;
             const int zo = (p + 1) * pl;
             const int vr = (PH & 1) ? wB : wA, vb = (PH & 1) ? wA : wB;
-            Raw<T>::st(Ro, mine ? vr : kOffPastBox, zo, r3[RS(4)]);
-            Raw<T>::st(Ro, mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
+            if constexpr (!ADD) {
+                Raw<T>::st(Ro, mine ? vr : kOffPastBox, zo, r3[RS(4)]);
+                Raw<T>::st(Ro, mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
+            } else {
+                const int cd = A.cs * 8, zd = (p + 1) * A.GH * 8;
+                const double x0 = a0[PH & 3] + (double)r3[RS(4)], x1 = a1[PH & 3] + (double)b4[RS(4)];
+                const int ar = (PH & 1) ? aB : aA, ab = (PH & 1) ? aA : aB;
+                Raw<double>::st(Ra, mine ? ar : kOffPastBox, zd, x0);
+                Raw<double>::st(Ra, mine ? ab : kOffPastBox, zd + cd, x1);
+                // the face ghosts that mirror the cells
+                const bool fz = p == 0 || p == n2 - 1;
+                if (mine && own && (fz || m == 0 || m == nm - 1 || y == 0 || y == n1 - 1)) {
+                    const int rb = (y + 1) * A.H, pd = A.GH * 8;
+                    auto ghost = [&](bool per, double v, int c, int image, int below, int zi, int zb) {
+                        // the periodic image (same colour) or the ghost beyond (the other colour)
+                        if (per) Raw<double>::st(Ra, image * 8, zi + (c ? cd : 0), v);
+                        else Raw<double>::st(Ra, below * 8, zb + (c ? 0 : cd), -v);
+                    };
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const double v = c ? x1 : x0;
+                        const int o = (c + y + PH) & 1, xs = m + o;  // slot of x = 2m + o in its row
+                        if (m == 0 && o == 0) ghost(A.per[0], v, c, rb + nm, rb, zd, zd);
+                        if (m == nm - 1 && o == 1) ghost(A.per[0], v, c, rb, rb + nm, zd, zd);
+                        if (y == 0) ghost(A.per[1], v, c, (n1 + 1) * A.H + xs, xs, zd, zd);
+                        if (y == n1 - 1) ghost(A.per[1], v, c, xs, (n1 + 1) * A.H + xs, zd, zd);
+                        if (p == 0) ghost(perz, v, c, rb + xs, rb + xs, (n2 + 1) * pd, 0);
+                        if (p == n2 - 1) ghost(perz, v, c, rb + xs, rb + xs, 0, (n2 + 1) * pd);
+                    }
+                }
+            }
         }
         if constexpr (RES) {  // stage 5
             const T sur =
@@ -350,13 +410,14 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A, const T* __restrict__
 // most 1024 columns is priced as (rounds of blocks over the 256 CUs) x (steps
 // of a block) x (time of a step), a step being latency-bound with few waves
 // on a CU and issue-bound with many; the cheapest is taken.
-SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32) {
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int cus, int ntmax) {
     SweepPlan best;
-    const int halo = (kind == kSweepPlain ? 4 : 5) - (zero ? 1 : 0);
-    const int lead = ((halo + 1) & ~1) + (kind == kSweepRestrict ? 6 : kind == kSweepNorm ? 5 : 4);
+    const bool res = kind == kSweepRestrict || kind == kSweepNorm;
+    const int halo = (res ? 5 : 4) - (zero ? 1 : 0);
+    const int lead = ((halo + 1) & ~1) + (kind == kSweepRestrict ? 6 : res ? 5 : 4);
     const int nm = n[0] / 2;
     // (the FP64 forms keep up to 168 registers a thread: at most 12 waves)
-    const int ntmax = f32 ? 1024 : 768;
+    ntmax = std::min(ntmax, f32 ? 1024 : 768);
     double cost = 1e30;
     auto split = [](int cells, int pieces, int unit) {  // the size of equal pieces, a multiple of unit
         const int u = cells / unit, q = (u + pieces - 1) / pieces;
@@ -381,7 +442,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
                 const int ZC = split(n[2], pz, 2);
                 const int nbz = (n[2] + ZC - 1) / ZC;
                 const long long blocks = (long long)nbx * nby * nbz;
-                const long long per_cu = (blocks + 255) / 256;
+                const long long per_cu = (blocks + cus - 1) / cus;
                 const long long rounds = (per_cu + fit - 1) / fit;
                 const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
                 const double step = std::max(1000.0, 300.0 + (f32 ? 110.0 : 130.0) * waves);
@@ -405,13 +466,35 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
     return best;
 }
 
+SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32, int cus,
+                           int ntmax) {
+    int n[3];
+    for (int d = 0; d < 3; ++d) {
+        n[d] = B.hi[d] - B.lo[d] + 1;
+        if (n[d] % 2 || n[d] < 4 || (B.lo[d] & 1)) return SweepPlan{};
+    }
+    SweepPlan P = plan_sweep(n, per, kind, zero, f32, cus, ntmax);
+    SweepArgs& A = P.args;
+    A.H = B.H;
+    A.GH = B.H * B.G[1];
+    A.cs = (int)B.cstride;
+    A.cH = Q.H;
+    A.cGH = Q.H * Q.G[1];
+    A.ccs = (int)Q.cstride;
+    A.cpar = (Q.lo[0] + Q.lo[1] + Q.lo[2]) & 1;
+    A.pid = B.pid;
+    A.h = B.h;
+    A.a = B.a;
+    return P;
+}
+
 template <class T>
-hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin,
-                        T* uout, const T* f, T* cf, double* partials, const int* active) {
+hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
+                        const T* f, T* cf, double* acc, double* partials, const int* active) {
     const dim3 G((unsigned)P.blocks);
-#define BXMG_SW(NT, ZERO, KIND, POST)                                                                     \
-    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST>), G, dim3(P.threads), 0, s, P.args, uin, uout, f, cf, partials, \
-                       active)
+#define BXMG_SW(NT, ZERO, KIND, POST)                                                                        \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, false>), G, dim3(P.threads), 0, s, P.args,          \
+                       (const SweepArgs*)nullptr, (const int2*)nullptr, uin, uout, f, cf, acc, partials, active)
 #define BXMG_SWN(ZERO, KIND, POST)                   \
     if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST); \
     else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST); \
@@ -422,6 +505,8 @@ hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post,
         if (zero) { BXMG_SWN(true, kSweepRestrict, false); } else { BXMG_SWN(false, kSweepRestrict, false); }
     } else if (kind == kSweepNorm && post && std::is_same<T, double>::value) {
         if constexpr (std::is_same<T, double>::value) { BXMG_SWN(false, kSweepNorm, true); }
+    } else if (kind == kSweepAdd && post && std::is_same<T, float>::value) {
+        if constexpr (std::is_same<T, float>::value) { BXMG_SWN(false, kSweepAdd, true); }
     } else if (kind == kSweepPlain && post) {
         BXMG_SWN(false, kSweepPlain, true);
     } else {
@@ -432,8 +517,24 @@ hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post,
     return hipGetLastError();
 }
 template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, int, const double*, double*,
-                                         const double*, double*, double*, const int*);
+                                         const double*, double*, double*, double*, const int*);
 template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, int, const float*, float*,
-                                        const float*, float*, double*, const int*);
+                                        const float*, float*, double*, double*, const int*);
+
+hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* where, int blocks, int threads,
+                             int kind, const float* uin, float* uout, const float* f, float* cf, double* acc,
+                             const int* active) {
+    if (blocks <= 0) return hipSuccess;
+    if (threads > kSweepJobThreads) return hipErrorInvalidValue;
+#define BXMG_SWJ(ZERO, KIND, POST)                                                                               \
+    hipLaunchKernelGGL((k_sweep<float, kSweepJobThreads, ZERO, KIND, POST, true>), dim3(blocks), dim3(threads), 0, s, \
+                       SweepArgs{}, jobs, where, uin, uout, f, cf, acc, (double*)nullptr, active)
+    if (kind == kSweepRestrict) BXMG_SWJ(true, kSweepRestrict, false);
+    else if (kind == kSweepPlain) BXMG_SWJ(false, kSweepPlain, true);
+    else if (kind == kSweepAdd) BXMG_SWJ(false, kSweepAdd, true);
+    else return hipErrorInvalidValue;
+#undef BXMG_SWJ
+    return hipGetLastError();
+}
 
 }  // namespace bxmg
