@@ -558,7 +558,7 @@ void plan_streams(bxmg_batch_s* b) {
                 std::array<SweepPlan, 2> P;
                 for (int k = 0; k < 2; ++k)
                     P[k] = plan_sweep_level(G.L[l].rb[0], G.L[l + 1].rb[0], G.per,
-                                            k == 0 ? kSweepRestrict : l ? kSweepPlain : kSweepAdd, k == 0, true, cus,
+                                            k == 0 ? kSweepRestrict : l ? kSweepPlain : kSweepAdd, k == 0, true, 0, cus,
                                             kSweepJobThreads);
                 it = plans.emplace(&G, P).first;
             }

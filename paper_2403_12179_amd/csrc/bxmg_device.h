@@ -27,6 +27,11 @@ struct Recip {
     }
 };
 
+template <class T>
+__device__ __forceinline__ T harm(T a, T b) {
+    return (a * b) * T(2) / (a + b);
+}
+
 // Fixed-tree block reduction of (max, sum, sum): wave64 butterflies, then
 // the 4 wave results in order.  The result is valid in thread 0.
 __device__ __forceinline__ void block_reduce3(double& mx, double& s2, double& bad, double* sh) {

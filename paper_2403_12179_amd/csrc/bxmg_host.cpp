@@ -187,23 +187,26 @@ static void upload_tiles(const TileSet& t, DevBuf<Tile>& buf, int& n) {
     n = (int)t.tiles.size();
 }
 
-// Levels the streaming smoother takes: one box, constant coefficient, 32-bit
-// storage, above the coarse cycle (below it the levels run in one workgroup).
+// Levels the streaming smoother takes: one box, 32-bit offsets, above the
+// coarse cycle (below it the levels run in one workgroup); with a variable
+// coefficient in FP32 only, as its FP64 form would not fit the registers.
 static void plan_streams(Hier* H, long long& max_tiles) {
     const size_t nl = H->L.size();
     H->a64.resize(nl);
     H->a32.resize(nl);
     const size_t end = H->coarse_start >= 0 ? (size_t)H->coarse_start : nl - 1;
-    for (size_t l = 0; l < end && !H->var; ++l) {
+    const bool f32 = H->precision == 1;
+    for (size_t l = 0; l < end && (!H->var || f32); ++l) {
         Level& L = *H->L[l];
         const Level& C = *H->L[l + 1];
         if (L.boxes.size() != 1 || C.boxes.size() != 1 || !L.push || !L.res) continue;
-        const bool f32 = H->precision == 1;
+        if (L.boxes[0].cells() != L.dom.cells()) continue;
+        const int mode = H->var ? (l == 0 ? 1 : 2) : 0;
         bool ok = true;
         for (int kind = 0; kind < 4; ++kind)
             for (int zero = 0; zero < 2; ++zero) {
                 SweepPlan& P = L.sweep[kind][zero];
-                P = plan_sweep_level(L.rb[0], C.rb[0], H->per, kind, zero != 0, f32);
+                P = plan_sweep_level(L.rb[0], C.rb[0], H->per, kind, zero != 0, f32, mode);
                 ok = ok && P.nt > 0;
                 max_tiles = std::max<long long>(max_tiles, P.blocks);
             }
@@ -579,6 +582,7 @@ void vcycle(Run& R, size_t l) {
     const Level& L = *H->L[l];
     const Level& C = *H->L[l + 1];
     const bool stream = R.streams(l);
+    const int mode = H->var ? (l == 0 ? 1 : 2) : 0;
     // the array the prolongation corrects
     T* u = stream ? lvl_a<T>(H, l) : lvl_u<T>(H, l);
     if (stream) {
@@ -586,7 +590,7 @@ void vcycle(Run& R, size_t l) {
         const SweepPlan& P = L.sweep[kSweepRestrict][zero ? 1 : 0];
         R.pre(l, kStageGS);
         HIPCHK(launch_sweep<T>(R.s, P, zero, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
-                               lvl_f<T>(H, l + 1), nullptr, nullptr, R.active));
+                               lvl_f<T>(H, l + 1), nullptr, nullptr, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l)));
         R.post(l, kStageGS);
     } else {
     smooth<T>(R, l, R.nu1);
@@ -628,7 +632,7 @@ void vcycle(Run& R, size_t l) {
     const SweepPlan& P = L.sweep[kind][0];
     R.pre(l, kStageGS);
     HIPCHK(launch_sweep<T>(R.s, P, false, true, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
-                           R.stream_add, R.stream_norms, R.active));
+                           R.stream_add, R.stream_norms, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l)));
     R.post(l, kStageGS);
     if (norm) R.streamed = P.blocks;
 }

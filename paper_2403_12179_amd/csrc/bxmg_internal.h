@@ -254,21 +254,23 @@ struct SweepPlan {
     SweepArgs args{};
 };
 // The blocks of a level of n cells (storage and coarse fields of args unset),
-// for cus compute units, at most ntmax threads each.
-SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int cus = 256,
+// for cus compute units, at most ntmax threads each.  mode: as in launch_sweep.
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode = 0, int cus = 256,
                      int ntmax = 1024);
 // The same for the one-box level B over the one-box level Q, all of args set;
 // nt = 0 if the level cannot be streamed.
 SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32,
-                           int cus = 256, int ntmax = 1024);
+                           int mode = 0, int cus = 256, int ntmax = 1024);
 // uin (not read when zero: the sweeps start from u = 0) -> uout, another
 // array.  post: the sweeps after a prolongation that left colour 0 to them
 // (launch_prolong, only_c1).  uout's ghosts are not written.  cf: the coarse f
 // (kSweepRestrict); acc: what the result is added to, its face ghosts
-// refreshed (kSweepAdd); partials: 3 per block (kSweepNorm).
+// refreshed (kSweepAdd); partials: 3 per block (kSweepNorm).  mode 0: constant
+// coefficient; FP32 only, 1: the cell beta, 2: face arrays fat[args.pid].
 template <class T>
 hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
-                        const T* f, T* cf, double* acc, double* partials, const int* active);
+                        const T* f, T* cf, double* acc, double* partials, const int* active, int mode,
+                        const T* beta, const FaceArrays<T>* fat);
 // FP32 over many levels in one launch of blocks of threads threads: block b
 // works block where[b].y of the level jobs[where[b].x], planned for at most
 // kSweepJobThreads threads.  kSweepRestrict (from zero), kSweepPlain, kSweepAdd.

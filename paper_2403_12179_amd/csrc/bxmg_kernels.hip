@@ -72,11 +72,6 @@ __device__ __forceinline__ long long fab_idx(const FBox& b, int i, int j, int k)
     return b.base + (long long)(i - b.glo[0]) + (long long)b.G[0] * ((long long)(j - b.glo[1]) + (long long)b.G[1] * (k - b.glo[2]));
 }
 
-template <class T>
-__device__ __forceinline__ T harm(T a, T b) {
-    return (a * b) * T(2) / (a + b);
-}
-
 // alpha h^2: the Helmholtz term's addition to the stencil's diagonal weight
 // sb (an exact zero for Poisson)
 template <class T>

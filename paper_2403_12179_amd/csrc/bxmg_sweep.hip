@@ -37,6 +37,16 @@
 // 3.37 ms.  Adding an FP32 correction to the FP64 iterate (kSweepAdd) takes
 // 415 us over the 52 million cells of 64 problems, 240 of which are its bytes
 // at the copy rate.
+//
+// With a coefficient (FP32) a thread has the 9 faces of its pair formed once
+// per plane and kept in 60 registers: a half-sweep launch forms 6 harmonic
+// means per cell, each a division.  Bound by that arithmetic (about 240
+// instructions a step, 140 of them the 13 divisions) times the recomputed
+// halo: 512^3, cell beta, sweeps from zero with residual and restriction 1380
+// us against 4 x 396 + 615, sweeps after the prolongation 1080 against 4 x
+// 396; 256^3 with face arrays 161 and 163 us against 4 x 60 + 97 and 4 x 60.
+// The 512^3 preconditioned solve went from 164 to 133 ms, the 128^3 mixed one
+// from 7.4 to 6.4 (its level 0 takes as long either way).
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -89,18 +99,22 @@ struct Raw<float> {
 // kSweepAdd: the result is added to acc (and its face ghosts refreshed)
 // instead of being stored.  JOBS: many levels in one launch; block b works
 // block where[b].y of job where[b].x (none: -1).
-template <class T, int NT, bool ZERO, int KIND, bool POST, bool JOBS>
+// MODE: 0 constant coefficient; 1 cell beta, faces are harmonic means; 2 face
+// arrays (fat).  The coefficients of a pair's faces and their sums are formed
+// (or loaded) once per plane, for all stages, and stay in registers.
+template <class T, int NT, bool ZERO, int KIND, bool POST, bool JOBS, int MODE>
 __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __restrict__ jobs,
                                              const int2* __restrict__ where, const T* __restrict__ uin,
                                              T* __restrict__ uout, const T* __restrict__ f, T* __restrict__ cf,
                                              double* __restrict__ acc, double* __restrict__ partials,
-                                             const int* __restrict__ active) {
+                                             const int* __restrict__ active, const T* __restrict__ beta,
+                                             const FaceArrays<T>* __restrict__ fat) {
     using std::integral_constant;
     constexpr bool REST = KIND == kSweepRestrict, NORM = KIND == kSweepNorm, ADD = KIND == kSweepAdd;
     constexpr bool RES = REST || NORM;
     // LDS half planes (one colour of one plane of the block's columns)
-    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bS = 12, nBuf = REST ? 14 : RES ? 12 : 10;
-    __shared__ T lds[nBuf * NT];
+    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bS = 12, bK = REST ? 14 : RES ? 12 : 10;
+    __shared__ T lds[(bK + (MODE == 1 ? 4 : 0)) * NT];  // bK, bK + 2: beta of colour 0, 1
     const int tid = threadIdx.x;
     // block -> (bx, by, bz), neighbouring blocks on one XCD
     int blk = blockIdx.x, job = 0;
@@ -140,7 +154,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
     const int z0 = bz * A.ZC, zlim = min(z0 + A.ZC, n2);
     // first plane loaded: the halo below, rounded to an even plane so that a
     // step's plane parity is known at compile time
-    constexpr int kHalo = (RES ? 5 : 4) - (ZERO ? 1 : 0), kFirst = (kHalo + 1) & ~1;
+    constexpr int kHalo = (RES ? 5 : 4) - (ZERO && MODE != 1 ? 1 : 0), kFirst = (kHalo + 1) & ~1;
     const int zs = perz ? z0 - kFirst : max(0, z0 - kFirst);
     const int zend = zlim + (REST ? 6 : RES ? 5 : 4);  // one past the last step
     const int zmax = min(zlim + (RES ? 4 : 3), perz ? zlim + 4 : n2 - 1);  // last plane with values in use
@@ -173,7 +187,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         gB = fxB ? ((y + 1) * A.H + (yo ? 0 : nm)) * es : fy ? (gy + 1 - yo) * es : kOffPastBox;
     }
     const T h2 = (T)(A.h * A.h), ih2 = (T)(1.0 / (A.h * A.h));
-    const T sb = T(6) + (T)(A.a * (A.h * A.h));
+    const T dg = (T)(A.a * (A.h * A.h)), sb = T(6) + dg;
     const Recip<T> rsb(sb);
     const int bytes = 2 * A.cs * es;
     const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
@@ -186,6 +200,28 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
     const int aA = own ? (row + yo) * 8 : kOffPastBox, aB = own ? (row + 1 - yo) * 8 : kOffPastBox;
     double a0[4] = {}, a1[4] = {};  // indexed by plane modulo 4
 
+    // MODE 1: the cell beta; MODE 2: the face arrays and the pair's offsets in
+    // them (x: the outer faces of the A and B cell; y, z: the cell's lower face)
+    const auto Rk = __builtin_amdgcn_make_buffer_rsrc((void*)(MODE == 1 ? beta : f), (short)0, bytes, kBufferDword3);
+    __amdgpu_buffer_rsrc_t R0, R1, R2;
+    int ox = 0, oxA = 0, oxB = 0, oyA = 0, oyB = 0, ozA = 0, ozB = 0, px = 0, py = 0, pz = 0;
+    if constexpr (MODE == 2) {
+        const FaceArrays<T> fa = fat[A.pid];
+        const int n0 = A.n[0];
+        px = (n0 + 1) * n1 * es;
+        py = n0 * (n1 + 1) * es;
+        pz = n0 * n1 * es;
+        R0 = __builtin_amdgcn_make_buffer_rsrc((void*)fa.c[0], (short)0, px * n2, kBufferDword3);
+        R1 = __builtin_amdgcn_make_buffer_rsrc((void*)fa.c[1], (short)0, py * n2, kBufferDword3);
+        R2 = __builtin_amdgcn_make_buffer_rsrc((void*)fa.c[2], (short)0, pz * (n2 + 1), kBufferDword3);
+        const int xr = 2 * m + (n0 + 1) * y, yr0 = 2 * m + n0 * y;
+        ox = in ? (xr + 1) * es : kOffPastBox;
+        oxA = in ? (xr + 2 * yo) * es : kOffPastBox;
+        oxB = in ? (xr + 2 - 2 * yo) * es : kOffPastBox;
+        oyA = ozA = in ? (yr0 + yo) * es : kOffPastBox;
+        oyB = ozB = in ? (yr0 + 1 - yo) * es : kOffPastBox;
+    }
+
     // the column's registers, indexed by plane modulo 8 (only a few of each
     // are live): values of colour 0 (r) and 1 (b) after 0..4 half-sweeps
     T r0[8], b0[8], r1[8], b2[8], r3[8], b4[8], fr[8], fb[8];
@@ -193,6 +229,20 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
     for (int k = 0; k < 8; ++k) {
         r0[k] = T(0); b0[k] = T(0); r1[k] = T(0); b2[k] = T(0);
         r3[k] = T(0); b4[k] = T(0); fr[k] = T(0); fb[k] = T(0);
+    }
+    // coefficients of the colour-c cell: inner (shared) and outer x face, y
+    // faces, lower z face, the sum of its faces; be: MODE 1's cell beta
+    T kin[8], ko[2][8], kd[2][8], ku[2][8], zl[2][8], ks[2][8], be[2][8];
+    if constexpr (MODE != 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            kin[k] = T(0);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                ko[c][k] = T(0); kd[c][k] = T(0); ku[c][k] = T(0);
+                zl[c][k] = T(0); ks[c][k] = T(0); be[c][k] = T(0);
+            }
+        }
     }
     T sprev = T(0), half = T(0);  // restriction: this row's pair sum, the even plane's sum of four
     double mx = 0.0, s2 = 0.0;
@@ -212,6 +262,24 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         const int vr = (PH & 1) ? vB : vA, vb = (PH & 1) ? vA : vB;
         fr[PH] = Raw<T>::ld(Rf, vr, zo);
         fb[PH] = Raw<T>::ld(Rf, vb, zo + co);
+        if constexpr (MODE == 1) {
+            be[0][PH] = Raw<T>::ld(Rk, vr, zo);
+            be[1][PH] = Raw<T>::ld(Rk, vb, zo + co);
+        }
+        if constexpr (MODE == 2) {
+            kin[PH] = Raw<T>::ld(R0, ox, z * px);
+            ko[0][PH] = Raw<T>::ld(R0, (PH & 1) ? oxB : oxA, z * px);
+            ko[1][PH] = Raw<T>::ld(R0, (PH & 1) ? oxA : oxB, z * px);
+            const int yr = (PH & 1) ? oyB : oyA, yb = (PH & 1) ? oyA : oyB, row1 = A.n[0] * es;
+            kd[0][PH] = Raw<T>::ld(R1, yr, z * py);
+            ku[0][PH] = Raw<T>::ld(R1, yr, z * py + row1);
+            kd[1][PH] = Raw<T>::ld(R1, yb, z * py);
+            ku[1][PH] = Raw<T>::ld(R1, yb, z * py + row1);
+            // (past a Dirichlet domain: the face on its upper side)
+            const int zf = !perz && q == n2 ? n2 : z;
+            zl[0][PH] = Raw<T>::ld(R2, (PH & 1) ? ozB : ozA, zf * pz);
+            zl[1][PH] = Raw<T>::ld(R2, (PH & 1) ? ozA : ozB, zf * pz);
+        }
         if constexpr (ADD) {
             const bool mine = q - 4 >= z0 && q - 4 < zlim;
             const int zd = (q - 3) * A.GH * 8;
@@ -246,8 +314,8 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         // neighbour sum of the colour-c cell of plane q - D: own_o = the
         // pair's other cell; oldv = the cell's own value before the update
         // (x- + x+ commutes, so the own cell's side does not matter)
-        auto sum = [&](auto dd, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
-            constexpr int D = decltype(dd)::value;
+        auto sum = [&](auto dd, auto cc, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
+            constexpr int D = decltype(dd)::value, C = decltype(cc)::value;
             if constexpr (EDGE > 0) {
                 const T g = POST && D == 1 ? oldv : -oldv;  // (stage 1 after a prolongation: the ghost's value)
                 n.x = (isA ? fxA : fxB) ? g : n.x;
@@ -258,8 +326,18 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
                     zp = !perz && q == D + n2 - 1 ? g : zp;
                 }
             }
-            return ((own_o + n.x) + (n.d + n.u)) + (zm + zp);
+            if constexpr (MODE == 0) return ((own_o + n.x) + (n.d + n.u)) + (zm + zp);
+            else
+                return ((kin[RS(D)] * own_o + ko[C][RS(D)] * n.x) + (kd[C][RS(D)] * n.d + ku[C][RS(D)] * n.u)) +
+                       (zl[C][RS(D)] * zm + zl[1 - C][RS(D - 1)] * zp);
         };
+        // the cell's new value from (neighbour sum - h^2 f)
+        auto relax = [&](auto dd, auto cc, T v) {
+            if constexpr (MODE == 0) return rsb.div(v);
+            else return v / ks[decltype(cc)::value][RS(decltype(dd)::value)];
+        };
+        constexpr integral_constant<int, 0> c0{};
+        constexpr integral_constant<int, 1> c1{};
         // every LDS value of the step, written in earlier steps
         Three t1{}, t2, t3, t4, t5r{}, t5b{};
         T spart = T(0);
@@ -272,29 +350,62 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
             t5b = near(bR3 + ((PH - 2) & 3), ISA(5, 1));
         }
         if constexpr (REST) spart = lds[(bS + ((PH - 1) & 1)) * NT + sup];
+        if constexpr (MODE == 1) {
+            const Three k0 = near(bK + 2 + ((PH - 1) & 1), ISA(1, 0)), k1 = near(bK + ((PH - 1) & 1), ISA(1, 1));
+            lds[(bK + (PH & 1)) * NT + tid] = be[0][RS(0)];
+            lds[(bK + 2 + (PH & 1)) * NT + tid] = be[1][RS(0)];
+            kin[RS(1)] = harm(be[0][RS(1)], be[1][RS(1)]);
+            // beyond a Dirichlet face beta is the cell's own
+            auto faces = [&](auto cc, bool isA, Three k) {
+                constexpr int C = decltype(cc)::value;
+                T lo = be[1 - C][RS(1)], hi = be[C][RS(0)];
+                if constexpr (EDGE > 0) {
+                    const T b = be[C][RS(1)];
+                    k.x = (isA ? fxA : fxB) ? b : k.x;
+                    if constexpr (EDGE > 1) {
+                        k.d = fyl ? b : k.d;
+                        k.u = fyr ? b : k.u;
+                        lo = !perz && q == 0 ? hi : lo;
+                        hi = !perz && q == n2 ? lo : hi;
+                    }
+                }
+                ko[C][RS(1)] = harm(be[C][RS(1)], k.x);
+                kd[C][RS(1)] = harm(k.d, be[C][RS(1)]);
+                ku[C][RS(1)] = harm(be[C][RS(1)], k.u);
+                zl[C][RS(0)] = harm(lo, hi);
+            };
+            faces(c0, ISA(1, 0), k0);
+            faces(c1, ISA(1, 1), k1);
+        }
+        if constexpr (MODE != 0) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                ks[c][RS(1)] = (((kin[RS(1)] + ko[c][RS(1)]) + (kd[c][RS(1)] + ku[c][RS(1)])) +
+                                (zl[c][RS(1)] + zl[1 - c][RS(0)])) + dg;
+        }
         // plane q enters: colour 1 for stage 1's neighbours
         if constexpr (!ZERO) lds[(bB0 + (PH & 1)) * NT + tid] = b0[RS(0)];
         {  // stage 1
             T su = T(0);
             if constexpr (!ZERO)
-                su = sum(integral_constant<int, 1>(), ISA(1, 0), b0[RS(1)], t1, b0[RS(2)], b0[RS(0)], r0[RS(1)]);
-            r1[RS(1)] = rsb.div(su - h2 * fr[RS(1)]);
+                su = sum(integral_constant<int, 1>(), c0, ISA(1, 0), b0[RS(1)], t1, b0[RS(2)], b0[RS(0)], r0[RS(1)]);
+            r1[RS(1)] = relax(integral_constant<int, 1>(), c0, su - h2 * fr[RS(1)]);
             lds[(bR1 + (PH & 1)) * NT + tid] = r1[RS(1)];
         }
         {  // stage 2
-            const T su = sum(integral_constant<int, 2>(), ISA(2, 1), r1[RS(2)], t2, r1[RS(3)], r1[RS(1)],
+            const T su = sum(integral_constant<int, 2>(), c1, ISA(2, 1), r1[RS(2)], t2, r1[RS(3)], r1[RS(1)],
                              ZERO ? T(0) : b0[RS(2)]);
-            b2[RS(2)] = rsb.div(su - h2 * fb[RS(2)]);
+            b2[RS(2)] = relax(integral_constant<int, 2>(), c1, su - h2 * fb[RS(2)]);
             lds[(bB2 + (PH & 1)) * NT + tid] = b2[RS(2)];
         }
         {  // stage 3
-            const T su = sum(integral_constant<int, 3>(), ISA(3, 0), b2[RS(3)], t3, b2[RS(4)], b2[RS(2)], r1[RS(3)]);
-            r3[RS(3)] = rsb.div(su - h2 * fr[RS(3)]);
+            const T su = sum(integral_constant<int, 3>(), c0, ISA(3, 0), b2[RS(3)], t3, b2[RS(4)], b2[RS(2)], r1[RS(3)]);
+            r3[RS(3)] = relax(integral_constant<int, 3>(), c0, su - h2 * fr[RS(3)]);
             lds[(bR3 + (PH & 3)) * NT + tid] = r3[RS(3)];
         }
         {  // stage 4
-            const T su = sum(integral_constant<int, 4>(), ISA(4, 1), r3[RS(4)], t4, r3[RS(5)], r3[RS(3)], b2[RS(4)]);
-            b4[RS(4)] = rsb.div(su - h2 * fb[RS(4)]);
+            const T su = sum(integral_constant<int, 4>(), c1, ISA(4, 1), r3[RS(4)], t4, r3[RS(5)], r3[RS(3)], b2[RS(4)]);
+            b4[RS(4)] = relax(integral_constant<int, 4>(), c1, su - h2 * fb[RS(4)]);
             if constexpr (RES) lds[(bB4 + (PH & 1)) * NT + tid] = b4[RS(4)];
         }
         {  // plane q-4 is final
@@ -336,11 +447,11 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         }
         if constexpr (RES) {  // stage 5
             const T sur =
-                sum(integral_constant<int, 5>(), ISA(5, 0), b4[RS(5)], t5r, b4[RS(6)], b4[RS(4)], r3[RS(5)]);
-            const T rr = fr[RS(5)] - (sur - sb * r3[RS(5)]) * ih2;
+                sum(integral_constant<int, 5>(), c0, ISA(5, 0), b4[RS(5)], t5r, b4[RS(6)], b4[RS(4)], r3[RS(5)]);
+            const T rr = fr[RS(5)] - (sur - (MODE == 0 ? sb : ks[0][RS(5)]) * r3[RS(5)]) * ih2;
             const T sub =
-                sum(integral_constant<int, 5>(), ISA(5, 1), r3[RS(5)], t5b, r3[RS(6)], r3[RS(4)], b4[RS(5)]);
-            const T rb = fb[RS(5)] - (sub - sb * b4[RS(5)]) * ih2;
+                sum(integral_constant<int, 5>(), c1, ISA(5, 1), r3[RS(5)], t5b, r3[RS(6)], r3[RS(4)], b4[RS(5)]);
+            const T rb = fb[RS(5)] - (sub - (MODE == 0 ? sb : ks[1][RS(5)]) * b4[RS(5)]) * ih2;
             if constexpr (NORM) {
                 const int p = q - 5;
                 const bool mine = own && p >= z0 && p < zlim;
@@ -410,14 +521,15 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
 // most 1024 columns is priced as (rounds of blocks over the 256 CUs) x (steps
 // of a block) x (time of a step), a step being latency-bound with few waves
 // on a CU and issue-bound with many; the cheapest is taken.
-SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int cus, int ntmax) {
+SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode, int cus, int ntmax) {
     SweepPlan best;
     const bool res = kind == kSweepRestrict || kind == kSweepNorm;
-    const int halo = (res ? 5 : 4) - (zero ? 1 : 0);
+    const int halo = (res ? 5 : 4) - (zero && mode != 1 ? 1 : 0);
     const int lead = ((halo + 1) & ~1) + (kind == kSweepRestrict ? 6 : res ? 5 : 4);
     const int nm = n[0] / 2;
-    // (the FP64 forms keep up to 168 registers a thread: at most 12 waves)
-    ntmax = std::min(ntmax, f32 ? 1024 : 768);
+    // (the FP64 forms and those with coefficients keep up to 168 registers a
+    // thread: at most 12 waves)
+    ntmax = std::min(ntmax, f32 && mode == 0 ? 1024 : 768);
     double cost = 1e30;
     auto split = [](int cells, int pieces, int unit) {  // the size of equal pieces, a multiple of unit
         const int u = cells / unit, q = (u + pieces - 1) / pieces;
@@ -437,7 +549,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
             if (cols > ntmax) continue;
             const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : cols <= 768 ? 768 : 1024;
             const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
-            const int fit = nt == 256 ? 5 : nt == 512 ? 2 : 1;  // blocks a CU holds (registers)
+            const int fit = mode ? (nt == 256 ? 3 : 1) : nt == 256 ? 5 : nt == 512 ? 2 : 1;  // blocks a CU holds (registers)
             for (int pz = 1; pz <= n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
                 const int ZC = split(n[2], pz, 2);
                 const int nbz = (n[2] + ZC - 1) / ZC;
@@ -445,7 +557,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
                 const long long per_cu = (blocks + cus - 1) / cus;
                 const long long rounds = (per_cu + fit - 1) / fit;
                 const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
-                const double step = std::max(1000.0, 300.0 + (f32 ? 110.0 : 130.0) * waves);
+                const double step = std::max(mode ? 1500.0 : 1000.0, 300.0 + (mode ? 300.0 : f32 ? 110.0 : 130.0) * waves);
                 const double c = rounds * (ZC + lead) * step + 1e-3 * blocks;
                 if (c < cost) {
                     cost = c;
@@ -466,14 +578,14 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
     return best;
 }
 
-SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32, int cus,
-                           int ntmax) {
+SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32, int mode,
+                           int cus, int ntmax) {
     int n[3];
     for (int d = 0; d < 3; ++d) {
         n[d] = B.hi[d] - B.lo[d] + 1;
         if (n[d] % 2 || n[d] < 4 || (B.lo[d] & 1)) return SweepPlan{};
     }
-    SweepPlan P = plan_sweep(n, per, kind, zero, f32, cus, ntmax);
+    SweepPlan P = plan_sweep(n, per, kind, zero, f32, mode, cus, ntmax);
     SweepArgs& A = P.args;
     A.H = B.H;
     A.GH = B.H * B.G[1];
@@ -490,36 +602,53 @@ SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int k
 
 template <class T>
 hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
-                        const T* f, T* cf, double* acc, double* partials, const int* active) {
+                        const T* f, T* cf, double* acc, double* partials, const int* active, int mode, const T* beta,
+                        const FaceArrays<T>* fat) {
     const dim3 G((unsigned)P.blocks);
-#define BXMG_SW(NT, ZERO, KIND, POST)                                                                        \
-    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, false>), G, dim3(P.threads), 0, s, P.args,          \
-                       (const SweepArgs*)nullptr, (const int2*)nullptr, uin, uout, f, cf, acc, partials, active)
-#define BXMG_SWN(ZERO, KIND, POST)                   \
-    if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST); \
-    else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST); \
-    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST); \
-    else if constexpr (sizeof(T) == 4) BXMG_SW(1024, ZERO, KIND, POST); \
+    constexpr bool F64 = std::is_same<T, double>::value;
+#define BXMG_SW(NT, ZERO, KIND, POST, MODE)                                                                       \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, false, MODE>), G, dim3(P.threads), 0, s, P.args,         \
+                       (const SweepArgs*)nullptr, (const int2*)nullptr, uin, uout, f, cf, acc, partials, active, \
+                       beta, fat)
+#define BXMG_SWN(ZERO, KIND, POST, MODE)                   \
+    if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST, MODE); \
+    else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST, MODE); \
+    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST, MODE); \
+    else if constexpr (!F64 && MODE == 0) BXMG_SW(1024, ZERO, KIND, POST, MODE); \
     else return hipErrorInvalidValue
-    if (kind == kSweepRestrict && !post) {
-        if (zero) { BXMG_SWN(true, kSweepRestrict, false); } else { BXMG_SWN(false, kSweepRestrict, false); }
-    } else if (kind == kSweepNorm && post && std::is_same<T, double>::value) {
-        if constexpr (std::is_same<T, double>::value) { BXMG_SWN(false, kSweepNorm, true); }
-    } else if (kind == kSweepAdd && post && std::is_same<T, float>::value) {
-        if constexpr (std::is_same<T, float>::value) { BXMG_SWN(false, kSweepAdd, true); }
+#define BXMG_SWM(ZERO, KIND, POST)                                \
+    if (mode == 0) { BXMG_SWN(ZERO, KIND, POST, 0); }             \
+    else if constexpr (!F64) {                                    \
+        if (mode == 1) { BXMG_SWN(ZERO, KIND, POST, 1); }         \
+        else { BXMG_SWN(ZERO, KIND, POST, 2); }                   \
+    } else return hipErrorInvalidValue
+    if (kind == kSweepRestrict && !post && zero) {
+        BXMG_SWM(true, kSweepRestrict, false);
+    } else if (kind == kSweepRestrict && !post && F64) {  // (FP32 levels start from zero)
+        if constexpr (F64) { BXMG_SWM(false, kSweepRestrict, false); }
+    } else if (kind == kSweepNorm && post && F64) {
+        if constexpr (F64) { BXMG_SWM(false, kSweepNorm, true); }
+    } else if (kind == kSweepAdd && post && !F64 && mode < 2) {  // (a level 0)
+        if constexpr (!F64) {
+            if (mode == 0) { BXMG_SWN(false, kSweepAdd, true, 0); }
+            else { BXMG_SWN(false, kSweepAdd, true, 1); }
+        }
     } else if (kind == kSweepPlain && post) {
-        BXMG_SWN(false, kSweepPlain, true);
+        BXMG_SWM(false, kSweepPlain, true);
     } else {
         return hipErrorInvalidValue;
     }
+#undef BXMG_SWM
 #undef BXMG_SWN
 #undef BXMG_SW
     return hipGetLastError();
 }
 template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, int, const double*, double*,
-                                         const double*, double*, double*, double*, const int*);
+                                         const double*, double*, double*, double*, const int*, int, const double*,
+                                         const FaceArrays<double>*);
 template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, int, const float*, float*,
-                                        const float*, float*, double*, double*, const int*);
+                                        const float*, float*, double*, double*, const int*, int, const float*,
+                                        const FaceArrays<float>*);
 
 hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* where, int blocks, int threads,
                              int kind, const float* uin, float* uout, const float* f, float* cf, double* acc,
@@ -527,8 +656,9 @@ hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* w
     if (blocks <= 0) return hipSuccess;
     if (threads > kSweepJobThreads) return hipErrorInvalidValue;
 #define BXMG_SWJ(ZERO, KIND, POST)                                                                               \
-    hipLaunchKernelGGL((k_sweep<float, kSweepJobThreads, ZERO, KIND, POST, true>), dim3(blocks), dim3(threads), 0, s, \
-                       SweepArgs{}, jobs, where, uin, uout, f, cf, acc, (double*)nullptr, active)
+    hipLaunchKernelGGL((k_sweep<float, kSweepJobThreads, ZERO, KIND, POST, true, 0>), dim3(blocks), dim3(threads), 0, s, \
+                       SweepArgs{}, jobs, where, uin, uout, f, cf, acc, (double*)nullptr, active, (const float*)nullptr, \
+                       (const FaceArrays<float>*)nullptr)
     if (kind == kSweepRestrict) BXMG_SWJ(true, kSweepRestrict, false);
     else if (kind == kSweepPlain) BXMG_SWJ(false, kSweepPlain, true);
     else if (kind == kSweepAdd) BXMG_SWJ(false, kSweepAdd, true);

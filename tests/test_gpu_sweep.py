@@ -61,6 +61,39 @@ def test_streamed_equals_half_sweeps(bx, n, lo, per, precision):
             assert abs(a - b).max() <= 1e-9 * abs(b).max()
 
 
+@pytest.mark.parametrize("n,per", [
+    ((32, 32, 32), (1, 1, 1)),
+    ((96, 48, 80), (0, 0, 0)),
+    ((16, 256, 16), (0, 1, 0)),
+    ((256, 16, 48), (0, 0, 1)),
+    ((32, 16, 208), (1, 1, 0)),
+    ((112, 144, 96), (1, 0, 0)),
+])
+def test_streamed_varcoef_equals_half_sweeps(bx, n, per):
+    """Coefficients over six decades, drawn cell by cell."""
+    bc = tuple(bx.PERIODIC if p else bx.DIRICHLET0 for p in per)
+    beta = 10.0 ** W.uniform_rhs(n, 63) ** 3 * 10.0 ** (2 * W.uniform_rhs(n, 64))
+    f = W.uniform_rhs(n, 61, mean_zero=all(per))
+    for par in (dict(), dict(alpha=977.25), dict(krylov=1)):
+        out = []
+        for knob in (1, 0):
+            ctx = bx.Context(0)
+            ctx.tune(2, knob)
+            ba = bx.BoxArray.chop((0, 0, 0), tuple(e - 1 for e in n), max(n), bc=bc)
+            phi = bx.MultiFab(ba, ctx=ctx).set_val(0.0).from_global(W.uniform_rhs(n, 62))
+            rhs = bx.MultiFab(ba, ctx=ctx).set_val(0.0).from_global(f)
+            bmf = bx.MultiFab(ba, ctx=ctx).set_val(1.0).from_global(beta)
+            res = bx.mlmg_solve(phi, rhs, bmf, precision=1, max_cycles=5, **par)
+            out.append((phi.to_global(), res))
+        (a, ra), (b, rb) = out
+        assert ra.cycles == rb.cycles and ra.status == rb.status
+        if not par.get("krylov"):
+            assert ra.hist == rb.hist
+            assert (a == b).all()
+        else:
+            assert abs(a - b).max() <= 1e-9 * abs(b).max()
+
+
 @pytest.mark.parametrize("per", [(1, 1, 1), (0, 0, 0), (1, 0, 1)])
 def test_streamed_batch_equals_half_sweeps(bx, per):
     sizes = [(32, 32, 32), (96, 48, 80), (16, 16, 16), (64, 64, 64), (16, 128, 32), (32, 32, 32), (40, 24, 56)]
