@@ -25,6 +25,7 @@
 #include <string>
 #include <vector>
 
+#include "bxmg_device.h"
 #include "bxmg_host.h"
 
 namespace bxmg {
@@ -216,8 +217,22 @@ __global__ void __launch_bounds__(kNB) k_nd_fnorm(NLev L, const double* __restri
     }
 }
 
-// full weighting onto the coarse unknowns (0 at the other coarse nodes), in
-// the order z, then y, then x offsets; the coarse u is zeroed on the way
+// the full weighting of r at coarse unknown (I, J, K), in the order z, then y,
+// then x offsets
+__device__ __forceinline__ double weighted(const NLev& F, const double* r, int I, int J, int K) {
+    const double w[3] = {0.25, 0.5, 0.25};
+    double s = 0.0;
+    for (int c = -1; c <= 1; ++c)
+        for (int b = -1; b <= 1; ++b)
+            for (int a = -1; a <= 1; ++a) {
+                const int i = wrap(F, 0, 2 * I + a), j = wrap(F, 1, 2 * J + b), k = wrap(F, 2, 2 * K + c);
+                s = s + ((w[a + 1] * w[b + 1]) * w[c + 1]) * r[nidx(F, i, j, k)];
+            }
+    return s;
+}
+
+// full weighting onto the coarse unknowns (0 at the other coarse nodes); the
+// coarse u is zeroed on the way
 __global__ void __launch_bounds__(kNB) k_nd_restrict(NLev F, const double* __restrict__ r, NLev C,
                                                     double* __restrict__ fc, double* __restrict__ uc, int kz) {
     const uint3 bk = xcd_block();
@@ -226,44 +241,45 @@ __global__ void __launch_bounds__(kNB) k_nd_restrict(NLev F, const double* __res
     if (t >= nx * ny) return;
     const int I = t % nx, J = t / nx;
     const int K0 = bk.y * kz, K1 = min(K0 + kz - 1, C.n[2]);
-    const double w[3] = {0.25, 0.5, 0.25};
     for (int K = K0; K <= K1; ++K) {
         const long long q = nidx(C, I, J, K);
-        double s = 0.0;
-        if (unknown(C, I, J, K)) {
-            for (int c = -1; c <= 1; ++c)
-                for (int b = -1; b <= 1; ++b)
-                    for (int a = -1; a <= 1; ++a) {
-                        const int i = wrap(F, 0, 2 * I + a), j = wrap(F, 1, 2 * J + b), k = wrap(F, 2, 2 * K + c);
-                        s = s + ((w[a + 1] * w[b + 1]) * w[c + 1]) * r[nidx(F, i, j, k)];
-                    }
-        }
-        fc[q] = s;
+        fc[q] = unknown(C, I, J, K) ? weighted(F, r, I, J, K) : 0.0;
         uc[q] = 0.0;
     }
 }
 
-// u_f += P e at the fine unknowns: fine node 2I + o takes the mean of the
-// coarse nodes I + o' (o' <= o), summed z, y, x
+// P e at fine node 2I + o: the mean of the coarse nodes I + o' (o' <= o),
+// summed z, y, x
+__device__ __forceinline__ double interpolated(const NLev& C, const double* e, int i, int j, int k) {
+    const int I[3] = {i >> 1, j >> 1, k >> 1}, o[3] = {i & 1, j & 1, k & 1};
+    double s = 0.0;
+    for (int cz = 0; cz <= o[2]; ++cz)
+        for (int cy = 0; cy <= o[1]; ++cy)
+            for (int cx = 0; cx <= o[0]; ++cx)
+                s = s + e[nidx(C, wrap(C, 0, I[0] + cx), wrap(C, 1, I[1] + cy), wrap(C, 2, I[2] + cz))];
+    return s * (1.0 / (double)(1 << (o[0] + o[1] + o[2])));  // (a power of two: the quotient's bits)
+}
+
+// u_f += P e at the fine unknowns of the colours from c0 on (with sweeps after
+// it colour 1 only: the first of them replaces colour 0 without reading it).
+// Threads take the sweeps' positions: of a row's nodes of one colour all have
+// the same parities, so a wave's lanes mostly sum the same 1, 2, 4 or 8 coarse
+// nodes.  256^3: 69 us, against 159 a thread per node of both colours.
 __global__ void __launch_bounds__(kNB) k_nd_prolong(NLev C, const double* __restrict__ e, NLev F,
-                                                   double* __restrict__ u) {
-    for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < F.size;
-         g += (long long)gridDim.x * blockDim.x) {
-        int i, j, k;
-        coords(F, g, i, j, k);
-        if (!unknown(F, i, j, k)) continue;
-        const long long q = nidx(F, i, j, k);
-        const int I[3] = {i >> 1, j >> 1, k >> 1}, o[3] = {i & 1, j & 1, k & 1};
-        double s = 0.0;
-        int cnt = 0;
-        for (int cz = 0; cz <= o[2]; ++cz)
-            for (int cy = 0; cy <= o[1]; ++cy)
-                for (int cx = 0; cx <= o[0]; ++cx) {
-                    s = s + e[nidx(C, wrap(C, 0, I[0] + cx), wrap(C, 1, I[1] + cy), wrap(C, 2, I[2] + cz))];
-                    ++cnt;
-                }
-        u[q] = u[q] + s / (double)cnt;
-    }
+                                                   double* __restrict__ u, int c0, int kz) {
+    const uint3 bk = xcd_block();
+    const int hx = (F.n[0] + 2) / 2, ny = F.n[1] + 1;
+    const int t = bk.x * kNB + threadIdx.x;
+    if (t >= hx * ny) return;
+    const int tx = t % hx, j = t / hx;
+    const int k0 = bk.y * kz, k1 = min(k0 + kz - 1, F.n[2]);
+    for (int k = k0; k <= k1; ++k)
+        for (int c = c0; c < 2; ++c) {
+            const int i = 2 * tx + ((c - j - k) & 1);
+            if (i > F.n[0] || !unknown(F, i, j, k)) continue;
+            const long long q = nidx(F, i, j, k);
+            u[q] = u[q] + interpolated(C, e, i, j, k);
+        }
 }
 
 // the periodic copies n_d take the values of their nodes 0
@@ -310,16 +326,12 @@ __global__ void __launch_bounds__(kNB) k_nd_sub(NLev L, double* __restrict__ u, 
     }
 }
 
-// Bottom: FP64 CG on the unknowns in one workgroup, vectors in device
-// memory (levels of a few thousand nodes, colour-split like the others);
-// fully periodic: right-hand side and solution projected to mean 0.  rtol
-// on the L2 norm, at most 4 N iterations.
+// Bottom: FP64 CG on the unknowns in one workgroup (vectors in device memory
+// or LDS, colour-split like the levels); fully periodic: right-hand side and
+// solution projected to mean 0.  rtol on the L2 norm, at most 4 N iterations.
 constexpr int kNBot = 1024;
-__global__ void __launch_bounds__(kNBot) k_nd_bottom(NLev L, double* __restrict__ x, const double* __restrict__ f,
-                                                    double* __restrict__ r, double* __restrict__ p,
-                                                    double* __restrict__ q, double rtol, int* __restrict__ iters) {
-    __shared__ double sh[2 * (kNBot / 64)];
-    __shared__ double bc[2];
+__device__ __forceinline__ void nd_bottom(const NLev& L, double* x, const double* f, double* r, double* p, double* q,
+                                          double rtol, int* iters, double* sh, double* bc) {
     const long long N = L.size;
     const bool sing = L.per[0] && L.per[1] && L.per[2];
     const double ih2 = 1.0 / (L.h * L.h);
@@ -422,6 +434,111 @@ __global__ void __launch_bounds__(kNBot) k_nd_bottom(NLev L, double* __restrict_
     }
     if (threadIdx.x == 0 && iters) *iters = it;
 }
+__global__ void __launch_bounds__(kNBot) k_nd_bottom(NLev L, double* __restrict__ x, const double* __restrict__ f,
+                                                    double* __restrict__ r, double* __restrict__ p,
+                                                    double* __restrict__ q, double rtol, int* __restrict__ iters) {
+    __shared__ double sh[2 * (kNBot / 64)];
+    __shared__ double bc[2];
+    nd_bottom(L, x, f, r, p, q, rtol, iters, sh, bc);
+}
+
+// The V-cycle from a small level down in one workgroup, every level's u, f and
+// r in LDS: f of the top level is read from device memory, its correction
+// written there.  One launch per phase, each of a few blocks, is bound by
+// launch and memory latency (3 to 6 us each, 11 phases a level); here a phase
+// is a barrier and a few LDS round trips.  Same stages, node by node in the
+// same arithmetic.  16^3 down to 2^3: 67 us a cycle against 120 in 34 launches.
+constexpr int kNCoarse = 8;  // levels (each halves every direction)
+struct NCoarse {
+    NLev L[kNCoarse];
+    int u[kNCoarse], f[kNCoarse], r[kNCoarse];  // offsets in LDS (elements)
+    int bp, bq;
+    int nl, nu1, nu2;
+    double rtol;
+};
+__global__ void __launch_bounds__(kNBot) k_nd_coarse(NCoarse C, const double* __restrict__ ftop,
+                                                    double* __restrict__ utop, int* __restrict__ iters) {
+    extern __shared__ double sm[];
+    __shared__ double sh[2 * (kNBot / 64)];
+    __shared__ double bc[2];
+    const int tid = threadIdx.x;
+    // the nodes of one colour (rows of half slots)
+    auto each = [&](const NLev& L, auto fn) {
+        const unsigned hx = L.H, ny = L.n[1] + 1, rows = ny * (L.n[2] + 1), n = hx * rows;
+        for (unsigned g = tid; g < n; g += kNBot) {
+            const unsigned row = g / hx, k = row / ny;
+            fn((int)g, (int)(g - row * hx), (int)(row - k * ny), (int)k);
+        }
+    };
+    const Recip<double> r6(6.0);
+    // a colour row's slot g is its offset in the colour block: neighbours are at
+    // fixed distances, but through a periodic face
+    auto sum6 = [&](const NLev& L, const double* u, int c, int g, int i, int j, int k) {
+        const int H = L.H, P = H * (L.n[1] + 1), par = i & 1;
+        const double* o = u + (1 - c) * (int)L.cs + g;
+        const int xm = i == 0 ? L.n[0] / 2 - 1 : par - 1, xp = i == L.n[0] - 1 && L.per[0] ? -(i >> 1) : par;
+        const int ym = j == 0 ? (L.n[1] - 1) * H : -H, yp = j == L.n[1] - 1 && L.per[1] ? -j * H : H;
+        const int zm = k == 0 ? (L.n[2] - 1) * P : -P, zp = k == L.n[2] - 1 && L.per[2] ? -k * P : P;
+        return ((o[xm] + o[xp]) + (o[ym] + o[yp])) + (o[zm] + o[zp]);
+    };
+    auto smooth = [&](const NLev& L, double* u, const double* f, int sweeps) {
+        const double h2 = L.h * L.h;
+        for (int c = 0; c < 2 * sweeps; ++c) {
+            each(L, [&](int g, int t, int j, int k) {
+                const int cc = c & 1, i = 2 * t + ((cc - j - k) & 1);
+                if (i > L.n[0] || !unknown(L, i, j, k)) return;
+                const int q = cc * (int)L.cs + g;
+                u[q] = r6.div(sum6(L, u, cc, g, i, j, k) - h2 * f[q]);
+            });
+            __syncthreads();
+        }
+    };
+    for (int q = tid; q < (int)C.L[0].alloc; q += kNBot) {
+        sm[C.f[0] + q] = ftop[q];
+        sm[C.u[0] + q] = 0.0;
+    }
+    __syncthreads();
+    for (int l = 0; l + 1 < C.nl; ++l) {
+        const NLev &L = C.L[l], &M = C.L[l + 1];
+        double *u = sm + C.u[l], *f = sm + C.f[l], *r = sm + C.r[l], *fc = sm + C.f[l + 1], *uc = sm + C.u[l + 1];
+        smooth(L, u, f, C.nu1);
+        const double ih2 = 1.0 / (L.h * L.h);
+        for (int c = 0; c < 2; ++c)
+            each(L, [&](int g, int t, int j, int k) {
+                const int i = 2 * t + ((c - j - k) & 1);
+                if (i > L.n[0]) return;
+                const int q = c * (int)L.cs + g;
+                r[q] = unknown(L, i, j, k) ? f[q] - (sum6(L, u, c, g, i, j, k) - 6.0 * u[q]) * ih2 : 0.0;
+            });
+        __syncthreads();
+        for (int c = 0; c < 2; ++c)
+            each(M, [&](int, int t, int J, int K) {
+                const int I = 2 * t + ((c - J - K) & 1);
+                if (I > M.n[0]) return;
+                const long long q = nidx(M, I, J, K);
+                fc[q] = unknown(M, I, J, K) ? weighted(L, r, I, J, K) : 0.0;
+                uc[q] = 0.0;
+            });
+        __syncthreads();
+    }
+    const int b = C.nl - 1;
+    nd_bottom(C.L[b], sm + C.u[b], sm + C.f[b], sm + C.r[b], sm + C.bp, sm + C.bq, C.rtol, iters, sh, bc);
+    __syncthreads();
+    for (int l = C.nl - 2; l >= 0; --l) {
+        const NLev &L = C.L[l], &M = C.L[l + 1];
+        double *u = sm + C.u[l], *e = sm + C.u[l + 1];
+        for (int c = C.nu2 > 0 ? 1 : 0; c < 2; ++c)
+            each(L, [&](int, int t, int j, int k) {
+                const int i = 2 * t + ((c - j - k) & 1);
+                if (i > L.n[0] || !unknown(L, i, j, k)) return;
+                const long long q = nidx(L, i, j, k);
+                u[q] = u[q] + interpolated(M, e, i, j, k);
+            });
+        __syncthreads();
+        smooth(L, u, sm + C.f[l], C.nu2);
+    }
+    for (int q = tid; q < (int)C.L[0].alloc; q += kNBot) utop[q] = sm[C.u[0] + q];
+}
 
 // Caller F-order node array <-> colour-split level array.
 template <bool TO_SPLIT>
@@ -465,7 +582,41 @@ struct NHier {
     DevBuf<double> part, bp, bq, fn;
     DevBuf<int> iters;
     std::string key;
+    int coarse = -1;      // first level of the one-workgroup cycle (-1: none)
+    NCoarse cc{};         // its levels
+    size_t coarse_lds = 0;
 };
+
+// The levels of the one-workgroup cycle: as many as fit its LDS.
+static void plan_coarse(NHier& H) {
+    const int nl = (int)H.L.size();
+    long long used = 2 * H.L[nl - 1].alloc;
+    int first = nl;
+    for (int l = nl - 1; l >= 1 && nl - l <= kNCoarse; --l) {
+        used += 3 * H.L[l].alloc;
+        if (used * 8 > lds_limit_bytes() - 1024) break;  // (1 KB: the kernel's own)
+        first = l;
+    }
+    if (first >= nl - 1) return;
+    NCoarse& C = H.cc;
+    int at = 0;
+    auto take = [&](long long n) {
+        const int o = at;
+        at += (int)n;
+        return o;
+    };
+    C.nl = nl - first;
+    for (int m = 0; m < C.nl; ++m) {
+        C.L[m] = H.L[first + m];
+        C.u[m] = take(C.L[m].alloc);
+        C.f[m] = take(C.L[m].alloc);
+        C.r[m] = take(C.L[m].alloc);
+    }
+    C.bp = take(H.L[nl - 1].alloc);
+    C.bq = take(H.L[nl - 1].alloc);
+    H.coarse = first;
+    H.coarse_lds = (size_t)at * 8;
+}
 
 struct NCache {
     std::vector<std::unique_ptr<NHier>> h;  // most recent last
@@ -519,6 +670,7 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
     H->bq.alloc(B.alloc);
     H->fn.alloc(3);
     H->iters.alloc(1);
+    plan_coarse(*H);
     if (C.h.size() >= 4) C.h.erase(C.h.begin());
     C.h.push_back(std::move(H));
     return C.h.back().get();
@@ -526,6 +678,18 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
 
 static void vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double brtol) {
     const NLev& L = H.L[l];
+    if ((int)l == H.coarse) {
+        static const hipError_t once = hipFuncSetAttribute(
+            (const void*)k_nd_coarse, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit_bytes() - 1024);
+        HIPCHK(once);
+        NCoarse C = H.cc;
+        C.nu1 = nu1;
+        C.nu2 = nu2;
+        C.rtol = brtol;
+        hipLaunchKernelGGL(k_nd_coarse, dim3(1), dim3(kNBot), H.coarse_lds, s, C, H.f[l].p, H.u[l].p, H.iters.p);
+        HIPCHK(hipGetLastError());
+        return;
+    }
     if (l + 1 == H.L.size()) {
         hipLaunchKernelGGL(k_nd_bottom, dim3(1), dim3(kNBot), 0, s, L, H.u[l].p, H.f[l].p, H.r[l].p, H.bp.p, H.bq.p,
                            brtol, H.iters.p);
@@ -544,7 +708,7 @@ static void vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double b
     hipLaunchKernelGGL(k_nd_restrict, plane_grid(C, false, kc), dim3(kNB), 0, s, L, H.r[l].p, C, H.f[l + 1].p,
                        H.u[l + 1].p, kc);
     vcycle(H, l + 1, s, nu1, nu2, brtol);
-    hipLaunchKernelGGL(k_nd_prolong, dim3(nblocks(L.size)), dim3(kNB), 0, s, C, H.u[l + 1].p, L, H.u[l].p);
+    hipLaunchKernelGGL(k_nd_prolong, gb, dim3(kNB), 0, s, C, H.u[l + 1].p, L, H.u[l].p, nu2 > 0 ? 1 : 0, kg);
     for (int q = 0; q < nu2; ++q)
         for (int c = 0; c < 2; ++c)
             hipLaunchKernelGGL(k_nd_gs, gb, dim3(kNB), 0, s, L, H.u[l].p, H.f[l].p, c, kg);
