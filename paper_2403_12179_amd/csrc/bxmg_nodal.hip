@@ -185,6 +185,269 @@ __global__ void __launch_bounds__(kNB) k_nd_resid(NLev L, const double* __restri
     }
 }
 
+// Streaming smoother: two red-black sweeps of a level and the residual after
+// them in one pass (the cell-centred one, bxmg_sweep.hip, describes the
+// scheme: a block walks a column of the level in z, the four half-sweeps and
+// the residual one plane behind each other, values in registers and the last
+// planes' in LDS).  A thread holds the pair of nodes (2m, 2m + 1) of a row; a
+// boundary node keeps its value through all stages, so no neighbour needs a
+// special case, and node n_d is written by the block that owns node n_d - 1.
+// ZERO: the sweeps start from u = 0, which is not read; otherwise colour 0 is
+// read at boundary nodes only.  KIND: 0 no residual, 1 the residual of the
+// unknowns into r, 2 its norms (3 partials per block).  uin and uout differ.
+// 256^3, FP64: sweeps and residual 171 us, sweeps and norms 175, against 4 x 56
+// and 122 in launches of their own; 128^3 28 and 23 us, against 4 x 9.0 and 17.
+// The arrays alone (u, f in, u, r out) take about 100 us at the copy rate.
+struct NSweep {
+    int nt = 0, threads = 0, blocks = 0;
+    int RM, RY;          // columns of a block with its halo: pairs, rows
+    int hm, hy;          // the halo below: pairs, rows (0: the block spans the level there)
+    int XM, TY, ZC;      // what a block owns
+    int nbx, nby, nbz;
+};
+template <int NT, bool ZERO, int KIND>
+__global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double* __restrict__ uin,
+                                                double* __restrict__ uout, const double* __restrict__ f,
+                                                double* __restrict__ r, double* __restrict__ partials) {
+    using std::integral_constant;
+    constexpr bool RES = KIND != 0;
+    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10;
+    __shared__ double lds[(RES ? 12 : 10) * NT];
+    const int tid = threadIdx.x;
+    int blk = blockIdx.x;
+    {
+        const int nb = gridDim.x;
+        if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
+    }
+    const int bx = blk % A.nbx, byz = blk / A.nbx;
+    const int by = byz % A.nby, bz = byz / A.nby;
+    const int nm = L.n[0] >> 1, n1 = L.n[1], n2 = L.n[2];
+    const bool perx = L.per[0] != 0, pery = L.per[1] != 0, perz = L.per[2] != 0;
+    const int ty = tid / A.RM, tm = tid - ty * A.RM;
+    const int mr = bx * A.XM - A.hm + tm, yr = by * A.TY - A.hy + ty;
+    int m = mr, y = yr;
+    bool in = ty < A.RY;
+    if (perx) { m %= nm; m += m < 0 ? nm : 0; } else in = in && m >= 0 && m <= nm;
+    if (pery) { y %= n1; y += y < 0 ? n1 : 0; } else in = in && y >= 0 && y <= n1;
+    const int x1 = min((bx + 1) * A.XM, nm), y1 = min((by + 1) * A.TY, n1);
+    const bool own = in && mr >= bx * A.XM && (mr < x1 || (!perx && mr == nm && x1 == nm)) && yr >= by * A.TY &&
+                     (yr < y1 || (!pery && yr == n1 && y1 == n1));
+    const int z0 = bz * A.ZC, zlim = min(z0 + A.ZC, n2);
+    constexpr int kHalo = (RES ? 5 : 4) - (ZERO ? 1 : 0), kFirst = (kHalo + 1) & ~1;
+    const int zs = perz ? z0 - kFirst : max(0, z0 - kFirst);
+    const int zend = zlim + 5;
+    const int zmax = perz ? zlim + 4 : min(zlim + 4, n2);
+    const bool top = !perz && zlim == n2;  // also writes plane n2
+    // in a plane of parity p the colour-c node of the pair is 2m + o, o = (c + y
+    // + p) & 1; "A" is the node with o = yo
+    const int yo = y & 1;
+    const bool wx = perx && A.hm == 0, wy = pery && A.hy == 0;
+    const int sl = tm > 0 ? tid - 1 : wx ? tid + A.RM - 1 : tid;
+    const int sr = tm < A.RM - 1 ? tid + 1 : wx ? tid - (A.RM - 1) : tid;
+    const int sdn = !in ? tid : ty > 0 ? tid - A.RM : wy ? tid + (A.RY - 1) * A.RM : tid;
+    const int sup = !in ? tid : ty < A.RY - 1 ? tid + A.RM : wy ? tid - (A.RY - 1) * A.RM : tid;
+    const int sxA = !in ? tid : yo ? sr : sl;
+    const int sxB = !in ? tid : yo ? sl : sr;
+    // boundary nodes (the slot beyond node n_0 counts as one)
+    const bool fy = in && !pery && (y == 0 || y == n1);
+    const bool fl = in && !perx && m == 0, fr_ = in && !perx && m == nm;
+    const bool fixA = fy || fr_ || (fl && yo == 0), fixB = fy || fr_ || (fl && yo == 1);
+    const bool edge_xy = __ballot(fixA || fixB) != 0;
+    const int v = in ? (y * L.H + m) * 8 : kOffPastBox;
+    const int co = (int)L.cs * 8, pl = L.H * (n1 + 1) * 8;
+    const int w = own ? v : kOffPastBox;
+    const double h2 = L.h * L.h, ih2 = 1.0 / (L.h * L.h);
+    const Recip<double> r6(6.0);
+    const int bytes = 2 * co;
+    const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
+    const auto Rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, bytes, kBufferDword3);
+    const auto Ro = __builtin_amdgcn_make_buffer_rsrc((void*)uout, (short)0, bytes, kBufferDword3);
+    const auto Rr = __builtin_amdgcn_make_buffer_rsrc((void*)(KIND == 1 ? r : uout), (short)0, bytes, kBufferDword3);
+
+    double r0[8], b0[8], r1[8], b2[8], r3[8], b4[8], f0[8], f1[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        r0[k] = 0.0; b0[k] = 0.0; r1[k] = 0.0; b2[k] = 0.0;
+        r3[k] = 0.0; b4[k] = 0.0; f0[k] = 0.0; f1[k] = 0.0;
+    }
+    double mx = 0.0, s2 = 0.0;
+    int nbad = 0;
+
+    auto load = [&](auto ph, int q) {
+        constexpr int PH = decltype(ph)::value;
+        int z = min(q, zmax);
+        if (perz) {
+            z += z < 0 ? n2 : 0;
+            z += z < 0 ? n2 : 0;
+            z -= z >= n2 ? n2 : 0;
+            z -= z >= n2 ? n2 : 0;
+        }
+        const int zo = z * pl;
+        f0[PH] = Raw<double>::ld(Rf, v, zo);
+        f1[PH] = Raw<double>::ld(Rf, v, zo + co);
+        if constexpr (!ZERO) {
+            b0[PH] = Raw<double>::ld(Ru, v, zo + co);
+            const bool fz = !perz && (z == 0 || z == n2);
+            if (edge_xy || fz) {
+                const bool fix = fz || ((PH & 1) ? fixB : fixA);
+                r0[PH] = Raw<double>::ld(Ru, fix ? v : kOffPastBox, zo);
+            }
+        }
+    };
+
+    auto step = [&](auto ph, auto edge, int q) {
+        constexpr int PH = decltype(ph)::value;
+        constexpr bool EDGE = decltype(edge)::value != 0;
+#define RS(d) ((PH - (d) + 16) & 7)              /* ring slot of plane q - d */
+#define ISA(d, c) ((((c) + PH - (d)) & 1) == 0)  /* its colour-c node is at o = yo */
+        struct Three { double x, d, u; };
+        auto near = [&](int buf, bool isA) {
+            const double* hp = lds + buf * NT;
+            return Three{hp[isA ? sxA : sxB], hp[sdn], hp[sup]};
+        };
+        auto fixed = [&](int d, bool isA) {  // in plane q - d
+            return (isA ? fixA : fixB) || (!perz && (q == d || q == d + n2));
+        };
+        auto relax = [&](int d, bool isA, double own_o, Three n, double zm, double zp, double fv, double old) {
+            const double x = r6.div(((own_o + n.x) + (n.d + n.u)) + (zm + zp) - h2 * fv);
+            if constexpr (EDGE) return fixed(d, isA) ? old : x;
+            else return x;
+        };
+        Three t1{}, t2, t3, t4, t5r{}, t5b{};
+        if constexpr (!ZERO) t1 = near(bB0 + ((PH - 1) & 1), ISA(1, 0));
+        t2 = near(bR1 + ((PH - 1) & 1), ISA(2, 1));
+        t3 = near(bB2 + ((PH - 1) & 1), ISA(3, 0));
+        t4 = near(bR3 + ((PH - 1) & 3), ISA(4, 1));
+        if constexpr (RES) {
+            t5r = near(bB4 + ((PH - 1) & 1), ISA(5, 0));
+            t5b = near(bR3 + ((PH - 2) & 3), ISA(5, 1));
+        }
+        if constexpr (!ZERO) lds[(bB0 + (PH & 1)) * NT + tid] = b0[RS(0)];
+        // the four half-sweeps
+        if constexpr (ZERO) r1[RS(1)] = relax(1, ISA(1, 0), 0.0, Three{0.0, 0.0, 0.0}, 0.0, 0.0, f0[RS(1)], 0.0);
+        else r1[RS(1)] = relax(1, ISA(1, 0), b0[RS(1)], t1, b0[RS(2)], b0[RS(0)], f0[RS(1)], r0[RS(1)]);
+        lds[(bR1 + (PH & 1)) * NT + tid] = r1[RS(1)];
+        b2[RS(2)] = relax(2, ISA(2, 1), r1[RS(2)], t2, r1[RS(3)], r1[RS(1)], f1[RS(2)], ZERO ? 0.0 : b0[RS(2)]);
+        lds[(bB2 + (PH & 1)) * NT + tid] = b2[RS(2)];
+        r3[RS(3)] = relax(3, ISA(3, 0), b2[RS(3)], t3, b2[RS(4)], b2[RS(2)], f0[RS(3)], r1[RS(3)]);
+        lds[(bR3 + (PH & 3)) * NT + tid] = r3[RS(3)];
+        b4[RS(4)] = relax(4, ISA(4, 1), r3[RS(4)], t4, r3[RS(5)], r3[RS(3)], f1[RS(4)], b2[RS(4)]);
+        if constexpr (RES) lds[(bB4 + (PH & 1)) * NT + tid] = b4[RS(4)];
+        {  // plane q-4 is final
+            const int pz = q - 4;
+            const bool mine = pz >= z0 && (pz < zlim || (top && pz == n2));
+            Raw<double>::st(Ro, mine ? w : kOffPastBox, pz * pl, r3[RS(4)]);
+            Raw<double>::st(Ro, mine ? w : kOffPastBox, pz * pl + co, b4[RS(4)]);
+        }
+        if constexpr (RES) {  // the residual of plane q-5
+            const int pz = q - 5;
+            const bool mine = own && pz >= z0 && pz < zlim && (perz || pz > 0);
+            const bool m0 = mine && !(ISA(5, 0) ? fixA : fixB), m1 = mine && !(ISA(5, 1) ? fixA : fixB);
+            const double s0 = ((b4[RS(5)] + t5r.x) + (t5r.d + t5r.u)) + (b4[RS(6)] + b4[RS(4)]);
+            const double s1 = ((r3[RS(5)] + t5b.x) + (t5b.d + t5b.u)) + (r3[RS(6)] + r3[RS(4)]);
+            const double v0 = f0[RS(5)] - (s0 - 6.0 * r3[RS(5)]) * ih2;
+            const double v1 = f1[RS(5)] - (s1 - 6.0 * b4[RS(5)]) * ih2;
+            if constexpr (KIND == 1) {
+                Raw<double>::st(Rr, m0 ? v : kOffPastBox, pz * pl, v0);
+                Raw<double>::st(Rr, m1 ? v : kOffPastBox, pz * pl + co, v1);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {  // (without branches: 0 adds nothing)
+                    const double x = (c ? m1 : m0) ? (c ? v1 : v0) : 0.0, a = fabs(x);
+                    const bool fine = a <= 1.7976931348623157e308;
+                    mx = fmax(mx, fine ? a : 0.0);
+                    nbad += fine ? 0 : 1;
+                    s2 = s2 + x * x;
+                }
+            }
+        }
+#undef RS
+#undef ISA
+    };
+
+    load(integral_constant<int, 0>(), zs);
+    load(integral_constant<int, 1>(), zs + 1);
+    for (int qb = zs;; qb += 8) {
+#define BXMG_STEP(PH)                                                           \
+    {                                                                           \
+        const int q = qb + PH;                                                  \
+        if (q >= zend) break;                                                   \
+        load(integral_constant<int, (PH + 2) & 7>(), q + 2);                    \
+        if (edge_xy || (!perz && (q <= 4 || q > n2)))                           \
+            step(integral_constant<int, PH>(), integral_constant<int, 1>(), q); \
+        else step(integral_constant<int, PH>(), integral_constant<int, 0>(), q); \
+        lds_barrier();                                                          \
+    }
+        BXMG_STEP(0) BXMG_STEP(1) BXMG_STEP(2) BXMG_STEP(3)
+        BXMG_STEP(4) BXMG_STEP(5) BXMG_STEP(6) BXMG_STEP(7)
+#undef BXMG_STEP
+    }
+    if constexpr (KIND == 2) {
+        double bad = (double)nbad;
+        block_reduce3(mx, s2, bad, lds);  // (every read of lds ended with the last barrier)
+        if (tid == 0) {
+            partials[3 * (size_t)blk] = mx;
+            partials[3 * (size_t)blk + 1] = s2;
+            partials[3 * (size_t)blk + 2] = bad;
+        }
+    }
+}
+
+// The blocks of a level (as plan_sweep); nt = 0: beyond 32-bit offsets.
+static NSweep plan_nd_sweep(const NLev& L, bool zero, int kind) {
+    NSweep best;
+    if (L.alloc * 8 > 0x7fffffffLL) return best;
+    const int halo = (kind ? 5 : 4) - (zero ? 1 : 0), lead = ((halo + 1) & ~1) + 5, nm = L.n[0] / 2;
+    double cost = 1e30;
+    auto split = [](int cells, int pieces, int unit) { return (cells / unit + pieces - 1) / pieces * unit; };
+    for (int px = 1; px <= nm; ++px) {
+        const int XM = split(nm, px, 1);
+        if (XM < 8 && px > 1) break;
+        const int hm = XM == nm ? 0 : (halo + 1) / 2, RM = XM == nm ? nm + (L.per[0] ? 0 : 1) : XM + 2 * hm;
+        if (RM > 768) continue;
+        for (int py = 1; py <= L.n[1] / 2; ++py) {
+            const int TY = split(L.n[1], py, 2);
+            const bool span = TY == L.n[1];
+            const int hy = span ? 0 : halo, RY = span ? TY + (L.per[1] ? 0 : 1) : TY + 2 * hy, cols = RM * RY;
+            if (cols > 768) continue;
+            const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : 768;
+            const int nbx = (nm + XM - 1) / XM, nby = (L.n[1] + TY - 1) / TY;
+            const int fit = nt == 256 ? 3 : 1;
+            for (int pz = 1; pz <= L.n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
+                const int ZC = split(L.n[2], pz, 2), nbz = (L.n[2] + ZC - 1) / ZC;
+                const long long blocks = (long long)nbx * nby * nbz, per_cu = (blocks + 255) / 256;
+                const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
+                const double c = (double)((per_cu + fit - 1) / fit) * (ZC + lead) *
+                                     std::max(1000.0, 300.0 + 130.0 * waves) + 1e-3 * (double)blocks;
+                if (c < cost) {
+                    cost = c;
+                    best.nt = nt;
+                    best.threads = (cols + 63) / 64 * 64;
+                    best.blocks = (int)blocks;
+                    best.RM = RM; best.RY = RY; best.hm = hm; best.hy = hy;
+                    best.XM = XM; best.TY = TY; best.ZC = ZC;
+                    best.nbx = nbx; best.nby = nby; best.nbz = nbz;
+                }
+                if (ZC == 2) break;
+            }
+        }
+    }
+    return best;
+}
+
+template <bool ZERO, int KIND>
+static hipError_t launch_nd_sweep(hipStream_t s, const NLev& L, const NSweep& P, const double* uin, double* uout,
+                                  const double* f, double* r, double* partials) {
+#define BXMG_NSW(NT)                                                                                             \
+    hipLaunchKernelGGL((k_nd_sweep<NT, ZERO, KIND>), dim3(P.blocks), dim3(P.threads), 0, s, L, P, uin, uout, f, r, \
+                       partials)
+    if (P.nt == 256) BXMG_NSW(256);
+    else if (P.nt == 512) BXMG_NSW(512);
+    else BXMG_NSW(768);
+#undef BXMG_NSW
+    return hipGetLastError();
+}
+
 // norms of f over the unknowns (max, sum of squares, non-finite count)
 __global__ void __launch_bounds__(kNB) k_nd_fnorm(NLev L, const double* __restrict__ f,
                                                  double* __restrict__ partials) {
@@ -582,6 +845,10 @@ struct NHier {
     DevBuf<double> part, bp, bq, fn;
     DevBuf<int> iters;
     std::string key;
+    // streamed levels: their second iterate array, the sweeps before (level 0:
+    // from its iterate, below from zero) and after the coarse levels
+    std::vector<DevBuf<double>> a;
+    std::vector<NSweep> pre, post;
     int coarse = -1;      // first level of the one-workgroup cycle (-1: none)
     NCoarse cc{};         // its levels
     size_t coarse_lds = 0;
@@ -663,20 +930,32 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
         H->f[q].alloc(H->L[q].alloc);
         H->r[q].alloc(H->L[q].alloc);
     }
+    plan_coarse(*H);
+    const size_t end = H->coarse > 0 ? (size_t)H->coarse : nl - 1;
     int np = 8192;
+    H->a.resize(nl);
+    H->pre.resize(nl);
+    H->post.resize(nl);
+    for (size_t q = 0; q < end; ++q) {
+        H->pre[q] = plan_nd_sweep(H->L[q], q > 0, 1);
+        H->post[q] = plan_nd_sweep(H->L[q], false, q > 0 ? 0 : 2);
+        if (H->pre[q].nt) H->a[q].alloc(H->L[q].alloc);
+        np = std::max(np, H->post[q].blocks);
+    }
     for (const NLev& l : H->L) np = std::max(np, plane_blocks(l, true, plane_depth(l, true, kKZr)));
     H->part.alloc(3 * (size_t)np);
     H->bp.alloc(B.alloc);
     H->bq.alloc(B.alloc);
     H->fn.alloc(3);
     H->iters.alloc(1);
-    plan_coarse(*H);
     if (C.h.size() >= 4) C.h.erase(C.h.begin());
     C.h.push_back(std::move(H));
     return C.h.back().get();
 }
 
-static void vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double brtol) {
+// Returns the number of partial norms of its residual that the cycle left in
+// H.part (0: none).
+static int vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double brtol) {
     const NLev& L = H.L[l];
     if ((int)l == H.coarse) {
         static const hipError_t once = hipFuncSetAttribute(
@@ -688,31 +967,44 @@ static void vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double b
         C.rtol = brtol;
         hipLaunchKernelGGL(k_nd_coarse, dim3(1), dim3(kNBot), H.coarse_lds, s, C, H.f[l].p, H.u[l].p, H.iters.p);
         HIPCHK(hipGetLastError());
-        return;
+        return 0;
     }
     if (l + 1 == H.L.size()) {
         hipLaunchKernelGGL(k_nd_bottom, dim3(1), dim3(kNBot), 0, s, L, H.u[l].p, H.f[l].p, H.r[l].p, H.bp.p, H.bq.p,
                            brtol, H.iters.p);
         HIPCHK(hipGetLastError());
-        return;
+        return 0;
     }
     const int kg = plane_depth(L, true, kKZ), kr = plane_depth(L, true, kKZr);
     const dim3 gb = plane_grid(L, true, kg);
-    for (int q = 0; q < nu1; ++q)
-        for (int c = 0; c < 2; ++c)
-            hipLaunchKernelGGL(k_nd_gs, gb, dim3(kNB), 0, s, L, H.u[l].p, H.f[l].p, c, kg);
-    hipLaunchKernelGGL(k_nd_resid, plane_grid(L, true, kr), dim3(kNB), 0, s, L, H.u[l].p, H.f[l].p, H.r[l].p,
-                       H.part.p, kr);
+    const bool stream = nu1 == 2 && nu2 == 2 && H.pre[l].nt > 0;
+    double* const u = stream ? H.a[l].p : H.u[l].p;  // what the coarse levels correct
+    if (stream) {
+        if (l > 0) HIPCHK((launch_nd_sweep<true, 1>(s, L, H.pre[l], nullptr, u, H.f[l].p, H.r[l].p, nullptr)));
+        else HIPCHK((launch_nd_sweep<false, 1>(s, L, H.pre[l], H.u[l].p, u, H.f[l].p, H.r[l].p, nullptr)));
+    } else {
+        for (int q = 0; q < nu1; ++q)
+            for (int c = 0; c < 2; ++c)
+                hipLaunchKernelGGL(k_nd_gs, gb, dim3(kNB), 0, s, L, u, H.f[l].p, c, kg);
+        hipLaunchKernelGGL(k_nd_resid, plane_grid(L, true, kr), dim3(kNB), 0, s, L, u, H.f[l].p, H.r[l].p, H.part.p,
+                           kr);
+    }
     const NLev& C = H.L[l + 1];
     const int kc = plane_depth(C, false, kKZt);
     hipLaunchKernelGGL(k_nd_restrict, plane_grid(C, false, kc), dim3(kNB), 0, s, L, H.r[l].p, C, H.f[l + 1].p,
                        H.u[l + 1].p, kc);
     vcycle(H, l + 1, s, nu1, nu2, brtol);
-    hipLaunchKernelGGL(k_nd_prolong, gb, dim3(kNB), 0, s, C, H.u[l + 1].p, L, H.u[l].p, nu2 > 0 ? 1 : 0, kg);
+    hipLaunchKernelGGL(k_nd_prolong, gb, dim3(kNB), 0, s, C, H.u[l + 1].p, L, u, nu2 > 0 ? 1 : 0, kg);
+    if (stream) {
+        if (l > 0) HIPCHK((launch_nd_sweep<false, 0>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, nullptr)));
+        else HIPCHK((launch_nd_sweep<false, 2>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, H.part.p)));
+        return l > 0 ? 0 : H.post[l].blocks;
+    }
     for (int q = 0; q < nu2; ++q)
         for (int c = 0; c < 2; ++c)
             hipLaunchKernelGGL(k_nd_gs, gb, dim3(kNB), 0, s, L, H.u[l].p, H.f[l].p, c, kg);
     HIPCHK(hipGetLastError());
+    return 0;
 }
 
 }  // namespace nodal
@@ -750,15 +1042,17 @@ extern "C" bxmg_status bxmg_nodal_solve(bxmg_ctx ctx, const bxmg_solve_params* p
         HIPCHK(hipGetLastError());
         const int kr0 = nodal::plane_depth(L0, true, nodal::kKZr);
         // norms reduced on the device and read back: of f (fonly) or of the
-        // residual of the current iterate
-        auto norms = [&](bool fonly, double out[3]) {
-            if (fonly)
+        // residual of the current iterate, unless taken partials hold it
+        auto norms = [&](bool fonly, int taken, double out[3]) {
+            if (taken) {
+            } else if (fonly)
                 hipLaunchKernelGGL(nodal::k_nd_fnorm, dim3(nb), dim3(nodal::kNB), 0, s, L0, H->f[0].p, H->part.p);
             else
                 hipLaunchKernelGGL(nodal::k_nd_resid, nodal::plane_grid(L0, true, kr0), dim3(nodal::kNB), 0, s, L0,
                                    H->u[0].p, H->f[0].p, H->r[0].p, H->part.p, kr0);
             HIPCHK(hipGetLastError());
-            HIPCHK(launch_norm_final(s, H->part.p, fonly ? (int)nb : nodal::plane_blocks(L0, true, kr0), H->fn.p));
+            HIPCHK(launch_norm_final(s, H->part.p, taken ? taken : fonly ? (int)nb : nodal::plane_blocks(L0, true, kr0),
+                                     H->fn.p));
             HIPCHK(hipMemcpyAsync(ctx->h_norm, H->fn.p, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             out[0] = ctx->h_norm[2] > 0.0 ? (double)NAN : ctx->h_norm[0];
@@ -766,16 +1060,16 @@ extern "C" bxmg_status bxmg_nodal_solve(bxmg_ctx ctx, const bxmg_solve_params* p
             out[2] = ctx->h_norm[2];
         };
         double fz[3];
-        norms(true, fz);
+        norms(true, 0, fz);
         const double fnorm = fz[0];
         info->f_inf = fnorm;
         int status = 0, cyc = 0;
         if (!(fnorm == fnorm)) {
             status = BXMG_ENONFINITE;
         } else if (fnorm > 0.0) {
-            for (;; ++cyc) {
+            for (int taken = 0;; ++cyc) {
                 double rn[3];
-                norms(false, rn);
+                norms(false, taken, rn);
                 if (cyc < kHist) {
                     info->hist[cyc] = rn[0] / fnorm;
                     info->hist_l2[cyc] = std::sqrt(rn[1]);
@@ -790,7 +1084,7 @@ extern "C" bxmg_status bxmg_nodal_solve(bxmg_ctx ctx, const bxmg_solve_params* p
                     if (rn[0] <= P.rel_tol * fnorm || rn[0] <= P.abs_tol) break;
                     if (cyc == P.max_cycles) { status = BXMG_ENOCONV; break; }
                 }
-                nodal::vcycle(*H, 0, s, P.nu1, P.nu2, P.bottom_rtol);
+                taken = nodal::vcycle(*H, 0, s, P.nu1, P.nu2, P.bottom_rtol);
             }
         } else {
             HIPCHK(hipMemsetAsync(H->u[0].p, 0, L0.alloc * sizeof(double), s));  // f == 0: u = 0

@@ -56,40 +56,6 @@
 
 namespace bxmg {
 
-namespace {
-
-// Barrier between LDS writers and readers of one step; global loads in
-// flight (the planes ahead) and stores are not waited for.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-template <class T>
-struct Raw;
-template <>
-struct Raw<double> {
-    static __device__ __forceinline__ double ld(__amdgpu_buffer_rsrc_t r, int v, int s) {
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
-    }
-    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, int v, int s, double x) {
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, v, s, 0);
-    }
-};
-template <>
-struct Raw<float> {
-    static __device__ __forceinline__ float ld(__amdgpu_buffer_rsrc_t r, int v, int s) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
-    }
-    static __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, int v, int s, float x) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, v, s, 0);
-    }
-};
-
-}  // namespace
-
 // KIND (SweepKind): what follows the sweeps.  ZERO: they start from u = 0,
 // which is not read.  POST: the sweeps after a prolongation, which leaves
 // colour 0 to them: colour 0's old values, read only beside Dirichlet faces,
