@@ -819,7 +819,10 @@ __global__ void __launch_bounds__(kBlock) k_admit_convert(Grid g, const ConvSrc*
                 acc_norm(v, mx, s2, bad);
             }
         }
-    if (__any(nz) && (threadIdx.x & 63) == 0) atomicOr(&nonzero[S.slot], 1);
+    // (looked at first: see k_fab_to_rb_nz)
+    if (__any(nz) && (threadIdx.x & 63) == 0 &&
+        !__hip_atomic_load(&nonzero[S.slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicOr(&nonzero[S.slot], 1);
     block_reduce3(mx, s2, bad, sh);
     if (threadIdx.x == 0) {
         partials[3 * tix] = mx;
@@ -1548,7 +1551,11 @@ __global__ void __launch_bounds__(kBlock) k_fab_to_rb_nz(Grid g, const double* _
                 nz = nz || __double_as_longlong(v) != 0;
             }
         }
-    if (__any(nz) && (threadIdx.x & 63) == 0) atomicOr(nonzero, 1);
+    // (looked at first: an atomic of every wave on one word takes longer than the
+    // pass, 168 us against 45 at 192^3)
+    if (__any(nz) && (threadIdx.x & 63) == 0 &&
+        !__hip_atomic_load(nonzero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicOr(nonzero, 1);
 }
 
 __global__ void __launch_bounds__(kBlock) k_rb_to_fab(Grid g, const double* __restrict__ rb, double* __restrict__ fab,
