@@ -81,6 +81,51 @@ __device__ __forceinline__ void block_reduce3(double& mx, double& s2, double& ba
     }
 }
 
+// Sums kept as s + c, c the rounding errors of s and of the products (Ogita,
+// Rump and Oishi 2005): as if summed in twice the precision, so that a sum
+// does not depend on how its terms are split over threads and blocks.  (An
+// infinite s makes c NaN: sum2 drops it.)
+struct Sum2 {
+    double s = 0.0, c = 0.0;
+    __device__ __forceinline__ void add(double x, double e) {
+        const double t = s + x, z = t - s;
+        c = c + (((s - (t - z)) + (x - z)) + e);
+        s = t;
+    }
+    __device__ __forceinline__ void dot(double a, double b) {
+        const double x = a * b;
+        add(x, __builtin_fma(a, b, -x));
+    }
+    __device__ __forceinline__ double value() const { return fabs(s) <= 1.7976931348623157e308 ? s + c : s; }
+};
+
+// Fixed-tree block sum of v; the result is valid in thread 0 (sh: 2 per wave).
+__device__ __forceinline__ void block_sum2(Sum2& v, double* sh) {
+    for (int o = 32; o > 0; o >>= 1) {
+        const double x = __shfl_xor(v.s, o), e = __shfl_xor(v.c, o);
+        v.add(x, e);
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane == 0) { sh[2 * wid] = v.s; sh[2 * wid + 1] = v.c; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int nw = (blockDim.x + 63) >> 6;
+        v.s = sh[0];
+        v.c = sh[1];
+        for (int w = 1; w < nw; ++w) v.add(sh[2 * w], sh[2 * w + 1]);
+    }
+}
+
+// A block's partial sums of two dots (launch_kr_sums).
+__device__ __forceinline__ void store_sums(double* __restrict__ partials, int blk, const Sum2& a, const Sum2& b) {
+    double* o = partials + 4 * (size_t)blk;
+    o[0] = a.s;
+    o[1] = a.c;
+    o[2] = b.s;
+    o[3] = b.c;
+}
+
 __device__ __forceinline__ void acc_norm(double rv, double& mx, double& s2, double& bad) {
     const double a = fabs(rv);
     if (!(a <= 1.7976931348623157e308)) bad += 1.0;  // NaN or Inf

@@ -152,6 +152,7 @@ struct Hier {
         DevBuf<double> r, q, x, f, part, sums;
         DevBuf<double> p[2];
         DevBuf<KrylovScalars> sc;
+        SweepPlan dir;  // of the direction pass (nt = 0: two launches)
     } kr;
     size_t bytes = 0;
     XGrid xgrid(size_t l) const {
@@ -1154,7 +1155,9 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
         K.q.alloc(n);
         K.p[0].alloc(n);
         K.p[1].alloc(n);
-        K.part.alloc(3 * (size_t)std::max(L0.ntcol, 1));
+        if (L0.boxes.size() == 1 && L0.boxes[0].cells() == L0.dom.cells() && L0.push && L0.res)
+            K.dir = plan_direction(L0.rb[0], H->per);
+        K.part.alloc(4 * (size_t)std::max(std::max(L0.ntcol, K.dir.blocks), 1));
         K.sums.alloc(3);
         K.sc.alloc(1);
         HIPCHK(hipMemsetAsync(K.sc.p, 0, sizeof(KrylovScalars), R.s));
@@ -1195,23 +1198,24 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
         HIPCHK(launch_batch_check(R.s, H->flags.p + 1, 1, H->fnorm.p, H->st.p, H->flags.p, H->hist.p,
                                   H->hist.p + kHist, H->flags.p + 2));
     };
+    const bool onepass = K.dir.nt > 0;  // the direction in one pass
     // z = M r, from the right-hand side already in place; zero: clear the
-    // correction first (the direction pass clears it on the way otherwise)
+    // correction first (the two-launch direction clears it on the way otherwise)
     auto precondition = [&](bool zero) {
         if (fp32) {
             if (zero && !R.streams(0)) HIPCHK(launch_zero<float>(R.s, H->u32[0]->p, n, R.active));
             vcycle<float>(R, 0);
-            fill_faces<float>(R, 0, H->u32[0]->p);
+            if (!onepass) fill_faces<float>(R, 0, H->u32[0]->p);
         } else {
             if (zero && !R.streams(0)) HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, n, R.active));
             vcycle<double>(R, 0);
-            fill_faces<double>(R, 0, H->u64[0]->p);
+            if (!onepass) fill_faces<double>(R, 0, H->u64[0]->p);
         }
     };
     auto dots = [&](int step) {
         if (fp32) HIPCHK(launch_kr_dots<float>(R.s, R.grid(L0.walk()), H->u32[0]->p, K.r.p, K.q.p, K.part.p));
         else HIPCHK(launch_kr_dots<double>(R.s, R.grid(L0.walk()), H->u64[0]->p, K.r.p, K.q.p, K.part.p));
-        HIPCHK(launch_norm_final(R.s, K.part.p, L0.ntcol, K.sums.p));
+        HIPCHK(launch_kr_sums(R.s, K.part.p, L0.ntcol, K.sums.p));
         HIPCHK(launch_kr_step(R.s, K.sums.p, K.sc.p, step, R.active));
     };
     // f - L u into r (and its norms into the partials); u's ghosts refreshed first
@@ -1226,11 +1230,21 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
         dots(2);
     };
     auto iterate = [&]() {
-        if (fp32) HIPCHK(launch_kr_axpy<float>(R.s, H->u32[0]->p, pc, pn, n, K.sc.p, R.active));
-        else HIPCHK(launch_kr_axpy<double>(R.s, H->u64[0]->p, pc, pn, n, K.sc.p, R.active));
-        std::swap(pc, pn);
-        HIPCHK(launch_kr_apply(R.s, R.grid(L0.walk()), pc, b64, K.q.p, K.part.p));
-        HIPCHK(launch_norm_final(R.s, K.part.p, L0.ntcol, K.sums.p));
+        if (onepass) {
+            if (fp32)
+                HIPCHK(launch_kr_direction<float>(R.s, K.dir, H->u32[0]->p, pc, pn, b64, K.q.p, K.sc.p, K.part.p,
+                                                  R.active));
+            else
+                HIPCHK(launch_kr_direction<double>(R.s, K.dir, H->u64[0]->p, pc, pn, b64, K.q.p, K.sc.p, K.part.p,
+                                                   R.active));
+            std::swap(pc, pn);
+        } else {
+            if (fp32) HIPCHK(launch_kr_axpy<float>(R.s, H->u32[0]->p, pc, pn, n, K.sc.p, R.active));
+            else HIPCHK(launch_kr_axpy<double>(R.s, H->u64[0]->p, pc, pn, n, K.sc.p, R.active));
+            std::swap(pc, pn);
+            HIPCHK(launch_kr_apply(R.s, R.grid(L0.walk()), pc, b64, K.q.p, K.part.p));
+        }
+        HIPCHK(launch_kr_sums(R.s, K.part.p, onepass ? K.dir.blocks : L0.ntcol, K.sums.p));
         HIPCHK(launch_kr_step(R.s, K.sums.p, K.sc.p, 0, R.active));
         if (fp32)
             HIPCHK(launch_kr_update<float>(R.s, R.grid(L0.walk()), x, pc, K.r.p, K.q.p, H->f32[0]->p, K.sc.p,
@@ -1239,7 +1253,7 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
             HIPCHK(launch_kr_update<double>(R.s, R.grid(L0.walk()), x, pc, K.r.p, K.q.p, H->f64[0]->p, K.sc.p,
                                             H->partials.p));
         stop_test();
-        precondition(false);
+        precondition(onepass);
         dots(1);
     };
     residual(R, R.grid(L0.walk()));

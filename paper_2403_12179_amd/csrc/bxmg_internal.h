@@ -469,19 +469,30 @@ struct KrylovScalars {
 template <class E>
 hipError_t launch_kr_axpy(hipStream_t s, E* e, const double* p, double* pn, long long n, const KrylovScalars* sc,
                           const int* active);
-// q = L p at every valid cell; partials[3 tile + 1] = the tile's sum of p.q.
+// q = L p at every valid cell; the tiles' partial sums of p.q (4 values each,
+// launch_kr_sums).
 hipError_t launch_kr_apply(hipStream_t s, const Grid& g, const double* p, const double* beta, double* q,
                            double* partials);
+// Both in one pass over a one-box level (plan_direction: nt = 0 if it cannot
+// be), p != pn: pn at the valid cells only, no ghost read; e is left as it is.
+// The blocks' partial sums of pn.q.
+SweepPlan plan_direction(const RBox& B, const int per[3]);
+template <class E>
+hipError_t launch_kr_direction(hipStream_t s, const SweepPlan& P, const E* e, const double* p, double* pn,
+                               const double* beta, double* q, const KrylovScalars* sc, double* partials,
+                               const int* active);
 // x += alpha p, r -= alpha q, rhs = (E) r at every valid cell; partials of
 // the new residual's norms as launch_resid writes them.
 template <class E>
 hipError_t launch_kr_update(hipStream_t s, const Grid& g, double* x, const double* p, double* r, const double* q,
                             E* rhs, const KrylovScalars* sc, double* partials);
-// partials[3 tile + 1] = sum of z.q, partials[3 tile + 2] = sum of z.r with
-// z = (double) e, over every valid cell.
+// The tiles' partial sums of z.q and z.r with z = (double) e.
 template <class E>
 hipError_t launch_kr_dots(hipStream_t s, const Grid& g, const E* e, const double* r, const double* q,
                           double* partials);
+// The dots of n tiles' or blocks' partial sums, summed as in twice the
+// precision: they do not depend on the tiles.
+hipError_t launch_kr_sums(hipStream_t s, const double* partials, int n, double* sums3);
 // From reduced sums (sums3[1], sums3[2]): step 0: alpha = rz / (p.q);
 // step 1: beta = -alpha (z.q) / rz, then rz = z.r; step 2 (a restart):
 // beta = 0, rz = z.r.  Nothing while active[0] == 0.

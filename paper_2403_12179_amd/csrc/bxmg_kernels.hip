@@ -2998,8 +2998,8 @@ template <int MODE, bool RES>
 __global__ void __launch_bounds__(kBlock) k_kr_apply(Grid g, const double* __restrict__ p,
                                                     const double* __restrict__ beta, double* __restrict__ q,
                                                     double* __restrict__ partials) {
-    __shared__ double sh[3 * (kBlock / 64)];
-    double z0 = 0.0, pq = 0.0, z1 = 0.0;
+    __shared__ double sh[2 * (kBlock / 64)];
+    Sum2 pq;
     const int tix = tile_index(g.rev);
     const Tile tl = g.tiles[tix];
     const RBox B = g.boxes[tl.box];
@@ -3034,15 +3034,11 @@ __global__ void __launch_bounds__(kBlock) k_kr_apply(Grid g, const double* __res
                 const double qv = (su - sb * nb[c].c) * ih2;
                 if constexpr (RES) Q.st((int)idx[c], qv);
                 else q[idx[c]] = qv;
-                pq = pq + nb[c].c * qv;
+                pq.dot(nb[c].c, qv);
             }
         }
-    block_reduce3(z0, pq, z1, sh);
-    if (threadIdx.x == 0) {
-        partials[3 * tix] = 0.0;
-        partials[3 * tix + 1] = pq;
-        partials[3 * tix + 2] = 0.0;
-    }
+    block_sum2(pq, sh);
+    if (threadIdx.x == 0) store_sums(partials, tix, pq, Sum2{});
 }
 
 // x += alpha p, r -= alpha q, rhs = (E) r; norms of the new r
@@ -3089,8 +3085,8 @@ __global__ void __launch_bounds__(kBlock) k_kr_update(Grid g, double* __restrict
 template <class E>
 __global__ void __launch_bounds__(kBlock) k_kr_dots(Grid g, const E* __restrict__ e, const double* __restrict__ r,
                                                    const double* __restrict__ q, double* __restrict__ partials) {
-    __shared__ double sh[3 * (kBlock / 64)];
-    double z0 = 0.0, zq = 0.0, zr = 0.0;
+    __shared__ double sh[2 * (kBlock / 64)];
+    Sum2 zq, zr;
     const int tix = tile_index(g.rev);
     const Tile tl = g.tiles[tix];
     const RBox B = g.boxes[tl.box];
@@ -3107,15 +3103,40 @@ __global__ void __launch_bounds__(kBlock) k_kr_dots(Grid g, const E* __restrict_
                 if (i > B.hi[0]) continue;
                 const long long idx = rb_idx(B, i, j, k);
                 const double zv = (double)e[idx];
-                zq = zq + zv * q[idx];
-                zr = zr + zv * r[idx];
+                zq.dot(zv, q[idx]);
+                zr.dot(zv, r[idx]);
             }
         }
-    block_reduce3(z0, zq, zr, sh);
+    block_sum2(zq, sh);
+    block_sum2(zr, sh);
+    if (threadIdx.x == 0) store_sums(partials, tix, zq, zr);
+}
+
+// The two dots from every block's partial sums, into sums3[1] and sums3[2].
+__global__ void __launch_bounds__(kNormThreads) k_kr_sums(const double* __restrict__ partials, int n,
+                                                         double* __restrict__ sums3) {
+    __shared__ double sh[2 * (kNormThreads / 64)];
+    Sum2 a, b;
+    for (int k0 = threadIdx.x; k0 < n; k0 += kNormUnroll * kNormThreads) {
+        double o[kNormUnroll][4];  // every load of a round in flight
+#pragma unroll
+        for (int v = 0; v < kNormUnroll; ++v)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int k = k0 + v * kNormThreads;
+                o[v][c] = k < n ? partials[4 * (size_t)k + c] : 0.0;
+            }
+#pragma unroll
+        for (int v = 0; v < kNormUnroll; ++v) {
+            a.add(o[v][0], o[v][1]);
+            b.add(o[v][2], o[v][3]);
+        }
+    }
+    block_sum2(a, sh);
+    block_sum2(b, sh);
     if (threadIdx.x == 0) {
-        partials[3 * tix] = 0.0;
-        partials[3 * tix + 1] = zq;
-        partials[3 * tix + 2] = zr;
+        sums3[1] = a.value();
+        sums3[2] = b.value();
     }
 }
 
@@ -3169,6 +3190,10 @@ hipError_t launch_kr_dots(hipStream_t s, const Grid& g, const E* e, const double
                           double* partials) {
     if (g.ntiles <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_kr_dots<E>, dim3(g.ntiles), dim3(kBlock), 0, s, g, e, r, q, partials);
+    return hipGetLastError();
+}
+hipError_t launch_kr_sums(hipStream_t s, const double* partials, int n, double* sums3) {
+    hipLaunchKernelGGL(k_kr_sums, dim3(1), dim3(kNormThreads), 0, s, partials, n, sums3);
     return hipGetLastError();
 }
 hipError_t launch_kr_step(hipStream_t s, const double* sums3, KrylovScalars* sc, int step, const int* active) {

@@ -483,6 +483,232 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
     }
 }
 
+// One conjugate-gradient direction on a one-box level in one pass:
+//   p' = (double) e + beta p,  q = L p',  partial sums of p'.q.
+// A block walks a column in z as k_sweep does, p' of a plane formed as it
+// enters and q one plane behind it; each face coefficient of a pair is formed
+// once (MODE 1: the cell beta; 0: constant).  p and pn differ; ghosts are not
+// read (minus the own cell beyond a Dirichlet face, own beta there) nor
+// written.  Same operations per cell as k_kr_axpy and k_kr_apply.
+// Bound by its bytes (36 a cell with e in FP32) and, with MODE 1, by 9 FP64
+// divisions a pair: 512^3, FP32 e, MODE 1 1180 us, 950 of them its bytes at the
+// copy rate; the two launches took 715 + 1415, the second with 12 divisions a
+// pair and 6 more FP64 loads a cell.
+constexpr int kDirThreads = 512;
+template <class E, int MODE>
+__global__ void __launch_bounds__(kDirThreads, 4)
+    k_kr_direction(SweepArgs A, const E* __restrict__ e, const double* __restrict__ p, double* __restrict__ pn,
+                   const double* __restrict__ beta, double* __restrict__ q_, const KrylovScalars* __restrict__ sc,
+                   double* __restrict__ partials, const int* __restrict__ active) {
+    using std::integral_constant;
+    constexpr int NT = kDirThreads, bP = 0, bK = 4;  // + 2 colour + plane parity
+    __shared__ double lds[(MODE ? 8 : 4) * NT];
+    if (active && !active[A.pid]) return;
+    const double bs = sc->beta;
+    const int tid = threadIdx.x;
+    int blk = blockIdx.x;
+    {
+        const int nb = gridDim.x;
+        if ((nb & 7) == 0) blk = (blk & 7) * (nb >> 3) + (blk >> 3);
+    }
+    const int bx = blk % A.nbx, byz = blk / A.nbx;
+    const int by = byz % A.nby, bz = byz / A.nby;
+    const int nm = A.n[0] >> 1, n1 = A.n[1], n2 = A.n[2];
+    const int ty = tid / A.RM, tm = tid - ty * A.RM;
+    const int mr = bx * A.XM - A.hm + tm, yr = by * A.TY - A.hy + ty;
+    int m = mr, y = yr;
+    bool in = ty < A.RY;
+    if (A.per[0]) { m %= nm; m += m < 0 ? nm : 0; } else in = in && m >= 0 && m < nm;
+    if (A.per[1]) { y %= n1; y += y < 0 ? n1 : 0; } else in = in && y >= 0 && y < n1;
+    const bool own = in && tm >= A.hm && tm < A.hm + A.XM && mr < nm && ty >= A.hy && ty < A.hy + A.TY && yr < n1;
+    const bool perz = A.per[2] != 0;
+    const bool fxl = in && !A.per[0] && m == 0, fxr = in && !A.per[0] && m == nm - 1;
+    const bool fyl = in && !A.per[1] && y == 0, fyr = in && !A.per[1] && y == n1 - 1;
+    const int z0 = bz * A.ZC, zlim = min(z0 + A.ZC, n2);
+    const int zs = perz ? z0 - 2 : max(0, z0 - 2), zend = zlim + 1;
+    const int zmax = perz ? zlim : min(zlim, n2 - 1);
+    const int yo = y & 1;
+    const bool wx = A.per[0] && A.hm == 0, wy = A.per[1] && A.hy == 0;
+    const int sl = tm > 0 ? tid - 1 : wx ? tid + A.RM - 1 : tid;
+    const int sr = tm < A.RM - 1 ? tid + 1 : wx ? tid - (A.RM - 1) : tid;
+    const int sdn = !in ? tid : ty > 0 ? tid - A.RM : wy ? tid + (A.RY - 1) * A.RM : tid;
+    const int sup = !in ? tid : ty < A.RY - 1 ? tid + A.RM : wy ? tid - (A.RY - 1) * A.RM : tid;
+    const int sxA = !in ? tid : yo ? sr : sl;
+    const int sxB = !in ? tid : yo ? sl : sr;
+    const bool fxA = yo ? fxr : fxl, fxB = yo ? fxl : fxr;
+    constexpr int es = (int)sizeof(E);
+    const int row = (y + 1) * A.H + m;
+    const int oA = in ? row + yo : -1, oB = in ? row + 1 - yo : -1;
+    const int vA = in ? oA * 8 : kOffPastBox, vB = in ? oB * 8 : kOffPastBox;
+    const int eA = in ? oA * es : kOffPastBox, eB = in ? oB * es : kOffPastBox;
+    const int wA = own ? vA : kOffPastBox, wB = own ? vB : kOffPastBox;
+    const int co = A.cs * 8, pl = A.GH * 8;
+    const double ih2 = 1.0 / (A.h * A.h), dg = A.a * (A.h * A.h);
+    const auto Re = __builtin_amdgcn_make_buffer_rsrc((void*)e, (short)0, 2 * A.cs * es, kBufferDword3);
+    const auto Rp = __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, 2 * co, kBufferDword3);
+    const auto Rn = __builtin_amdgcn_make_buffer_rsrc((void*)pn, (short)0, 2 * co, kBufferDword3);
+    const auto Rq = __builtin_amdgcn_make_buffer_rsrc((void*)q_, (short)0, 2 * co, kBufferDword3);
+    const auto Rk = __builtin_amdgcn_make_buffer_rsrc((void*)(MODE ? beta : p), (short)0, 2 * co, kBufferDword3);
+
+    // by colour and plane modulo 4
+    E ev[2][4] = {};
+    double po[2][4] = {}, be[2][4] = {}, pv[2][4] = {}, zl[2][4] = {};
+    Sum2 pq;
+
+    auto load = [&](auto ph, int q) {
+        constexpr int PH = decltype(ph)::value;
+        int z = min(q, zmax);
+        if (perz) {
+            z += z < 0 ? n2 : 0;
+            z -= z >= n2 ? n2 : 0;
+        }
+        const int zo = z * pl + pl, ze = z * A.GH * es + A.GH * es;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const bool isA = ((c + PH) & 1) == 0;
+            ev[c][PH] = Raw<E>::ld(Re, isA ? eA : eB, ze + c * A.cs * es);
+            po[c][PH] = Raw<double>::ld(Rp, isA ? vA : vB, zo + c * co);
+            if constexpr (MODE != 0) be[c][PH] = Raw<double>::ld(Rk, isA ? vA : vB, zo + c * co);
+        }
+    };
+    struct Three { double x, d, u; };
+    auto near = [&](int buf, bool isA) {
+        const double* hp = lds + buf * NT;
+        return Three{hp[isA ? sxA : sxB], hp[sdn], hp[sup]};
+    };
+    auto step = [&](auto ph, int q) {
+        constexpr int PH = decltype(ph)::value, P1 = (PH + 3) & 3, P2 = (PH + 2) & 3;  // planes q, q-1, q-2
+        constexpr int s0 = PH & 1, s1 = s0 ^ 1;
+        Three np[2], nk[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {  // neighbours of plane q-1's cells, of the other colour
+            const bool isA = ((c + P1) & 1) == 0;
+            np[c] = near(bP + 2 * (1 - c) + s1, isA);
+            if constexpr (MODE != 0) nk[c] = near(bK + 2 * (1 - c) + s1, isA);
+        }
+        const bool mine = q >= z0 && q < zlim;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const bool isA = ((c + PH) & 1) == 0;
+            pv[c][PH] = (double)ev[c][PH] + bs * po[c][PH];
+            lds[(bP + 2 * c + s0) * NT + tid] = pv[c][PH];
+            Raw<double>::st(Rn, mine ? (isA ? wA : wB) : kOffPastBox, q * pl + pl + c * co, pv[c][PH]);
+            if constexpr (MODE != 0) {
+                lds[(bK + 2 * c + s0) * NT + tid] = be[c][PH];
+                double lo = be[1 - c][P1], hi = be[c][PH];
+                lo = !perz && q == 0 ? hi : lo;
+                hi = !perz && q == n2 ? lo : hi;
+                zl[c][PH] = harm(lo, hi);
+            }
+        }
+        const bool mine1 = q - 1 >= z0 && q - 1 < zlim;
+        const double kin = MODE ? harm(be[0][P1], be[1][P1]) : 1.0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const bool isA = ((c + P1) & 1) == 0, fx = isA ? fxA : fxB;
+            const double v = pv[c][P1], g = -v;
+            const double x = fx ? g : np[c].x, d = fyl ? g : np[c].d, u = fyr ? g : np[c].u;
+            const double zm = !perz && q == 1 ? g : pv[1 - c][P2], zp = !perz && q == n2 ? g : pv[1 - c][PH];
+            double su, sb;
+            if constexpr (MODE == 0) {
+                su = ((pv[1 - c][P1] + x) + (d + u)) + (zm + zp);
+                sb = 6.0;
+            } else {
+                const double b = be[c][P1];
+                const double ko = harm(b, fx ? b : nk[c].x), kd = harm(fyl ? b : nk[c].d, b),
+                             ku = harm(b, fyr ? b : nk[c].u), kl = zl[c][P1], kh = zl[1 - c][PH];
+                su = ((kin * pv[1 - c][P1] + ko * x) + (kd * d + ku * u)) + (kl * zm + kh * zp);
+                sb = ((kin + ko) + (kd + ku)) + (kl + kh);
+            }
+            sb = sb + dg;
+            const double qv = (su - sb * v) * ih2;
+            Raw<double>::st(Rq, mine1 ? (isA ? wA : wB) : kOffPastBox, q * pl + c * co, qv);
+            pq.dot(own && mine1 ? v : 0.0, own && mine1 ? qv : 0.0);
+        }
+    };
+    load(integral_constant<int, 0>(), zs);
+    load(integral_constant<int, 1>(), zs + 1);
+    for (int qb = zs;; qb += 4) {
+#define BXMG_STEP(PH)                                            \
+    {                                                            \
+        const int q = qb + PH;                                   \
+        if (q >= zend) break;                                    \
+        load(integral_constant<int, (PH + 2) & 3>(), q + 2);     \
+        step(integral_constant<int, PH>(), q);                   \
+        lds_barrier();                                           \
+    }
+        BXMG_STEP(0) BXMG_STEP(1) BXMG_STEP(2) BXMG_STEP(3)
+#undef BXMG_STEP
+    }
+    block_sum2(pq, lds);
+    if (tid == 0) store_sums(partials, blk, pq, Sum2{});
+}
+
+// The blocks of k_kr_direction: the split with the fewest columns and planes
+// read per cell that still gives every CU two rounds of two blocks.
+SweepPlan plan_direction(const RBox& B, const int per[3]) {
+    SweepPlan best;
+    int n[3];
+    for (int d = 0; d < 3; ++d) {
+        n[d] = B.hi[d] - B.lo[d] + 1;
+        if (n[d] % 2 || n[d] < 4 || (B.lo[d] & 1)) return best;
+    }
+    const int nm = n[0] / 2;
+    double cost = 1e30;
+    auto split = [](int cells, int pieces, int unit) { return (cells / unit + pieces - 1) / pieces * unit; };
+    for (int px = 1; px <= nm; ++px) {
+        const int XM = split(nm, px, 1), hm = XM == nm ? 0 : 1, RM = XM + 2 * hm;
+        if (XM < 8 && px > 1) break;
+        if (RM > kDirThreads) continue;
+        for (int py = 1; py <= n[1]; ++py) {
+            const int TY = split(n[1], py, 1), hy = TY == n[1] ? 0 : 1, cols = RM * (TY + 2 * hy);
+            if (cols > kDirThreads) continue;
+            const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
+            for (int pz = 1; pz <= n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
+                const int ZC = split(n[2], pz, 2), nbz = (n[2] + ZC - 1) / ZC;
+                const long long blocks = (long long)nbx * nby * nbz, rounds = (blocks + 511) / 512;
+                const double c = (double)rounds * (ZC + 4) * (1.0 + (cols + 63) / 64) + 1e-3 * (double)blocks;
+                if (c < cost) {
+                    cost = c;
+                    best.nt = kDirThreads;
+                    best.threads = (cols + 63) / 64 * 64;
+                    best.blocks = (int)blocks;
+                    SweepArgs& A = best.args;
+                    A.RM = RM; A.RY = TY + 2 * hy; A.hm = hm; A.hy = hy;
+                    A.XM = XM; A.TY = TY; A.ZC = ZC;
+                    A.nbx = nbx; A.nby = nby; A.nbz = nbz;
+                }
+                if (ZC == 2) break;
+            }
+        }
+    }
+    SweepArgs& A = best.args;
+    for (int d = 0; d < 3; ++d) { A.n[d] = n[d]; A.per[d] = per[d]; }
+    A.H = B.H;
+    A.GH = B.H * B.G[1];
+    A.cs = (int)B.cstride;
+    A.pid = B.pid;
+    A.h = B.h;
+    A.a = B.a;
+    return best;
+}
+
+template <class E>
+hipError_t launch_kr_direction(hipStream_t s, const SweepPlan& P, const E* e, const double* p, double* pn,
+                               const double* beta, double* q, const KrylovScalars* sc, double* partials,
+                               const int* active) {
+    const dim3 G(P.blocks), B(P.threads);
+    if (beta)
+        hipLaunchKernelGGL((k_kr_direction<E, 1>), G, B, 0, s, P.args, e, p, pn, beta, q, sc, partials, active);
+    else
+        hipLaunchKernelGGL((k_kr_direction<E, 0>), G, B, 0, s, P.args, e, p, pn, beta, q, sc, partials, active);
+    return hipGetLastError();
+}
+template hipError_t launch_kr_direction<float>(hipStream_t, const SweepPlan&, const float*, const double*, double*,
+                                               const double*, double*, const KrylovScalars*, double*, const int*);
+template hipError_t launch_kr_direction<double>(hipStream_t, const SweepPlan&, const double*, const double*, double*,
+                                                const double*, double*, const KrylovScalars*, double*, const int*);
+
 // Blocks of a level: every split of its rows and planes into blocks of at
 // most 1024 columns is priced as (rounds of blocks over the 256 CUs) x (steps
 // of a block) x (time of a step), a step being latency-bound with few waves
