@@ -710,9 +710,10 @@ template hipError_t launch_kr_direction<double>(hipStream_t, const SweepPlan&, c
                                                 const double*, double*, const KrylovScalars*, double*, const int*);
 
 // Blocks of a level: every split of its rows and planes into blocks of at
-// most 1024 columns is priced as (rounds of blocks over the 256 CUs) x (steps
-// of a block) x (time of a step), a step being latency-bound with few waves
-// on a CU and issue-bound with many; the cheapest is taken.
+// most 1024 columns is priced as (rounds of blocks over the CUs) x (steps of a
+// block) x (time of a step) and the cheapest taken.  A step's time in clocks
+// is linear in the waves on a CU (fitted to timings of every split of levels
+// of 32^3 to 128^3: the plans are within 10 % of the best one there).
 SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode, int cus, int ntmax) {
     SweepPlan best;
     const bool res = kind == kSweepRestrict || kind == kSweepNorm;
@@ -729,7 +730,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
     };
     for (int px = 1; px <= nm; ++px) {
         const int XM = split(nm, px, 1);
-        if (XM < 8 && px > 1) break;
+        if (XM < 4 && px > 1) break;
         const bool wx = XM == nm;
         const int hm = wx ? 0 : (halo + 1) / 2, RM = XM + 2 * hm;
         if (RM > ntmax) continue;
@@ -749,7 +750,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
                 const long long per_cu = (blocks + cus - 1) / cus;
                 const long long rounds = (per_cu + fit - 1) / fit;
                 const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
-                const double step = std::max(mode ? 1500.0 : 1000.0, 300.0 + (mode ? 300.0 : f32 ? 110.0 : 130.0) * waves);
+                const double step = mode ? 700.0 + 280.0 * waves : f32 ? 600.0 + 80.0 * waves : 550.0 + 115.0 * waves;
                 const double c = rounds * (ZC + lead) * step + 1e-3 * blocks;
                 if (c < cost) {
                     cost = c;
