@@ -136,13 +136,8 @@ struct Hier {
     CoarseCycle<float> cc32_host{};
     DevBuf<double> partials;  // 3 per tile of the largest tiled launch, + 3
     DevBuf<double> fnorm;     // 3
-    // the solve's stop test on the device (the batch engine's, one slot):
-    // slot state, flags {active, slot index 0, active count, guess not +0}, the history
-    // (kHist of |r|/|f|, then kHist of |r|_2) and the norms of f
-    DevBuf<BatchSlot> st;
-    DevBuf<int> flags;
-    DevBuf<double> hist;
-    DevBuf<double> fn3;
+    DevBuf<SolveState> state;  // the solve's stop test on the device
+    DevBuf<int> guess_nz;      // whether its guess has a value other than +0.0
     DevBuf<int> iters;
     // multigrid-preconditioned CG on level 0 (allocated by its first solve):
     // residual, two directions (read one, write the other), q = L p, the
@@ -355,11 +350,9 @@ static std::unique_ptr<Hier> build_hier(const bxmg_ba_s* ba, int precision, bool
     plan_streams(H.get(), max_tiles);
     H->partials.alloc(6 * max_tiles + 8);  // two sets: the fused residual's colour-1 and colour-0 norms
     H->fnorm.alloc(4);
-    H->st.alloc(1);
-    H->flags.alloc(4);
-    HIPCHK(hipMemset(H->flags.p, 0, 4 * sizeof(int)));
-    H->hist.alloc(2 * kHist);
-    H->fn3.alloc(4);
+    H->state.alloc(1);
+    HIPCHK(hipMemset(H->state.p, 0, sizeof(SolveState)));
+    H->guess_nz.alloc(1);
     H->iters.alloc(1);
     return H;
 }
@@ -654,14 +647,6 @@ void setup_faces(Run& R, T* beta0) {
         }
     }
 }
-
-// Host copy of a solve's stop-test state: the two histories, the slot, the flag.
-struct SolveState {
-    double hist[kHist];
-    double hist_l2[kHist];
-    BatchSlot st;
-    int active;
-};
 
 double norm_readback(Run& R, double* h_norm, const double* dev) {
     HIPCHK(hipMemcpyAsync(h_norm, dev, 3 * sizeof(double), hipMemcpyDeviceToHost, R.s));
@@ -1194,9 +1179,7 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
     Run R0 = R;  // the same, with launches that run whatever the stop flag says
     R0.active = nullptr;
     auto stop_test = [&]() {
-        HIPCHK(launch_norm_final(R.s, H->partials.p, L0.ntcol, H->fnorm.p));
-        HIPCHK(launch_batch_check(R.s, H->flags.p + 1, 1, H->fnorm.p, H->st.p, H->flags.p, H->hist.p,
-                                  H->hist.p + kHist, H->flags.p + 2));
+        HIPCHK(launch_solve_check(R.s, H->partials.p, L0.ntcol, H->state.p));
     };
     const bool onepass = K.dir.nt > 0;  // the direction in one pass
     // z = M r, from the right-hand side already in place; zero: clear the
@@ -1292,8 +1275,8 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
         // restart from the fresh residual (already in r): the slot runs on
         hs->st.cycles += 1;
         hs->active = 1;
-        HIPCHK(hipMemcpyAsync(H->st.p, &hs->st, sizeof(BatchSlot), hipMemcpyHostToDevice, R.s));
-        HIPCHK(hipMemcpyAsync(H->flags.p, &hs->active, sizeof(int), hipMemcpyHostToDevice, R.s));
+        HIPCHK(hipMemcpyAsync(&H->state.p->st, &hs->st, sizeof(BatchSlot), hipMemcpyHostToDevice, R.s));
+        HIPCHK(hipMemcpyAsync(&H->state.p->active, &hs->active, sizeof(int), hipMemcpyHostToDevice, R.s));
         restart();
         iterate();
         queued = hs->st.cycles;
@@ -1340,10 +1323,10 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         const Level& L0 = *H->L[0];
         double* u = H->u64[0]->p;
         double* f = H->f64[0]->p;
-        // caller layout -> colour-split level 0; flags[3] = whether the guess
+        // caller layout -> colour-split level 0; guess_nz = whether the guess
         // has a value other than +0.0 (the first residual skips the reads of
         // an all-zero guess)
-        int* const guess_nz = H->flags.p + 3;
+        int* const guess_nz = H->guess_nz.p;
         HIPCHK(hipMemsetAsync(guess_nz, 0, sizeof(int), R.s));
         HIPCHK(launch_fab_to_rb_nz(R.s, L0.view_grid(), (const double*)phi->data, phi->d_fboxes.p, u, guess_nz));
         // f, with the norms of f per tile on the way (reduced below)
@@ -1368,9 +1351,8 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         // level-0 values refreshes the face ghosts it mirrors (push levels)
         fill_faces<double>(R, 0, u);
         const FaceArrays<double>* nf = nullptr;
-        // The stop test runs on the device (the batch engine's, for one
-        // slot): k_batch_admit takes the norm of f, and k_batch_check after
-        // every residual records the history and clears the active flag once
+        // The stop test runs on the device: k_solve_admit takes the norm of f,
+        // and k_solve_check after every residual records the history and clears the active flag once
         // the solve stops (converged, max_cycles, fixed_cycles, non-finite).
         // Every kernel of a V-cycle honours the flag, so the host enqueues
         // cycles ahead of the device and reads the state back only now and
@@ -1381,11 +1363,8 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         S0.abs_tol = P.abs_tol;
         S0.max_cycles = P.max_cycles;
         S0.fixed_cycles = P.fixed_cycles;
-        hs->st = S0;  // pinned: the source of the copy
-        HIPCHK(hipMemcpyAsync(H->st.p, &hs->st, sizeof S0, hipMemcpyHostToDevice, R.s));
-        HIPCHK(launch_norm_final(R.s, H->partials.p, L0.view_grid().ntiles, H->fn3.p));
-        HIPCHK(launch_batch_admit(R.s, H->fn3.p, H->st.p, H->flags.p, 0));
-        R.active = H->flags.p;
+        HIPCHK(launch_solve_admit(R.s, H->partials.p, L0.view_grid().ntiles, S0, H->state.p));
+        R.active = &H->state.p->active;
         // FP64 solves on a pushing, buffer-addressed level 0 with post-smoothing
         // take the colour-1 residual norms in the V-cycle's last level-0 sweep
         const bool fusable = P.precision == 0 && L0.push && L0.res && P.nu2 > 0;
@@ -1393,9 +1372,7 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
         const int* first_nz = guess_nz;  // for the first residual only
         auto check = [&](bool fused) {  // residual of the current iterate, then the stop test
             if (R.streamed) {  // the post-sweeps took all of its norms
-                HIPCHK(launch_norm_final(R.s, H->partials.p, R.streamed, H->fnorm.p));
-                HIPCHK(launch_batch_check(R.s, H->flags.p + 1, 1, H->fnorm.p, H->st.p, H->flags.p, H->hist.p,
-                                          H->hist.p + kHist, H->flags.p + 2));
+                HIPCHK(launch_solve_check(R.s, H->partials.p, R.streamed, H->state.p));
                 R.streamed = 0;
                 return;
             }
@@ -1414,9 +1391,7 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
             }
             first_nz = nullptr;
             R.post(0, kStageResid);
-            HIPCHK(launch_norm_final(R.s, H->partials.p, (fused ? 2 : 1) * L0.ntcol, H->fnorm.p));
-            HIPCHK(launch_batch_check(R.s, H->flags.p + 1, 1, H->fnorm.p, H->st.p, H->flags.p, H->hist.p,
-                                      H->hist.p + kHist, H->flags.p + 2));
+            HIPCHK(launch_solve_check(R.s, H->partials.p, (fused ? 2 : 1) * L0.ntcol, H->state.p));
         };
         auto cycle = [&]() {  // returns whether its last level-0 sweep took the colour-1 norms
             if (P.precision == 0) {
@@ -1441,9 +1416,7 @@ static bxmg_status solve_impl(bxmg_ctx ctx, const bxmg_solve_params* params, bxm
             }
         };
         auto look = [&]() {
-            HIPCHK(hipMemcpyAsync(hs->hist, H->hist.p, 2 * kHist * sizeof(double), hipMemcpyDeviceToHost, R.s));
-            HIPCHK(hipMemcpyAsync(&hs->st, H->st.p, sizeof(BatchSlot), hipMemcpyDeviceToHost, R.s));
-            HIPCHK(hipMemcpyAsync(&hs->active, H->flags.p, sizeof(int), hipMemcpyDeviceToHost, R.s));
+            HIPCHK(hipMemcpyAsync(hs, H->state.p, sizeof(SolveState), hipMemcpyDeviceToHost, R.s));
             HIPCHK(hipStreamSynchronize(R.s));
         };
         // cycles to enqueue ahead of the device, predicted from the history:

@@ -202,6 +202,14 @@ struct BatchSlot {
     int pad;
 };
 constexpr int kHist = 256;
+// A lone solve's stop test on the device, one contiguous copy to the host:
+// the histories (|r|/|f| and |r|_2), the slot, the flag its kernels look at.
+struct SolveState {
+    double hist[kHist];
+    double hist_l2[kHist];
+    BatchSlot st;
+    int active;
+};
 
 // ------------------------------------------------------------ launchers
 // All launchers enqueue on `s` and return hipSuccess or the launch error.
@@ -420,9 +428,11 @@ struct GhostSet {
 };
 hipError_t launch_fill_sets(hipStream_t s, void* data, bool f32, const GhostSet* sets, int nsets, long long max_n,
                             const int* active);
-// Admission of one problem: ||f||_inf from fn3 (max, sum, bad) into st[slot],
-// and active[slot] = 1 unless f is zero or not finite.
-hipError_t launch_batch_admit(hipStream_t s, const double* fn3, BatchSlot* st, int* active, int slot);
+// A lone solve's start (||f||_inf from n partials into slot, active unless f is
+// zero or not finite) and its stop test (the residual's norms from n partials;
+// nothing once the solve has stopped).
+hipError_t launch_solve_admit(hipStream_t s, const double* partials, int n, const BatchSlot& slot, SolveState* state);
+hipError_t launch_solve_check(hipStream_t s, const double* partials, int n, SolveState* state);
 // Admission of n problems in one launch each way: box q of the launch grid g
 // reads the caller's initial guess and right-hand side through src[q]
 // (pointers, and FBoxes whose bases are relative to them) and writes them
@@ -440,14 +450,9 @@ hipError_t launch_admit_convert(hipStream_t s, const Grid& g, const ConvSrc* src
 // a[slots[q]] = v for q < n
 hipError_t launch_set_slots(hipStream_t s, const int* slots, int n, int* a, int v);
 // For q < n: slot = slots[q] takes state states[q] with ||f|| from norms[3 slot]
-// and the decision of launch_batch_admit.
+// and the decision of launch_solve_admit.
 hipError_t launch_batch_admit_many(hipStream_t s, const double* norms, const BatchSlot* states, const int* slots,
                                    int n, BatchSlot* st, int* active);
-// The same decision with the norms of f reduced from n per-tile partials in
-// the same launch (fn3 receives them, as launch_norm_final writes them) and
-// the slot state S passed by value instead of copied to st[slot] beforehand.
-hipError_t launch_batch_admit_norms(hipStream_t s, const double* partials, int n, const BatchSlot& S, double* fn3,
-                                    BatchSlot* st, int* active, int slot);
 // Zero element ranges [start, start + len) of the problems still active.
 struct ZeroRange {
     long long start, len;

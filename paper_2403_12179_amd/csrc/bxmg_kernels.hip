@@ -2772,8 +2772,34 @@ __global__ void __launch_bounds__(kBlock) k_norm_seg(const double* __restrict__ 
     if (threadIdx.x == 0) { norms[3 * p] = mx; norms[3 * p + 1] = s2; norms[3 * p + 2] = bad; }
 }
 
-// One thread per member slot, one block: the same stop test as the
-// single-problem driver (history entry, then stop or count one more cycle).
+// The stop test: history entry, then stop (true) or count one more cycle.
+// norms: (max|r|, sum r^2, non-finite count) of the current iterate.
+__device__ __forceinline__ bool check_slot(BatchSlot& S, const double* norms, double* __restrict__ hist,
+                                           double* __restrict__ hist_l2) {
+    const double rinf = norms[2] > 0.0 ? (double)NAN : norms[0];
+    const int c = S.cycles;
+    if (c < kHist) {
+        hist[c] = rinf / S.fnorm;
+        hist_l2[c] = sqrt(norms[1]);
+        S.nhist = c + 1;
+    }
+    bool done = false;
+    if (!(fabs(rinf) <= 1.7976931348623157e308)) {
+        S.status = kStatusNonFinite;
+        done = true;
+    } else if (S.fixed_cycles > 0) {
+        done = (c == S.fixed_cycles);
+    } else if (rinf <= S.rel_tol * S.fnorm || rinf <= S.abs_tol) {
+        done = true;
+    } else if (c == S.max_cycles) {
+        S.status = kStatusNoConv;
+        done = true;
+    }
+    if (!done) S.cycles = c + 1;
+    return done;
+}
+
+// One thread per member slot, one block.
 __global__ void __launch_bounds__(1024) k_batch_check(const int* __restrict__ slots, int n,
                                                      const double* __restrict__ norms, BatchSlot* __restrict__ st,
                                                      int* __restrict__ active, double* __restrict__ hist,
@@ -2788,32 +2814,26 @@ __global__ void __launch_bounds__(1024) k_batch_check(const int* __restrict__ sl
         if (!active[p]) continue;
         if (seen) seen[p] = 1;  // the iterate after this check is no zero guess
         BatchSlot S = st[p];
-        const double rinf = norms[3 * p + 2] > 0.0 ? (double)NAN : norms[3 * p];
-        const int c = S.cycles;
-        if (c < kHist) {
-            hist[(long long)p * kHist + c] = rinf / S.fnorm;
-            hist_l2[(long long)p * kHist + c] = sqrt(norms[3 * p + 1]);
-            S.nhist = c + 1;
-        }
-        bool done = false;
-        if (!(fabs(rinf) <= 1.7976931348623157e308)) {
-            S.status = kStatusNonFinite;
-            done = true;
-        } else if (S.fixed_cycles > 0) {
-            done = (c == S.fixed_cycles);
-        } else if (rinf <= S.rel_tol * S.fnorm || rinf <= S.abs_tol) {
-            done = true;
-        } else if (c == S.max_cycles) {
-            S.status = kStatusNoConv;
-            done = true;
-        }
-        if (done) active[p] = 0;
-        else { S.cycles = c + 1; ++mine; }
+        if (check_slot(S, norms + 3 * p, hist + (long long)p * kHist, hist_l2 + (long long)p * kHist)) active[p] = 0;
+        else ++mine;
         st[p] = S;
     }
     if (mine) atomicAdd(&cnt, mine);
     __syncthreads();
     if (threadIdx.x == 0) *nactive = cnt;
+}
+
+// A lone solve: the norms from their partials and the stop test in one launch.
+__global__ void __launch_bounds__(kNormThreads) k_solve_check(const double* __restrict__ partials, int n,
+                                                             SolveState* __restrict__ D) {
+    __shared__ double sh[3 * (kNormThreads / 64)];
+    if (!D->active) return;
+    double r[3];
+    norm_reduce(partials, n, sh, r[0], r[1], r[2]);
+    if (threadIdx.x != 0) return;
+    BatchSlot S = D->st;
+    if (check_slot(S, r, D->hist, D->hist_l2)) D->active = 0;
+    D->st = S;
 }
 
 template <class T>
@@ -2839,20 +2859,18 @@ __global__ void __launch_bounds__(kBlock) k_fill_sets(T* __restrict__ data, cons
     }
 }
 
-__global__ void k_batch_admit(const double* __restrict__ fn3, BatchSlot* __restrict__ st, int* __restrict__ active,
-                              int slot) {
+// Start of a lone solve: ||f||_inf from its partials into the slot S, active
+// unless f is zero or not finite.
+__global__ void __launch_bounds__(kNormThreads) k_solve_admit(const double* __restrict__ partials, int n, BatchSlot S,
+                                                             SolveState* __restrict__ D) {
+    __shared__ double sh[3 * (kNormThreads / 64)];
+    double f, s2, bad;
+    norm_reduce(partials, n, sh, f, s2, bad);
     if (threadIdx.x != 0) return;
-    BatchSlot S = st[slot];
-    S.fnorm = fn3[0];
-    int act = 1;
-    if (fn3[2] > 0.0) {
-        S.status = kStatusNonFinite;
-        act = 0;
-    } else if (!(fn3[0] > 0.0)) {
-        act = 0;  // f == 0: the solution is the initial guess
-    }
-    st[slot] = S;
-    active[slot] = act;
+    S.fnorm = f;
+    if (bad > 0.0) S.status = kStatusNonFinite;
+    D->st = S;
+    D->active = bad > 0.0 || !(f > 0.0) ? 0 : 1;  // f == 0: the solution is the initial guess
 }
 
 hipError_t launch_fill_sets(hipStream_t s, void* data, bool f32, const GhostSet* sets, int nsets, long long max_n,
@@ -2861,38 +2879,6 @@ hipError_t launch_fill_sets(hipStream_t s, void* data, bool f32, const GhostSet*
     const dim3 G((unsigned)std::min<long long>(nblk(max_n), 1024), (unsigned)nsets);
     if (f32) hipLaunchKernelGGL(k_fill_sets<float>, G, dim3(kBlock), 0, s, (float*)data, sets, active);
     else hipLaunchKernelGGL(k_fill_sets<double>, G, dim3(kBlock), 0, s, (double*)data, sets, active);
-    return hipGetLastError();
-}
-
-// Admission in one launch: the norms of f reduced from the per-tile partials
-// (as k_norm_final, into fn3), the slot state S written, then the decision
-// of k_batch_admit.
-__global__ void __launch_bounds__(kNormThreads) k_batch_admit_norms(const double* __restrict__ partials, int n,
-                                                                   BatchSlot S, double* __restrict__ fn3,
-                                                                   BatchSlot* __restrict__ st,
-                                                                   int* __restrict__ active, int slot) {
-    __shared__ double sh[3 * (kNormThreads / 64)];
-    double mx, s2, bad;
-    norm_reduce(partials, n, sh, mx, s2, bad);
-    if (threadIdx.x != 0) return;
-    fn3[0] = mx;
-    fn3[1] = s2;
-    fn3[2] = bad;
-    S.fnorm = mx;
-    int act = 1;
-    if (bad > 0.0) {
-        S.status = kStatusNonFinite;
-        act = 0;
-    } else if (!(mx > 0.0)) {
-        act = 0;  // f == 0: the solution is the initial guess
-    }
-    st[slot] = S;
-    active[slot] = act;
-}
-
-hipError_t launch_batch_admit_norms(hipStream_t s, const double* partials, int n, const BatchSlot& S, double* fn3,
-                                    BatchSlot* st, int* active, int slot) {
-    hipLaunchKernelGGL(k_batch_admit_norms, dim3(1), dim3(kNormThreads), 0, s, partials, n, S, fn3, st, active, slot);
     return hipGetLastError();
 }
 
@@ -2930,8 +2916,13 @@ hipError_t launch_batch_admit_many(hipStream_t s, const double* norms, const Bat
     return hipGetLastError();
 }
 
-hipError_t launch_batch_admit(hipStream_t s, const double* fn3, BatchSlot* st, int* active, int slot) {
-    hipLaunchKernelGGL(k_batch_admit, dim3(1), dim3(64), 0, s, fn3, st, active, slot);
+hipError_t launch_solve_admit(hipStream_t s, const double* partials, int n, const BatchSlot& slot, SolveState* state) {
+    hipLaunchKernelGGL(k_solve_admit, dim3(1), dim3(kNormThreads), 0, s, partials, n, slot, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_solve_check(hipStream_t s, const double* partials, int n, SolveState* state) {
+    hipLaunchKernelGGL(k_solve_check, dim3(1), dim3(kNormThreads), 0, s, partials, n, state);
     return hipGetLastError();
 }
 
