@@ -301,13 +301,11 @@ struct BLevel {
     DevVec<FaceArrays<float>> fat32;
     int flip = 0;
     // streaming smoother (every member's level is one box, FP32, constant
-    // coefficient): the launches before and after the coarse levels, and above
-    // level 0 the boxes in the second iterate array
+    // coefficient): the launches before and after the coarse levels
     bool stream = false;
     DevVec<SweepArgs> pre, post;
     DevVec<int2> pre_at, post_at;
     int npre = 0, npost = 0, pre_threads = 0, post_threads = 0;
-    DevVec<RBox> rb2;
 };
 
 struct Done {
@@ -515,15 +513,14 @@ std::vector<int2> deal_blocks(const std::vector<SweepArgs>& jobs) {
 // Levels whose pre- and post-sweeps are one launch each over all problems.
 // The sweeps write another array than they read.  Level 0 needs none: the
 // pre-sweeps start from zero, and the post-sweeps add their result to the
-// FP64 iterate.  Above it the pre-sweeps' array, which the prolongation
-// corrects, lies in the ranges that the level has in the FP64 arena and that
+// FP64 iterate.  Above it the pre-sweeps' array lies in the ranges that the level has in the FP64 arena and that
 // a mixed-precision batch otherwise leaves idle; FP64 batches have no such
 // range and keep one launch per half-sweep.  64 periodic problems of 32^3 to
-// 128^3 (52 million cells): the level-0 sweeps, restriction, zeroing and the
-// update of the iterate took 8 x 91 + 372 us a cycle and take 216 + 415; the
-// batch went from 23.0 to 17.0 ms.  With blocks in problem order and an equal
-// share of the chip planned for every problem it took 19.2: a launch ends with
-// its longest blocks, and the largest problems set it.
+// 128^3 (52 million cells): the level-0 sweeps, transfers, zeroing and the
+// update of the iterate took 8 x 91 + 555 us a cycle and take 219 + 455; the
+// batch went from 23.0 to 15.5 ms.  With blocks in problem order and an equal
+// share of the chip planned for every problem the sweeps took a quarter more:
+// a launch ends with its longest blocks, and the largest problems set it.
 void plan_streams(bxmg_batch_s* b) {
     for (BLevel& B : b->lev) B.stream = false;
     if (b->prec != 1 || b->var || b->P.nu1 != 2 || b->P.nu2 != 2) return;
@@ -536,19 +533,11 @@ void plan_streams(bxmg_batch_s* b) {
         if (l + 1 < b->lmax && !b->lev[l + 1].stream) continue;
         std::map<const GeoPlan*, std::array<SweepPlan, 2>> plans;
         std::vector<SweepArgs> job[2];
-        std::vector<RBox> rb2;
         int threads[2] = {0, 0};
         bool ok = true;
         for (int s : b->members) {
             const Problem& p = *b->slots[s];
             const GeoPlan& G = *p.plan;
-            if (l >= (int)G.L.size()) continue;
-            RBox r2 = G.L[l].rb[0];
-            r2.base = 2 * (r2.base + p.off);
-            r2.pid = s;
-            for (int q = 0; q < 6; ++q)
-                if (r2.nb[q] >= 0) r2.nb[q] = (int)rb2.size();
-            rb2.push_back(r2);
             if (l >= G.cs) continue;
             if (G.L[l + 1].rb.size() != 1) { ok = false; break; }
             auto it = plans.find(&G);
@@ -572,6 +561,8 @@ void plan_streams(bxmg_batch_s* b) {
                 A.f = at0;
                 A.cf = p.off + G.L[l + 1].off;
                 A.acc = at0;
+                A.ec = p.off + G.L[l + 1].off;
+                A.order = b->P.prolong;
                 A.uin = second;
                 A.uout = k ? at0 : second;
                 job[k].push_back(A);
@@ -589,7 +580,6 @@ void plan_streams(bxmg_batch_s* b) {
         B.npost = (int)post.size();
         B.pre_threads = threads[0];
         B.post_threads = threads[1];
-        if (l) B.rb2.assign(rb2);
     }
 }
 
@@ -811,13 +801,13 @@ void b_sweep_pre(bxmg_batch_s* b, hipStream_t s, int l) {
     BLevel& B = b->lev[l];
     float* a = second_array(b, l);
     HIPCHK(launch_sweep_jobs(s, B.pre.p(), B.pre_at.p(), B.npre, B.pre_threads, kSweepRestrict, a, a, b->f32.p,
-                             b->f32.p, nullptr, b->active.p));
+                             b->f32.p, nullptr, b->active.p, nullptr));
 }
 
 void b_sweep_post(bxmg_batch_s* b, hipStream_t s, int l) {
     BLevel& B = b->lev[l];
     HIPCHK(launch_sweep_jobs(s, B.post.p(), B.post_at.p(), B.npost, B.post_threads, l ? kSweepPlain : kSweepAdd,
-                             second_array(b, l), b->u32.p, b->f32.p, nullptr, b->u64.p, b->active.p));
+                             second_array(b, l), b->u32.p, b->f32.p, nullptr, b->u64.p, b->active.p, b->u32.p));
 }
 
 template <class T>
@@ -844,21 +834,18 @@ void b_vcycle(bxmg_batch_s* b, hipStream_t s) {
     else HIPCHK(launch_coarse_cycle<T>(s, coarse_descs<T>(b), b->ncc, b->active.p, b->var, b->cc_bottom));
     for (int l = b->lmax - 1; l >= 0; --l) {
         BLevel& B = b->lev[l];
+        if (B.stream) {
+            b_sweep_post(b, s, l);
+            continue;
+        }
         // small one-box coarse levels: the staged prolongation reads the
         // cells their ghosts mirror, so no ghost refresh before it
-        Grid g = level_grid(b, l);
+        const Grid g = level_grid(b, l);
         const bool self = B.coarse_self && prolong_staged(g.push, b->P.nu2 > 0, B.stage_values);
         if (!self) HIPCHK(launch_fill_sets(s, u, f32, B.fullc.p(), B.nfullc, B.mfullc, b->active.p));
-        T* uf = u;
-        if constexpr (std::is_same<T, float>::value)
-            if (B.stream && l > 0) {
-                g.boxes = B.rb2.p();
-                uf = second_array(b, l);
-            }
-        HIPCHK(launch_prolong<T>(s, g, b->lev[l + 1].rb.p(), B.cbox.p(), u, uf, b->P.prolong, b->P.nu2 > 0,
+        HIPCHK(launch_prolong<T>(s, g, b->lev[l + 1].rb.p(), B.cbox.p(), u, u, b->P.prolong, b->P.nu2 > 0,
                                  B.stage_values, self));
-        if (B.stream) b_sweep_post(b, s, l);
-        else b_smooth<T>(b, s, l, b->P.nu2);
+        b_smooth<T>(b, s, l, b->P.nu2);
     }
 }
 

@@ -62,6 +62,17 @@ __device__ __forceinline__ T harm(T a, T b) {
     return (a * b) * T(2) / (a + b);
 }
 
+// A value that is the same in every lane, into scalar registers.
+__device__ __forceinline__ float uniform(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 // Fixed-tree block reduction of (max, sum, sum): wave64 butterflies, then
 // the 4 wave results in order.  The result is valid in thread 0.
 __device__ __forceinline__ void block_reduce3(double& mx, double& s2, double& bad, double* sh) {

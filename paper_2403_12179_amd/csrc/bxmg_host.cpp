@@ -584,7 +584,8 @@ void vcycle(Run& R, size_t l) {
         const SweepPlan& P = L.sweep[kSweepRestrict][zero ? 1 : 0];
         R.pre(l, kStageGS);
         HIPCHK(launch_sweep<T>(R.s, P, zero, false, kSweepRestrict, lvl_u<T>(H, l), u, lvl_f<T>(H, l),
-                               lvl_f<T>(H, l + 1), nullptr, nullptr, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l)));
+                               lvl_f<T>(H, l + 1), nullptr, nullptr, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l),
+                               (const T*)nullptr, R.prolong));
         R.post(l, kStageGS);
     } else {
     smooth<T>(R, l, R.nu1);
@@ -600,6 +601,18 @@ void vcycle(Run& R, size_t l) {
     R.post(l, kStageRestrict);
     }
     vcycle<T>(R, l + 1);
+    if (stream) {
+        const bool norm = R.stream_norms && l == 0;
+        const int kind = norm ? kSweepNorm : R.stream_add && l == 0 ? kSweepAdd : kSweepPlain;
+        const SweepPlan& P = L.sweep[kind][0];
+        R.pre(l, kStageGS);
+        HIPCHK(launch_sweep<T>(R.s, P, false, true, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
+                               R.stream_add, R.stream_norms, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l),
+                               lvl_u<T>(H, l + 1), R.prolong));
+        R.post(l, kStageGS);
+        if (norm) R.streamed = P.blocks;
+        return;
+    }
     // a small one-box coarse level needs no ghost refresh where the staged
     // prolongation reads the cells its ghosts mirror (on large levels the
     // refresh launch costs less than the mirroring in every tile)
@@ -617,18 +630,7 @@ void vcycle(Run& R, size_t l) {
     HIPCHK(launch_prolong<T>(R.s, R.grid(L.walk()), C.d_rb.p, L.cbox.p, lvl_u<T>(H, l + 1), u, R.prolong, R.nu2 > 0,
                              L.stage_values, self, faces));
     R.post(l, kStageProlong);
-    if (!stream) {
-        smooth<T>(R, l, R.nu2, true);
-        return;
-    }
-    const bool norm = R.stream_norms && l == 0;
-    const int kind = norm ? kSweepNorm : R.stream_add && l == 0 ? kSweepAdd : kSweepPlain;
-    const SweepPlan& P = L.sweep[kind][0];
-    R.pre(l, kStageGS);
-    HIPCHK(launch_sweep<T>(R.s, P, false, true, kind, u, lvl_u<T>(H, l), lvl_f<T>(H, l), (T*)nullptr,
-                           R.stream_add, R.stream_norms, R.active, mode, lvl_beta<T>(H, l), lvl_fat<T>(H, l)));
-    R.post(l, kStageGS);
-    if (norm) R.streamed = P.blocks;
+    smooth<T>(R, l, R.nu2, true);
 }
 
 // Coefficient setup: cell beta at level 0 (exchange + even reflection), then

@@ -254,7 +254,8 @@ struct SweepArgs {
     int cH, cGH, ccs, cpar;  // the coarse level's storage; parity of its lower corner
     int pid;           // problem slot of active[]
     double h, a;
-    long long uin, uout, f, cf, acc;  // launch_sweep_jobs: element offsets of the arrays
+    int order;         // of the prolongation
+    long long uin, uout, f, cf, acc, ec;  // launch_sweep_jobs: element offsets of the arrays
 };
 struct SweepPlan {
     int nt = 0;  // the kernel's form: up to 256, 512, 768 or 1024 threads (0: the level is not streamed)
@@ -270,22 +271,23 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
 SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int kind, bool zero, bool f32,
                            int mode = 0, int cus = 256, int ntmax = 1024);
 // uin (not read when zero: the sweeps start from u = 0) -> uout, another
-// array.  post: the sweeps after a prolongation that left colour 0 to them
-// (launch_prolong, only_c1).  uout's ghosts are not written.  cf: the coarse f
-// (kSweepRestrict); acc: what the result is added to, its face ghosts
-// refreshed (kSweepAdd); partials: 3 per block (kSweepNorm).  mode 0: constant
-// coefficient; FP32 only, 1: the cell beta, 2: face arrays fat[args.pid].
+// array, ghosts neither read nor written.  post: the sweeps after the coarse
+// levels, uin corrected by the interpolation (order 1 or 2) of ec, the next
+// level's u, on the way.  cf: the coarse f (kSweepRestrict); acc: what the
+// result is added to, its face ghosts refreshed (kSweepAdd); partials: 3 per
+// block (kSweepNorm).  mode 0: constant coefficient; FP32 only, 1: the cell
+// beta, 2: face arrays fat[args.pid].
 template <class T>
 hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
                         const T* f, T* cf, double* acc, double* partials, const int* active, int mode,
-                        const T* beta, const FaceArrays<T>* fat);
+                        const T* beta, const FaceArrays<T>* fat, const T* ec, int order);
 // FP32 over many levels in one launch of blocks of threads threads: block b
 // works block where[b].y of the level jobs[where[b].x], planned for at most
 // kSweepJobThreads threads.  kSweepRestrict (from zero), kSweepPlain, kSweepAdd.
 constexpr int kSweepJobThreads = 512;
 hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* where, int blocks, int threads,
                              int kind, const float* uin, float* uout, const float* f, float* cf, double* acc,
-                             const int* active);
+                             const int* active, const float* ec);
 
 // r = f - L u on both colours, optional store of r (R = T, or float for the
 // mixed-precision cast), partial norms (max|r|, sum r^2, bad count) at

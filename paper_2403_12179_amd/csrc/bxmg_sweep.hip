@@ -28,25 +28,25 @@
 // compiled for the walls it touches (none, an x face alone, any).
 //
 // Measured on the 256^3 FP64 Dirichlet level 0: two sweeps, residual and
-// restriction 181 us, against 4 x 50 + 66 us one launch each; two sweeps and
-// the norms 186, two sweeps from zero 114.  The arrays alone take 52 to 66 us
-// at the copy rate; loads, stores, LDS traffic (18 reads and 6 writes of a
-// value per thread and step) and FP64 issue (about 85 instructions) overlap
-// only in part, as a block's waves run the same phase of a step together.
-// The 256^3 solve went from 8.77 to 6.06 ms, the 192^3 heat step from 4.47 to
-// 3.37 ms.  Adding an FP32 correction to the FP64 iterate (kSweepAdd) takes
-// 415 us over the 52 million cells of 64 problems, 240 of which are its bytes
-// at the copy rate.
+// restriction 160 us, against 4 x 50 + 66 us one launch each; two sweeps after
+// the coarse levels with the interpolation and the norms 217, against 58 + 4 x
+// 50 + 66.  The arrays alone take 52 to 66 us at the copy rate; loads, stores,
+// LDS traffic (18 to 26 reads and 6 writes of a value per thread and step) and
+// FP64 issue (85 to 110 instructions) overlap only in part, as a block's waves
+// run the same phase of a step together.  The 256^3 solve went from 8.78 to
+// 5.56 ms, the 192^3 heat step from 4.49 to 2.60 ms.  Adding an FP32
+// correction to the FP64 iterate (kSweepAdd) takes 455 us over the 52 million
+// cells of 64 problems, 240 of which are its bytes at the copy rate.
 //
 // With a coefficient (FP32) a thread has the 9 faces of its pair formed once
 // per plane and kept in 60 registers: a half-sweep launch forms 6 harmonic
 // means per cell, each a division.  Bound by that arithmetic (about 240
 // instructions a step, 140 of them the 13 divisions) times the recomputed
 // halo: 512^3, cell beta, sweeps from zero with residual and restriction 1380
-// us against 4 x 396 + 615, sweeps after the prolongation 1080 against 4 x
-// 396; 256^3 with face arrays 161 and 163 us against 4 x 60 + 97 and 4 x 60.
-// The 512^3 preconditioned solve went from 164 to 133 ms, the 128^3 mixed one
-// from 7.4 to 6.4 (its level 0 takes as long either way).
+// us against 4 x 396 + 615, sweeps after the coarse levels 1255 against 256 + 4
+// x 396; 256^3 with face arrays 160 and 180 us against 4 x 60 + 97 and 85 + 4 x
+// 60.  The 512^3 preconditioned solve went from 164 to 112 ms (with its
+// direction pass below), the 128^3 mixed one from 6.8 to 5.2.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -57,10 +57,16 @@
 namespace bxmg {
 
 // KIND (SweepKind): what follows the sweeps.  ZERO: they start from u = 0,
-// which is not read.  POST: the sweeps after a prolongation, which leaves
-// colour 0 to them: colour 0's old values, read only beside Dirichlet faces,
-// are minus the ghosts there.  uout's ghosts are left alone: no streamed level
-// reads them.
+// which is not read.  POST: the sweeps after the coarse levels, whose
+// correction (ec, the next level's u) is interpolated on the way in: colour 1
+// as it enters, colour 0's old value only where it is read, beside Dirichlet
+// faces.  The coarse planes of a block's columns go through LDS, four at a
+// time, a ghost there being the cell it mirrors (minus, beyond a Dirichlet
+// face); a thread carries one value of the next plane.  So the prolongation
+// costs 8 LDS reads a pair and no pass of its own: 256^3 FP64, sweeps and norms
+// 217 us with it, 197 without, and 58 the three launches that it took; 192^3
+// 104 against 85 + 46.
+// No ghost is read or written.
 // NT: threads per block (columns of a block, halo included, at most NT).
 // kSweepAdd: the result is added to acc (and its face ghosts refreshed)
 // instead of being stored.  JOBS: many levels in one launch; block b works
@@ -74,13 +80,14 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
                                              T* __restrict__ uout, const T* __restrict__ f, T* __restrict__ cf,
                                              double* __restrict__ acc, double* __restrict__ partials,
                                              const int* __restrict__ active, const T* __restrict__ beta,
-                                             const FaceArrays<T>* __restrict__ fat) {
+                                             const FaceArrays<T>* __restrict__ fat, const T* __restrict__ ec) {
     using std::integral_constant;
     constexpr bool REST = KIND == kSweepRestrict, NORM = KIND == kSweepNorm, ADD = KIND == kSweepAdd;
     constexpr bool RES = REST || NORM;
     // LDS half planes (one colour of one plane of the block's columns)
     constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bS = 12, bK = REST ? 14 : RES ? 12 : 10;
-    __shared__ T lds[(bK + (MODE == 1 ? 4 : 0)) * NT];  // bK, bK + 2: beta of colour 0, 1
+    constexpr int bC = bK + (MODE == 1 ? 4 : 0);  // (bK, bK + 2: beta of colour 0, 1)
+    __shared__ T lds[(bC + (POST ? 4 : 0)) * NT];  // bC: coarse planes
     const int tid = threadIdx.x;
     // block -> (bx, by, bz), neighbouring blocks on one XCD
     int blk = blockIdx.x, job = 0;
@@ -100,6 +107,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         f += A.f;
         cf += A.cf;
         acc += A.acc;
+        ec += A.ec;
     }
     const int bx = blk % A.nbx, byz = blk / A.nbx;
     const int by = byz % A.nby, bz = byz / A.nby;
@@ -142,23 +150,42 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
     const int es = (int)sizeof(T);
     const int row = (y + 1) * A.H + m, co = A.cs * es, pl = A.GH * es;
     const int vA = in ? (row + yo) * es : kOffPastBox, vB = in ? (row + 1 - yo) * es : kOffPastBox;
-    const int wA = own ? vA : kOffPastBox, wB = own ? vB : kOffPastBox;  // stores past the box are dropped
-    // POST: offset (from the plane's start) of an x or y ghost of the colour-0
-    // cell in planes of even and odd parity; past the box: none
-    int gA = kOffPastBox, gB = kOffPastBox;
+    // POST: the block's coarse columns, one per thread (its offset in a plane,
+    // parity and sign), and the pair's place among them
+    const int y0 = by * A.TY - A.hy, cy0 = (y0 >> 1) - 1, CW = A.RM + 2;
+    int ci = 0, cp = 0, ic = 0;
+    bool cin = false, cneg = false;
     if constexpr (POST) {
-        const int gy = fyl ? row - A.H : fyr ? row + A.H : 0;
-        const bool fy = fyl || fyr;
-        gA = fxA ? ((y + 1) * A.H + (yo ? nm : 0)) * es : fy ? (gy + yo) * es : kOffPastBox;
-        gB = fxB ? ((y + 1) * A.H + (yo ? 0 : nm)) * es : fy ? (gy + 1 - yo) * es : kOffPastBox;
+        const int cy = tid / CW, nr = ((y0 + A.RY - 1) >> 1) + 2 - cy0;
+        cin = cy < nr;
+        auto mirror = [&](int v, int n, int per) {
+            if (per) {
+                v %= n;
+                return v < 0 ? v + n : v;
+            }
+            const bool out = v < 0 || v >= n;
+            cneg = cneg != out;
+            v = v < 0 ? -1 - v : v >= n ? 2 * n - 1 - v : v;
+            return min(max(v, 0), n - 1);  // (columns further out are never used)
+        };
+        const int I = mirror(bx * A.XM - A.hm - 1 + tid - cy * CW, nm, A.per[0]);
+        const int J = mirror(cy0 + cy, n1 >> 1, A.per[1]);
+        ci = cin ? ((J + 1) * A.cH + ((I + 1) >> 1)) * (int)sizeof(T) : kOffPastBox;
+        cp = (I + J + A.cpar) & 1;
+        ic = in ? ((yr >> 1) - cy0) * CW + tm + 1 : CW + 1;
     }
-    const T h2 = (T)(A.h * A.h), ih2 = (T)(1.0 / (A.h * A.h));
-    const T dg = (T)(A.a * (A.h * A.h)), sb = T(6) + dg;
-    const Recip<T> rsb(sb);
+    const T h2 = uniform((T)(A.h * A.h)), ih2 = uniform((T)(1.0 / (A.h * A.h)));
+    const T dg = uniform((T)(A.a * (A.h * A.h))), sb = uniform(T(6) + dg);
+    Recip<T> rsb(sb);
+    rsb.b = sb;
+    rsb.yh = uniform(rsb.yh);
+    rsb.yl = uniform(rsb.yl);
     const int bytes = 2 * A.cs * es;
     const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
     const auto Rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, bytes, kBufferDword3);
     const auto Ro = __builtin_amdgcn_make_buffer_rsrc((void*)uout, (short)0, bytes, kBufferDword3);
+    const auto Rc = __builtin_amdgcn_make_buffer_rsrc((void*)(POST ? ec : f), (short)0,
+                                                      POST ? 2 * A.ccs * es : bytes, kBufferDword3);
     // kSweepAdd: the same cells of acc, loaded with the plane four ahead (a
     // load after a step's stores would wait for them)
     const auto Ra = __builtin_amdgcn_make_buffer_rsrc((void*)(ADD ? (const void*)acc : (const void*)f), (short)0,
@@ -255,16 +282,23 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         if constexpr (!ZERO) {
             b0[PH] = Raw<T>::ld(Ru, vb, zo + co);
             // colour 0's old value is read only through Dirichlet ghosts
-            const bool ez = !perz && (z == 0 || z == n2 - 1);
-            if (edge_xy || ez) {
-                if constexpr (POST) {  // the ghost itself (offsets from the plane below)
-                    const int g = (PH & 1) ? gB : gA, gz = z == 0 ? vr : vr + 2 * pl;
-                    r0[PH] = Raw<T>::ld(Ru, ez && g == kOffPastBox ? gz : g + pl, zo + co - pl);
-                } else {
-                    r0[PH] = Raw<T>::ld(Ru, vr, zo);
-                }
-            }
+            r0[PH] = T(0);  // (or each slot's last value would stay live)
+            if (edge_xy || (!perz && (z == 0 || z == n2 - 1))) r0[PH] = Raw<T>::ld(Ru, vr, zo);
         }
+    };
+    // coarse plane K of the block (wrapped or mirrored; its sign: cneg and beyond)
+    T cr = T(0);
+    auto load_coarse = [&](int K) {
+        const int nk = n2 >> 1;
+        const int below = perz ? K + nk : -1 - K, above = perz ? K - nk : 2 * nk - 1 - K;
+        K = K < 0 ? below : K >= nk ? above : K;
+        if (perz) K = K < 0 ? K + nk : K >= nk ? K - nk : K;  // (twice, as above)
+        K = min(max(K, 0), nk - 1);
+        return Raw<T>::ld(Rc, ci + ((cp + K) & 1) * (A.ccs * es), (K + 1) * A.cGH * es);
+    };
+    auto put_coarse = [&](int slot, int K, T v) {
+        const bool beyond = !perz && (K < 0 || K >= (n2 >> 1));
+        if (cin) lds[(bC + slot) * NT + tid] = cneg != beyond ? -v : v;
     };
 
     // EDGE: 0 inside, 1 beside a Dirichlet x face, 2 beside any
@@ -283,7 +317,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         auto sum = [&](auto dd, auto cc, bool isA, T own_o, Three n, T zm, T zp, T oldv) {
             constexpr int D = decltype(dd)::value, C = decltype(cc)::value;
             if constexpr (EDGE > 0) {
-                const T g = POST && D == 1 ? oldv : -oldv;  // (stage 1 after a prolongation: the ghost's value)
+                const T g = -oldv;
                 n.x = (isA ? fxA : fxB) ? g : n.x;
                 if constexpr (EDGE > 1) {
                     n.d = fyl ? g : n.d;
@@ -304,17 +338,46 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         };
         constexpr integral_constant<int, 0> c0{};
         constexpr integral_constant<int, 1> c1{};
-        // every LDS value of the step, written in earlier steps
+        if constexpr (POST) {
+            // the correction at the colour-c cell of plane q: its parent and the
+            // neighbours towards it
+            auto interp = [&](int c) {
+                constexpr int kr = PH >> 1;  // coarse plane modulo 4, from the first
+                const T* a = lds + (bC + (kr & 3)) * NT + ic;
+                const T* b = lds + (bC + (((PH & 1) ? kr + 1 : kr + 3) & 3)) * NT + ic;
+                const int dx = ISA(0, c) == (yo != 0) ? 1 : -1, dyc = yo ? CW : -CW;
+                const T c000 = a[0], c100 = a[dx], c010 = a[dyc], c001 = b[0];
+                const T c110 = a[dx + dyc], c101 = b[dx], c011 = b[dyc], c111 = b[dx + dyc];
+                const T v =
+                    (((T(27) * c000 + T(9) * ((c100 + c010) + c001)) + T(3) * ((c110 + c101) + c011)) + c111) *
+                    T(0.015625);
+                return A.order == 1 ? c000 : v;
+            };
+            b0[RS(0)] = b0[RS(0)] + interp(1);
+            if constexpr (EDGE > 0) r0[RS(0)] = r0[RS(0)] + interp(0);
+            if constexpr ((PH & 1) == 0) {
+                put_coarse(((PH >> 1) + 1) & 3, (q >> 1) + 1, cr);
+                cr = load_coarse((q >> 1) + 2);
+            }
+            if constexpr (NORM || MODE != 0) __builtin_amdgcn_sched_barrier(0);
+        }
+        // every LDS value of the step, written in earlier steps (in parts where
+        // all of them at once would spill)
+        constexpr bool kTight = POST && (NORM || MODE != 0);
         Three t1{}, t2, t3, t4, t5r{}, t5b{};
         T spart = T(0);
         if constexpr (!ZERO) t1 = near(bB0 + ((PH - 1) & 1), ISA(1, 0));
         t2 = near(bR1 + ((PH - 1) & 1), ISA(2, 1));
-        t3 = near(bB2 + ((PH - 1) & 1), ISA(3, 0));
-        t4 = near(bR3 + ((PH - 1) & 3), ISA(4, 1));
-        if constexpr (RES) {
+        auto near34 = [&] {
+            t3 = near(bB2 + ((PH - 1) & 1), ISA(3, 0));
+            t4 = near(bR3 + ((PH - 1) & 3), ISA(4, 1));
+        };
+        if constexpr (!kTight) near34();
+        auto near5 = [&] {
             t5r = near(bB4 + ((PH - 1) & 1), ISA(5, 0));
             t5b = near(bR3 + ((PH - 2) & 3), ISA(5, 1));
-        }
+        };
+        if constexpr (RES && !kTight) near5();
         if constexpr (REST) spart = lds[(bS + ((PH - 1) & 1)) * NT + sup];
         if constexpr (MODE == 1) {
             const Three k0 = near(bK + 2 + ((PH - 1) & 1), ISA(1, 0)), k1 = near(bK + ((PH - 1) & 1), ISA(1, 1));
@@ -364,6 +427,10 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
             b2[RS(2)] = relax(integral_constant<int, 2>(), c1, su - h2 * fb[RS(2)]);
             lds[(bB2 + (PH & 1)) * NT + tid] = b2[RS(2)];
         }
+        if constexpr (kTight) {
+            __builtin_amdgcn_sched_barrier(0);
+            near34();
+        }
         {  // stage 3
             const T su = sum(integral_constant<int, 3>(), c0, ISA(3, 0), b2[RS(3)], t3, b2[RS(4)], b2[RS(2)], r1[RS(3)]);
             r3[RS(3)] = relax(integral_constant<int, 3>(), c0, su - h2 * fr[RS(3)]);
@@ -378,10 +445,10 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
             const int p = q - 4;
             const bool mine = p >= z0 && p < zlim;
             const int zo = (p + 1) * pl;
-            const int vr = (PH & 1) ? wB : wA, vb = (PH & 1) ? wA : wB;
-            if constexpr (!ADD) {
-                Raw<T>::st(Ro, mine ? vr : kOffPastBox, zo, r3[RS(4)]);
-                Raw<T>::st(Ro, mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
+            const int vr = (PH & 1) ? vB : vA, vb = (PH & 1) ? vA : vB;
+            if constexpr (!ADD) {  // (stores past the box are dropped)
+                Raw<T>::st(Ro, own && mine ? vr : kOffPastBox, zo, r3[RS(4)]);
+                Raw<T>::st(Ro, own && mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
             } else {
                 const int cd = A.cs * 8, zd = (p + 1) * A.GH * 8;
                 const double x0 = a0[PH & 3] + (double)r3[RS(4)], x1 = a1[PH & 3] + (double)b4[RS(4)];
@@ -412,6 +479,10 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
             }
         }
         if constexpr (RES) {  // stage 5
+            if constexpr (kTight) {
+                __builtin_amdgcn_sched_barrier(0);
+                near5();
+            }
             const T sur =
                 sum(integral_constant<int, 5>(), c0, ISA(5, 0), b4[RS(5)], t5r, b4[RS(6)], b4[RS(4)], r3[RS(5)]);
             const T rr = fr[RS(5)] - (sur - (MODE == 0 ? sb : ks[0][RS(5)]) * r3[RS(5)]) * ih2;
@@ -453,6 +524,13 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
 #undef ISA
     };
 
+    if constexpr (POST) {
+        const T a = load_coarse((zs >> 1) - 1), b = load_coarse(zs >> 1);
+        cr = load_coarse((zs >> 1) + 1);
+        put_coarse(3, (zs >> 1) - 1, a);
+        put_coarse(0, zs >> 1, b);
+        lds_barrier();
+    }
     load(integral_constant<int, 0>(), zs);
     load(integral_constant<int, 1>(), zs + 1);
     for (int qb = zs;; qb += 8) {
@@ -461,7 +539,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         const int q = qb + PH;                                                                 \
         if (q >= zend) break;                                                                  \
         load(integral_constant<int, (PH + 2) & 7>(), q + 2);                                   \
-        if (edge_y || (!perz && (q <= 5 || q >= n2)))                                          \
+        if (edge_y || (!perz && (q <= 5 || q >= n2 - 1)))                                      \
             step(integral_constant<int, PH>(), integral_constant<int, 2>(), q);                \
         else if (edge_xy) step(integral_constant<int, PH>(), integral_constant<int, 1>(), q);  \
         else step(integral_constant<int, PH>(), integral_constant<int, 0>(), q);               \
@@ -721,8 +799,8 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
     const int lead = ((halo + 1) & ~1) + (kind == kSweepRestrict ? 6 : res ? 5 : 4);
     const int nm = n[0] / 2;
     // (the FP64 forms and those with coefficients keep up to 168 registers a
-    // thread: at most 12 waves)
-    ntmax = std::min(ntmax, f32 && mode == 0 ? 1024 : 768);
+    // thread: at most 12 waves, 8 where those would spill)
+    ntmax = std::min(ntmax, f32 && mode == 0 ? 1024 : mode == 2 && kind != kSweepRestrict ? 512 : 768);
     double cost = 1e30;
     auto split = [](int cells, int pieces, int unit) {  // the size of equal pieces, a multiple of unit
         const int u = cells / unit, q = (u + pieces - 1) / pieces;
@@ -738,7 +816,8 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
             const int TY = split(n[1], py, 2);
             const bool wy = TY == n[1];
             const int hy = wy ? 0 : halo, RY = TY + 2 * hy;
-            const int cols = RM * RY;
+            // (after the coarse levels a block also needs a thread per coarse column)
+            const int cols = std::max(RM * RY, kind == kSweepRestrict ? 0 : (RM + 2) * (RY / 2 + 3));
             if (cols > ntmax) continue;
             const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : cols <= 768 ? 768 : 1024;
             const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
@@ -796,17 +875,20 @@ SweepPlan plan_sweep_level(const RBox& B, const RBox& Q, const int per[3], int k
 template <class T>
 hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post, int kind, const T* uin, T* uout,
                         const T* f, T* cf, double* acc, double* partials, const int* active, int mode, const T* beta,
-                        const FaceArrays<T>* fat) {
+                        const FaceArrays<T>* fat, const T* ec, int order) {
     const dim3 G((unsigned)P.blocks);
+    SweepArgs args = P.args;
+    args.order = order;
     constexpr bool F64 = std::is_same<T, double>::value;
 #define BXMG_SW(NT, ZERO, KIND, POST, MODE)                                                                       \
-    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, false, MODE>), G, dim3(P.threads), 0, s, P.args,         \
+    hipLaunchKernelGGL((k_sweep<T, NT, ZERO, KIND, POST, false, MODE>), G, dim3(P.threads), 0, s, args,           \
                        (const SweepArgs*)nullptr, (const int2*)nullptr, uin, uout, f, cf, acc, partials, active, \
-                       beta, fat)
+                       beta, fat, ec)
 #define BXMG_SWN(ZERO, KIND, POST, MODE)                   \
     if (P.nt == 256) BXMG_SW(256, ZERO, KIND, POST, MODE); \
     else if (P.nt == 512) BXMG_SW(512, ZERO, KIND, POST, MODE); \
-    else if (P.nt == 768) BXMG_SW(768, ZERO, KIND, POST, MODE); \
+    else if (MODE == 2 && POST) return hipErrorInvalidValue; \
+    else if (P.nt == 768) BXMG_SW((MODE == 2 && POST ? 512 : 768), ZERO, KIND, POST, MODE); \
     else if constexpr (!F64 && MODE == 0) BXMG_SW(1024, ZERO, KIND, POST, MODE); \
     else return hipErrorInvalidValue
 #define BXMG_SWM(ZERO, KIND, POST)                                \
@@ -838,20 +920,20 @@ hipError_t launch_sweep(hipStream_t s, const SweepPlan& P, bool zero, bool post,
 }
 template hipError_t launch_sweep<double>(hipStream_t, const SweepPlan&, bool, bool, int, const double*, double*,
                                          const double*, double*, double*, double*, const int*, int, const double*,
-                                         const FaceArrays<double>*);
+                                         const FaceArrays<double>*, const double*, int);
 template hipError_t launch_sweep<float>(hipStream_t, const SweepPlan&, bool, bool, int, const float*, float*,
                                         const float*, float*, double*, double*, const int*, int, const float*,
-                                        const FaceArrays<float>*);
+                                        const FaceArrays<float>*, const float*, int);
 
 hipError_t launch_sweep_jobs(hipStream_t s, const SweepArgs* jobs, const int2* where, int blocks, int threads,
                              int kind, const float* uin, float* uout, const float* f, float* cf, double* acc,
-                             const int* active) {
+                             const int* active, const float* ec) {
     if (blocks <= 0) return hipSuccess;
     if (threads > kSweepJobThreads) return hipErrorInvalidValue;
 #define BXMG_SWJ(ZERO, KIND, POST)                                                                               \
     hipLaunchKernelGGL((k_sweep<float, kSweepJobThreads, ZERO, KIND, POST, true, 0>), dim3(blocks), dim3(threads), 0, s, \
                        SweepArgs{}, jobs, where, uin, uout, f, cf, acc, (double*)nullptr, active, (const float*)nullptr, \
-                       (const FaceArrays<float>*)nullptr)
+                       (const FaceArrays<float>*)nullptr, ec)
     if (kind == kSweepRestrict) BXMG_SWJ(true, kSweepRestrict, false);
     else if (kind == kSweepPlain) BXMG_SWJ(false, kSweepPlain, true);
     else if (kind == kSweepAdd) BXMG_SWJ(false, kSweepAdd, true);
