@@ -195,24 +195,30 @@ __global__ void __launch_bounds__(kNB) k_nd_resid(NLev L, const double* __restri
 // ZERO: the sweeps start from u = 0, which is not read; otherwise colour 0 is
 // read at boundary nodes only.  KIND: 0 no residual, 1 the residual of the
 // unknowns into r, 2 its norms (3 partials per block).  uin and uout differ.
-// 256^3, FP64: sweeps and residual 171 us, sweeps and norms 175, against 4 x 56
-// and 122 in launches of their own; 128^3 28 and 23 us, against 4 x 9.0 and 17.
-// The arrays alone (u, f in, u, r out) take about 100 us at the copy rate.
+// POST: the sweeps after the coarse levels; the correction e of colour 1 is
+// interpolated as it enters, from the coarse planes of the block's columns in
+// LDS (two at a time, a thread carrying one value of the next).
+// 256^3, FP64: sweeps and residual 165 us, sweeps with the interpolation and the
+// norms 195, against 4 x 56 + 122 and 159 + 4 x 56 + 122 in launches of their
+// own; 128^3 27 and 28 us, against 4 x 9.0 + 17 and 12 + 4 x 9.0.  The arrays
+// alone (u, f in, u, r out) take about 100 us at the copy rate.
 struct NSweep {
     int nt = 0, threads = 0, blocks = 0;
     int RM, RY;          // columns of a block with its halo: pairs, rows
     int hm, hy;          // the halo below: pairs, rows (0: the block spans the level there)
     int XM, TY, ZC;      // what a block owns
     int nbx, nby, nbz;
+    int cH, cpl, ccs;    // the coarse level: row, plane and colour block (elements)
 };
-template <int NT, bool ZERO, int KIND>
+template <int NT, bool ZERO, int KIND, bool POST>
 __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double* __restrict__ uin,
                                                 double* __restrict__ uout, const double* __restrict__ f,
-                                                double* __restrict__ r, double* __restrict__ partials) {
+                                                double* __restrict__ r, double* __restrict__ partials,
+                                                const double* __restrict__ e) {
     using std::integral_constant;
     constexpr bool RES = KIND != 0;
-    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10;
-    __shared__ double lds[(RES ? 12 : 10) * NT];
+    constexpr int bB0 = 0, bR1 = 2, bB2 = 4, bR3 = 6, bB4 = 10, bC = RES ? 12 : 10;
+    __shared__ double lds[(bC + (POST ? 2 : 0)) * NT];
     const int tid = threadIdx.x;
     int blk = blockIdx.x;
     {
@@ -256,9 +262,37 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
     const int v = in ? (y * L.H + m) * 8 : kOffPastBox;
     const int co = (int)L.cs * 8, pl = L.H * (n1 + 1) * 8;
     const int w = own ? v : kOffPastBox;
-    const double h2 = L.h * L.h, ih2 = 1.0 / (L.h * L.h);
+    const double h2 = uniform(L.h * L.h), ih2 = uniform(1.0 / (L.h * L.h));
     const Recip<double> r6(6.0);
     const int bytes = 2 * co;
+    // POST: the block's coarse columns, one per thread (offset in a plane, parity
+    // of I + J), and the pair's place among them
+    const int y0 = by * A.TY - A.hy, CW = A.RM + 1;
+    int ci = kOffPastBox, cp = 0, ic = 0;
+    if constexpr (POST) {
+        const int cy = tid / CW, nr = ((y0 + A.RY - 1) >> 1) + 2 - (y0 >> 1);
+        auto node = [](int c, int n, bool per) {
+            if (!per) return min(max(c, 0), n);
+            c %= n;
+            return c < 0 ? c + n : c;
+        };
+        const int I = node(bx * A.XM - A.hm + tid - cy * CW, nm, perx), J = node((y0 >> 1) + cy, n1 >> 1, pery);
+        if (cy < nr) ci = (J * A.cH + (I >> 1)) * 8;
+        cp = (I + J) & 1;
+        ic = in ? ((yr >> 1) - (y0 >> 1)) * CW + tm : 0;
+    }
+    const auto Rc = __builtin_amdgcn_make_buffer_rsrc((void*)(POST ? e : f), (short)0, POST ? 2 * A.ccs * 8 : bytes,
+                                                      kBufferDword3);
+    auto load_coarse = [&](int K) {  // of plane K (wrapped; past the last one of a Dirichlet level: any)
+        const int nk = n2 >> 1;
+        if (perz) {
+            K = K < 0 ? K + nk : K >= nk ? K - nk : K;
+            K = K < 0 ? K + nk : K >= nk ? K - nk : K;
+        }
+        K = min(max(K, 0), nk);
+        return Raw<double>::ld(Rc, ci + ((cp + K) & 1) * (A.ccs * 8), K * A.cpl * 8);
+    };
+    double cr = 0.0;
     const auto Ru = __builtin_amdgcn_make_buffer_rsrc((void*)(ZERO ? f : uin), (short)0, bytes, kBufferDword3);
     const auto Rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, bytes, kBufferDword3);
     const auto Ro = __builtin_amdgcn_make_buffer_rsrc((void*)uout, (short)0, bytes, kBufferDword3);
@@ -288,6 +322,7 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
         if constexpr (!ZERO) {
             b0[PH] = Raw<double>::ld(Ru, v, zo + co);
             const bool fz = !perz && (z == 0 || z == n2);
+            r0[PH] = 0.0;  // (or each slot's last value would stay live)
             if (edge_xy || fz) {
                 const bool fix = fz || ((PH & 1) ? fixB : fixA);
                 r0[PH] = Raw<double>::ld(Ru, fix ? v : kOffPastBox, zo);
@@ -313,6 +348,28 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
             if constexpr (EDGE) return fixed(d, isA) ? old : x;
             else return x;
         };
+        if constexpr (POST) {
+            // colour 1 of plane q: its row's parity decides between 2 coarse nodes
+            // along x or y (even planes), 2 along z or all 8 (odd ones)
+            const double* a = lds + (bC + ((PH >> 1) & 1)) * NT + ic;
+            double v;
+            if constexpr ((PH & 1) == 0) {
+                v = (a[0] + a[yo ? CW : 1]) * 0.5;
+            } else {
+                const double* b = lds + (bC + (((PH >> 1) + 1) & 1)) * NT + ic;
+                const double two = (a[0] + b[0]) * 0.5;
+                const double all =
+                    (((((((a[0] + a[1]) + a[CW]) + a[CW + 1]) + b[0]) + b[1]) + b[CW]) + b[CW + 1]) * 0.125;
+                v = yo ? all : two;
+            }
+            const double x = b0[RS(0)] + v;
+            if constexpr (EDGE) b0[RS(0)] = fixed(0, ISA(0, 1)) ? b0[RS(0)] : x;
+            else b0[RS(0)] = x;
+            if constexpr ((PH & 1) == 0) {
+                if (ci != kOffPastBox) lds[(bC + (((PH >> 1) + 1) & 1)) * NT + tid] = cr;
+                cr = load_coarse((q >> 1) + 2);
+            }
+        }
         Three t1{}, t2, t3, t4, t5r{}, t5b{};
         if constexpr (!ZERO) t1 = near(bB0 + ((PH - 1) & 1), ISA(1, 0));
         t2 = near(bR1 + ((PH - 1) & 1), ISA(2, 1));
@@ -365,6 +422,12 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
 #undef ISA
     };
 
+    if constexpr (POST) {
+        const double v = load_coarse(zs >> 1);
+        cr = load_coarse((zs >> 1) + 1);
+        if (ci != kOffPastBox) lds[bC * NT + tid] = v;
+        lds_barrier();
+    }
     load(integral_constant<int, 0>(), zs);
     load(integral_constant<int, 1>(), zs + 1);
     for (int qb = zs;; qb += 8) {
@@ -373,7 +436,7 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
         const int q = qb + PH;                                                  \
         if (q >= zend) break;                                                   \
         load(integral_constant<int, (PH + 2) & 7>(), q + 2);                    \
-        if (edge_xy || (!perz && (q <= 4 || q > n2)))                           \
+        if (edge_xy || (!perz && (q <= 4 || q >= n2)))                          \
             step(integral_constant<int, PH>(), integral_constant<int, 1>(), q); \
         else step(integral_constant<int, PH>(), integral_constant<int, 0>(), q); \
         lds_barrier();                                                          \
@@ -394,7 +457,7 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
 }
 
 // The blocks of a level (as plan_sweep); nt = 0: beyond 32-bit offsets.
-static NSweep plan_nd_sweep(const NLev& L, bool zero, int kind) {
+static NSweep plan_nd_sweep(const NLev& L, const NLev& C, bool zero, int kind, bool post) {
     NSweep best;
     if (L.alloc * 8 > 0x7fffffffLL) return best;
     const int halo = (kind ? 5 : 4) - (zero ? 1 : 0), lead = ((halo + 1) & ~1) + 5, nm = L.n[0] / 2;
@@ -402,13 +465,14 @@ static NSweep plan_nd_sweep(const NLev& L, bool zero, int kind) {
     auto split = [](int cells, int pieces, int unit) { return (cells / unit + pieces - 1) / pieces * unit; };
     for (int px = 1; px <= nm; ++px) {
         const int XM = split(nm, px, 1);
-        if (XM < 8 && px > 1) break;
+        if (XM < 4 && px > 1) break;
         const int hm = XM == nm ? 0 : (halo + 1) / 2, RM = XM == nm ? nm + (L.per[0] ? 0 : 1) : XM + 2 * hm;
         if (RM > 768) continue;
         for (int py = 1; py <= L.n[1] / 2; ++py) {
             const int TY = split(L.n[1], py, 2);
             const bool span = TY == L.n[1];
-            const int hy = span ? 0 : halo, RY = span ? TY + (L.per[1] ? 0 : 1) : TY + 2 * hy, cols = RM * RY;
+            const int hy = span ? 0 : halo, RY = span ? TY + (L.per[1] ? 0 : 1) : TY + 2 * hy;
+            const int cols = std::max(RM * RY, post ? (RM + 1) * (RY / 2 + 3) : 0);
             if (cols > 768) continue;
             const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : 768;
             const int nbx = (nm + XM - 1) / XM, nby = (L.n[1] + TY - 1) / TY;
@@ -417,8 +481,8 @@ static NSweep plan_nd_sweep(const NLev& L, bool zero, int kind) {
                 const int ZC = split(L.n[2], pz, 2), nbz = (L.n[2] + ZC - 1) / ZC;
                 const long long blocks = (long long)nbx * nby * nbz, per_cu = (blocks + 255) / 256;
                 const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
-                const double c = (double)((per_cu + fit - 1) / fit) * (ZC + lead) *
-                                     std::max(1000.0, 300.0 + 130.0 * waves) + 1e-3 * (double)blocks;
+                const double c = (double)((per_cu + fit - 1) / fit) * (ZC + lead) * (550.0 + 115.0 * waves) +
+                                 1e-3 * (double)blocks;
                 if (c < cost) {
                     cost = c;
                     best.nt = nt;
@@ -432,15 +496,18 @@ static NSweep plan_nd_sweep(const NLev& L, bool zero, int kind) {
             }
         }
     }
+    best.cH = C.H;
+    best.cpl = C.H * (C.n[1] + 1);
+    best.ccs = (int)C.cs;
     return best;
 }
 
-template <bool ZERO, int KIND>
+template <bool ZERO, int KIND, bool POST>
 static hipError_t launch_nd_sweep(hipStream_t s, const NLev& L, const NSweep& P, const double* uin, double* uout,
-                                  const double* f, double* r, double* partials) {
+                                  const double* f, double* r, double* partials, const double* e) {
 #define BXMG_NSW(NT)                                                                                             \
-    hipLaunchKernelGGL((k_nd_sweep<NT, ZERO, KIND>), dim3(P.blocks), dim3(P.threads), 0, s, L, P, uin, uout, f, r, \
-                       partials)
+    hipLaunchKernelGGL((k_nd_sweep<NT, ZERO, KIND, POST>), dim3(P.blocks), dim3(P.threads), 0, s, L, P, uin, uout, f, \
+                       r, partials, e)
     if (P.nt == 256) BXMG_NSW(256);
     else if (P.nt == 512) BXMG_NSW(512);
     else BXMG_NSW(768);
@@ -937,8 +1004,8 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
     H->pre.resize(nl);
     H->post.resize(nl);
     for (size_t q = 0; q < end; ++q) {
-        H->pre[q] = plan_nd_sweep(H->L[q], q > 0, 1);
-        H->post[q] = plan_nd_sweep(H->L[q], false, q > 0 ? 0 : 2);
+        H->pre[q] = plan_nd_sweep(H->L[q], H->L[q + 1], q > 0, 1, false);
+        H->post[q] = plan_nd_sweep(H->L[q], H->L[q + 1], false, q > 0 ? 0 : 2, true);
         if (H->pre[q].nt) H->a[q].alloc(H->L[q].alloc);
         np = std::max(np, H->post[q].blocks);
     }
@@ -978,10 +1045,13 @@ static int vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double br
     const int kg = plane_depth(L, true, kKZ), kr = plane_depth(L, true, kKZr);
     const dim3 gb = plane_grid(L, true, kg);
     const bool stream = nu1 == 2 && nu2 == 2 && H.pre[l].nt > 0;
-    double* const u = stream ? H.a[l].p : H.u[l].p;  // what the coarse levels correct
+    double* const u = stream ? H.a[l].p : H.u[l].p;
     if (stream) {
-        if (l > 0) HIPCHK((launch_nd_sweep<true, 1>(s, L, H.pre[l], nullptr, u, H.f[l].p, H.r[l].p, nullptr)));
-        else HIPCHK((launch_nd_sweep<false, 1>(s, L, H.pre[l], H.u[l].p, u, H.f[l].p, H.r[l].p, nullptr)));
+        if (l > 0)
+            HIPCHK((launch_nd_sweep<true, 1, false>(s, L, H.pre[l], nullptr, u, H.f[l].p, H.r[l].p, nullptr, nullptr)));
+        else
+            HIPCHK((launch_nd_sweep<false, 1, false>(s, L, H.pre[l], H.u[l].p, u, H.f[l].p, H.r[l].p, nullptr,
+                                                     nullptr)));
     } else {
         for (int q = 0; q < nu1; ++q)
             for (int c = 0; c < 2; ++c)
@@ -994,12 +1064,15 @@ static int vcycle(NHier& H, size_t l, hipStream_t s, int nu1, int nu2, double br
     hipLaunchKernelGGL(k_nd_restrict, plane_grid(C, false, kc), dim3(kNB), 0, s, L, H.r[l].p, C, H.f[l + 1].p,
                        H.u[l + 1].p, kc);
     vcycle(H, l + 1, s, nu1, nu2, brtol);
-    hipLaunchKernelGGL(k_nd_prolong, gb, dim3(kNB), 0, s, C, H.u[l + 1].p, L, u, nu2 > 0 ? 1 : 0, kg);
     if (stream) {
-        if (l > 0) HIPCHK((launch_nd_sweep<false, 0>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, nullptr)));
-        else HIPCHK((launch_nd_sweep<false, 2>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, H.part.p)));
+        double* const e = H.u[l + 1].p;
+        if (l > 0)
+            HIPCHK((launch_nd_sweep<false, 0, true>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, nullptr, e)));
+        else
+            HIPCHK((launch_nd_sweep<false, 2, true>(s, L, H.post[l], u, H.u[l].p, H.f[l].p, nullptr, H.part.p, e)));
         return l > 0 ? 0 : H.post[l].blocks;
     }
+    hipLaunchKernelGGL(k_nd_prolong, gb, dim3(kNB), 0, s, C, H.u[l + 1].p, L, u, nu2 > 0 ? 1 : 0, kg);
     for (int q = 0; q < nu2; ++q)
         for (int c = 0; c < 2; ++c)
             hipLaunchKernelGGL(k_nd_gs, gb, dim3(kNB), 0, s, L, H.u[l].p, H.f[l].p, c, kg);

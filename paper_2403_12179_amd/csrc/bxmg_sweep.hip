@@ -65,7 +65,7 @@ namespace bxmg {
 // face); a thread carries one value of the next plane.  So the prolongation
 // costs 8 LDS reads a pair and no pass of its own: 256^3 FP64, sweeps and norms
 // 217 us with it, 197 without, and 58 the three launches that it took; 192^3
-// 104 against 85 + 46.
+// 87 against 85 + 34.
 // No ghost is read or written.
 // NT: threads per block (columns of a block, halo included, at most NT).
 // kSweepAdd: the result is added to acc (and its face ghosts refreshed)
