@@ -416,20 +416,20 @@ __global__ void __launch_bounds__(kBlock) k_fill_fab(T* __restrict__ data, const
 // source box sbox, source cell = dst cell + soff), components
 // [scomp, scomp+n) into [dcomp, dcomp+n).
 // Bound by the latency of hint, tag, boxes and value, one after the other:
-// 4 cells per thread, kBlock apart, with all their loads in flight before the
-// first store, and each XCD takes one contiguous run of the regions (208 x 176
+// kCopyCells = 4 per thread, kBlock apart, with all their loads in flight before
+// the first store, and each XCD takes one contiguous run of the regions (208 x 176
 // x 240 cells, 64^3 boxes into 32^3 ones with ghosts: 68 -> 52 us).  Ghost
 // fills (k_fill_fab) keep one cell: theirs are bound by the lines that their
 // short rows touch, and small ones by a block's own latency (4 cells make a
 // 48^3 fill 4.4 -> 6.7 us and a 256^3 one in 512 boxes 101 -> 125 us).
-constexpr int kCopyCells = 4;
-template <class T>
+template <class T, int kCopyCells>
 __global__ void __launch_bounds__(kBlock) k_copy_fab(T* __restrict__ dst, const FBox* __restrict__ dboxes,
                                                     const T* __restrict__ src, const FBox* __restrict__ sboxes,
                                                     const Tag* __restrict__ tags, int ntags, long long ncells,
                                                     int dcomp, int scomp, int ncomp, const int* __restrict__ hints) {
-    const unsigned nb = gridDim.x;  // a multiple of 8
-    const long long c0 = (long long)((blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3)) * kCopyCells;
+    const unsigned nb = gridDim.x;  // a multiple of 8 with more than one cell
+    const long long c0 = kCopyCells == 1 ? blockIdx.x
+                                         : (long long)((blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3)) * kCopyCells;
     long long s0[kCopyCells], d0[kCopyCells], scs[kCopyCells], dcs[kCopyCells];
     bool on[kCopyCells];
     auto place = [&](int q, long long g, const Tag& t) {
@@ -2418,18 +2418,28 @@ hipError_t launch_fill_rb(hipStream_t s, void* data, bool f32, const GhostCopy* 
     return hipGetLastError();
 }
 
+// Up to this many cells (a few rounds of blocks over the chip) one cell per
+// thread has the shorter chain: 64^3 4.1 us against 4.9, 96^3 5.5 against 6.8,
+// 128^3 10.3 against 10.5; 160^3 18.7 against 15.8.
+constexpr long long kCopyOne = 1LL << 21;
 hipError_t launch_copy_fab(hipStream_t s, bool f32, void* dst, const FBox* dboxes, const void* src,
                            const FBox* sboxes, const Tag* tags, int ntags, long long ncells, int dcomp, int scomp,
                            int ncomp, const int* hints) {
     if (ncells <= 0) return hipSuccess;
-    const long long per = 8LL * kBlock * kCopyCells;
-    const dim3 G((unsigned)((ncells + per - 1) / per * 8)), B(kBlock);
-    if (f32)
-        hipLaunchKernelGGL(k_copy_fab<float>, G, B, 0, s, (float*)dst, dboxes, (const float*)src, sboxes, tags, ntags,
-                           ncells, dcomp, scomp, ncomp, hints);
-    else
-        hipLaunchKernelGGL(k_copy_fab<double>, G, B, 0, s, (double*)dst, dboxes, (const double*)src, sboxes, tags,
-                           ntags, ncells, dcomp, scomp, ncomp, hints);
+    const bool four = ncells > kCopyOne;
+    const long long per = 8LL * kBlock * 4;
+    const dim3 G(four ? (unsigned)((ncells + per - 1) / per * 8) : nblk(ncells)), B(kBlock);
+#define BXMG_COPY(T, KC)                                                                                          \
+    hipLaunchKernelGGL((k_copy_fab<T, KC>), G, B, 0, s, (T*)dst, dboxes, (const T*)src, sboxes, tags, ntags, ncells, \
+                       dcomp, scomp, ncomp, hints)
+    if (f32) {
+        if (four) BXMG_COPY(float, 4);
+        else BXMG_COPY(float, 1);
+    } else {
+        if (four) BXMG_COPY(double, 4);
+        else BXMG_COPY(double, 1);
+    }
+#undef BXMG_COPY
     return hipGetLastError();
 }
 
