@@ -9,10 +9,11 @@ right-hand side i.i.d. uniform[-1, 1] (seed 2), inputs resident in HBM.
 value = fine-cell V-cycle updates per second = 256^3 * cycles / solve time.
 
 The JSON line also carries
-  roofline     : the level-0 Gauss-Seidel colour kernel (the dominant one),
-                 algorithmic bytes per launch / its mean duration from HIP
-                 events recorded around each of its launches in the timed
-                 steps, against the 8 TB/s HBM peak; traffic = HBM bytes per
+  roofline     : the level-0 smoothing launches (the dominant ones: two
+                 red-black sweeps with the residual after them, or with the
+                 prolongation before them), algorithmic bytes per launch /
+                 their mean duration from HIP events recorded around each
+                 launch of the first timed step, against the 8 TB/s HBM peak; traffic = HBM bytes per
                  launch from rocprofv3 counters (FETCH_SIZE + WRITE_SIZE,
                  scaled by the same counters on a copy of known size), when a
                  summary taken on the current kernel source is committed;
@@ -79,20 +80,24 @@ PEAK_GBPS = 8000.0
 # the sources that decide what the counted launches do: the kernels, and the
 # host code that lays out the levels and picks their tiles
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2403_12179_amd", "csrc", f)
-               for f in ("bxmg_kernels.hip", "bxmg_host.cpp", "bxmg_host.h")]
+               for f in ("bxmg_kernels.hip", "bxmg_sweep.hip", "bxmg_device.h", "bxmg_host.cpp", "bxmg_host.h")]
 COUNTERS = os.path.join(ROOT, "profiles", "counters_gs_level0_256c512.json")
-GS_KERNEL = "k_gs<double, 0>"
-GS_MATCH = "k_gs<double, 0"
+GS_KERNEL = "k_sweep<double>"
+GS_MATCH = "k_sweep<double"
 COPY_BYTES = 1 << 30
 
-# Compulsory bytes per fine cell per V(2,2) cycle, FP64 (s = 8 B), per level
-# l with N_l cells: 8 half-sweeps x 1.5 s N_l + residual/restriction
-# (2 + 1/8) s N_l + zeroing the coarse guess s N_l / 8 + prolongation
-# (2 + 1/8) s N_l = 16.375 s N_l; sum over levels 8/7 N_0; plus the level-0
-# convergence residual 2 s N_0.
+# Bytes per fine cell that a V(2,2) cycle of one launch per half-sweep moves at
+# least, FP64 (s = 8 B), per level l with N_l cells: 8 half-sweeps x 1.5 s N_l +
+# residual/restriction (2 + 1/8) s N_l + zeroing the coarse guess s N_l / 8 +
+# prolongation (2 + 1/8) s N_l = 16.375 s N_l; sum over levels 8/7 N_0; plus the
+# level-0 convergence residual 2 s N_0.  The streaming smoother moves fewer (a
+# launch reads u and f, reads or writes an eighth of them for the coarse level,
+# writes u); the model stays, so that effective GB/s compare across versions.
 BYTES_PER_CELL_CYCLE = 8.0 * (16.375 * 8.0 / 7.0 + 2.0)
-GS_BYTES_PER_CELL = 1.5 * 8.0  # one colour: read other colour, rhs of this colour, write this colour
-
+GS_BYTES_PER_CELL = 3.125 * 8.0
+# ... and one colour of a level that is not streamed (buffer addressing off):
+# read the other colour and this colour's rhs, write this colour
+HALF_BYTES_PER_CELL = 1.5 * 8.0
 
 def src_sha():
     h = hashlib.sha256()
@@ -119,7 +124,8 @@ def make_problem(bx, W):
 
 
 def shape_key(z, r, ly):
-    return "%d,%d,%d" % (z, r, ly)
+    # (the streamed launches do not depend on the tile knobs)
+    return "streamed" if r else "%d,%d,%d" % (z, r, ly)
 
 
 def traffic_from_counters(key):
@@ -1048,7 +1054,7 @@ def main():
         mean_cycles = sum(cycles) / len(cycles)
         value = N ** 3 * mean_cycles / (ms_per_step / 1000.0)
         gs_avg_ms = gs_ms.value / max(launches.value, 1)
-        gs_bytes = GS_BYTES_PER_CELL * N ** 3
+        gs_bytes = (GS_BYTES_PER_CELL if r else HALF_BYTES_PER_CELL) * N ** 3
         achieved = gs_bytes / (gs_avg_ms / 1000.0) / 1e9
         key = shape_key(z, r, ly)
         traffic = traffic_from_counters(key)
@@ -1074,7 +1080,8 @@ def main():
             "autotuned_launch_shape": tuned,
             "final_rel_resid_inf": res.rel_resid_inf,
             "boxes_kept": boxes_kept,
-            "roofline": {"bound": "hbm", "kernel": GS_KERNEL + " (level 0, one colour)", "achieved": achieved,
+            "roofline": {"bound": "hbm", "kernel": GS_KERNEL + " (level 0, two sweeps and a transfer)" if r
+                         else "k_gs<double, 0> (level 0, one colour)", "achieved": achieved,
                          "peak": PEAK_GBPS, "unit": "GB/s", "frac": achieved / PEAK_GBPS, "traffic": traffic,
                          "algorithmic_bytes_per_launch": gs_bytes, "avg_launch_ms": gs_avg_ms,
                          "launches_timed": launches.value, "launch_shape": key},

@@ -331,8 +331,10 @@ bxmg_status bxmg_autotune(bxmg_ctx ctx, const bxmg_solve_params* params, bxmg_mu
 /* ---------------------------------------------------------- profiling --- */
 /* Kernel timing with HIP events recorded on the context's stream around
  * every launch of one stage on the finest level (level 0) during solves:
- *   0 red-black Gauss-Seidel colour, 1 convergence residual + norms,
- *   2 residual + restriction, 3 prolongation + correction,
+ *   0 red-black Gauss-Seidel (a colour, or on a streamed level two sweeps
+ *   with the residual and restriction, or with the prolongation and the
+ *   norms, which are then no stages of their own), 1 convergence residual +
+ *   norms, 2 residual + restriction, 3 prolongation + correction,
  *   4 ghost fills of the solution, 5 the fused coarse cycle (whichever
  *   level it starts at); -1 switches timing off (default).
  * Times accumulate until read; the events add a few microseconds per timed

@@ -117,6 +117,9 @@ struct GeoPlan {
     DevBuf<int> cbox0;
     DevBuf<Tile> tface[3];
     int ntface[3] = {0, 0, 0};
+    // sweeps before and after the coarse levels, by level and share of the chip
+    // (a power of two of compute units)
+    std::map<std::pair<int, int>, std::array<SweepPlan, 2>> sweeps;
     Grid grid0() const {
         return merged0 ? Grid{vrb0.p, t0.p, nt0, 0, nullptr, 0, 0}
                        : Grid{rb0.p, t0.p, nt0, L[0].push ? 1 : 0, nullptr, 0, res0};
@@ -518,7 +521,7 @@ std::vector<int2> deal_blocks(const std::vector<SweepArgs>& jobs) {
 // range and keep one launch per half-sweep.  64 periodic problems of 32^3 to
 // 128^3 (52 million cells): the level-0 sweeps, transfers, zeroing and the
 // update of the iterate took 8 x 91 + 555 us a cycle and take 219 + 455; the
-// batch went from 23.0 to 15.5 ms.  With blocks in problem order and an equal
+// batch went from 23.0 to 14.9 ms.  With blocks in problem order and an equal
 // share of the chip planned for every problem the sweeps took a quarter more:
 // a launch ends with its longest blocks, and the largest problems set it.
 void plan_streams(bxmg_batch_s* b) {
@@ -531,25 +534,25 @@ void plan_streams(bxmg_batch_s* b) {
         if (!B.res || !b->lev[l + 1].res || !B.push || !B.one_box) continue;
         // (a level below that is not streamed is zeroed by the residual launch above it)
         if (l + 1 < b->lmax && !b->lev[l + 1].stream) continue;
-        std::map<const GeoPlan*, std::array<SweepPlan, 2>> plans;
         std::vector<SweepArgs> job[2];
         int threads[2] = {0, 0};
         bool ok = true;
         for (int s : b->members) {
             const Problem& p = *b->slots[s];
-            const GeoPlan& G = *p.plan;
+            GeoPlan& G = *p.plan;
             if (l >= G.cs) continue;
             if (G.L[l + 1].rb.size() != 1) { ok = false; break; }
-            auto it = plans.find(&G);
-            if (it == plans.end()) {
-                // the problem's share of the chip
-                const int cus = std::max(1, (int)std::lround(256.0 * (double)G.dom.cells() / cells));
+            // the problem's share of the chip, as a power of two so that its plans
+            // outlive a change of the members
+            const int cus = 1 << std::max(0, (int)std::lround(std::log2(256.0 * (double)G.dom.cells() / cells)));
+            auto it = G.sweeps.find({l, cus});
+            if (it == G.sweeps.end()) {
                 std::array<SweepPlan, 2> P;
                 for (int k = 0; k < 2; ++k)
                     P[k] = plan_sweep_level(G.L[l].rb[0], G.L[l + 1].rb[0], G.per,
                                             k == 0 ? kSweepRestrict : l ? kSweepPlain : kSweepAdd, k == 0, true, 0, cus,
                                             kSweepJobThreads);
-                it = plans.emplace(&G, P).first;
+                it = G.sweeps.emplace(std::make_pair(l, cus), P).first;
             }
             for (int k = 0; k < 2; ++k) {
                 const SweepPlan& P = it->second[k];

@@ -201,6 +201,10 @@ static void plan_streams(Hier* H, long long& max_tiles) {
         bool ok = true;
         for (int kind = 0; kind < 4; ++kind)
             for (int zero = 0; zero < 2; ++zero) {
+                // from zero: before the coarse levels only (FP32 and lower levels
+                // always); the norms and the addition on level 0
+                if (kind == kSweepRestrict ? !zero && (f32 || l > 0) : zero != 0) continue;
+                if ((kind == kSweepNorm && (f32 || l > 0)) || (kind == kSweepAdd && (!f32 || l > 0))) continue;
                 SweepPlan& P = L.sweep[kind][zero];
                 P = plan_sweep_level(L.rb[0], C.rb[0], H->per, kind, zero != 0, f32, mode);
                 ok = ok && P.nt > 0;
