@@ -248,7 +248,11 @@ __global__ void __launch_bounds__(kCB) k_fine_resid(CGeo g, const FRB* __restric
     block_norms(mx, s2, bad, partials + 3 * (long long)blk);
 }
 
-// Fine cells += trilinear interpolation of the coarse correction Ec.
+// Fine cells += trilinear interpolation of the coarse correction Ec.  A slot's
+// cells (2I + 1, 2I + 2) lie between the same two coarse columns, and two fine
+// planes between the same two coarse ones: 4 coarse loads per two planes of a
+// pair instead of 32, with the pair's own values of all planes loaded first.
+// 256^3 fine cells: 144 -> 68 us, 57 of them u in and out at the copy rate.
 __global__ void __launch_bounds__(kCB) k_fine_prolong(CGeo g, const FRB* __restrict__ fb, double* __restrict__ u,
                                                       const double* __restrict__ Ec) {
     const uint3 bk = xcd_block();
@@ -259,20 +263,51 @@ __global__ void __launch_bounds__(kCB) k_fine_prolong(CGeo g, const FRB* __restr
     const int ts = t % ns, j = B.lo[1] + t / ns;
     const int k0 = B.lo[2] + bk.y * kKZs, k1 = min(k0 + kKZs - 1, B.hi[2]);
     const int J = j >> 1, sj = (j & 1) ? 1 : -1;
-    for (int k = k0; k <= k1; ++k) {
-        const int K = k >> 1, sk = (k & 1) ? 1 : -1;
+    const int i0 = B.glo[0] + 2 * ts;  // odd: boxes are whole coarse cells
+    const bool on0 = i0 >= B.lo[0], on1 = i0 + 1 <= B.hi[0];
+    const int I = i0 >> 1;
+    double v[kKZs][2];
+#pragma unroll
+    for (int q = 0; q < kKZs; ++q) {
+        const int k = min(k0 + q, k1);
+        v[q][0] = on0 ? u[frb_at(B, i0, j, k)] : 0.0;
+        v[q][1] = on1 ? u[frb_at(B, i0 + 1, j, k)] : 0.0;
+    }
+    // coarse planes w and w + 1 of the pair's columns and rows: [column][row]
+    double lo[2][2], hi[2][2];
+    auto plane = [&](int K, double (&c)[2][2]) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            c[a][0] = Ec[ridx(g, I + a, J, K)];
+            c[a][1] = Ec[ridx(g, I + a, J + sj, K)];
+        }
+    };
+    int w = (k0 - 1) >> 1;
+    plane(w, lo);
+    plane(w + 1, hi);
+#pragma unroll
+    for (int q = 0; q < kKZs; ++q) {
+        const int k = k0 + q;
+        if (k > k1) break;
+        if (((k - 1) >> 1) != w) {
+            ++w;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) lo[a][b] = hi[a][b];
+            plane(w + 1, hi);
+        }
+        const bool odd = (k & 1) != 0;  // its parent is plane w, else w + 1
+#pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int i = B.glo[0] + 2 * ts + e;
-            if (i < B.lo[0] || i > B.hi[0]) continue;
-            const int I = i >> 1, si = (i & 1) ? 1 : -1;
-            const double c000 = Ec[ridx(g, I, J, K)], c100 = Ec[ridx(g, I + si, J, K)];
-            const double c010 = Ec[ridx(g, I, J + sj, K)], c001 = Ec[ridx(g, I, J, K + sk)];
-            const double c110 = Ec[ridx(g, I + si, J + sj, K)], c101 = Ec[ridx(g, I + si, J, K + sk)];
-            const double c011 = Ec[ridx(g, I, J + sj, K + sk)], c111 = Ec[ridx(g, I + si, J + sj, K + sk)];
-            const double v = (((27.0 * c000 + 9.0 * ((c100 + c010) + c001)) + 3.0 * ((c110 + c101) + c011)) + c111) *
-                             (1.0 / 64.0);
-            const long long c = frb_at(B, i, j, k);
-            u[c] = u[c] + v;
+            if (!(e ? on1 : on0)) continue;
+            const double c000 = odd ? lo[e][0] : hi[e][0], c100 = odd ? lo[1 - e][0] : hi[1 - e][0];
+            const double c010 = odd ? lo[e][1] : hi[e][1], c001 = odd ? hi[e][0] : lo[e][0];
+            const double c110 = odd ? lo[1 - e][1] : hi[1 - e][1], c101 = odd ? hi[1 - e][0] : lo[1 - e][0];
+            const double c011 = odd ? hi[e][1] : lo[e][1], c111 = odd ? hi[1 - e][1] : lo[1 - e][1];
+            u[frb_at(B, i0 + e, j, k)] =
+                v[q][e] + (((27.0 * c000 + 9.0 * ((c100 + c010) + c001)) + 3.0 * ((c110 + c101) + c011)) + c111) *
+                              (1.0 / 64.0);
         }
     }
 }
