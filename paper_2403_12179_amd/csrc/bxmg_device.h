@@ -6,7 +6,11 @@ namespace bxmg {
 
 // Raw-buffer resources (a base, a size in bytes, 32-bit lane offsets).
 constexpr int kBufferDword3 = 0x00020000;  // raw buffer, gfx9 data format
-// A byte offset beyond every box resource (their sizes stay below 2^31 bytes).
+// A lane offset beyond every box resource (their sizes stay below 2^31 bytes):
+// the access is dropped.  The hardware compares it with the resource's size
+// less the scalar offset, so that must not be negative: a plane below the box
+// would take away what is left up to 2^31, and in the largest boxes the
+// access would land in their last planes.
 constexpr int kOffPastBox = (int)0x80000000u;
 
 // a / b for a loop-invariant b whose reciprocal is held in two parts,

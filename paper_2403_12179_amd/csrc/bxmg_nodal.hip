@@ -393,20 +393,22 @@ __global__ void __launch_bounds__(NT) k_nd_sweep(NLev L, NSweep A, const double*
         {  // plane q-4 is final
             const int pz = q - 4;
             const bool mine = pz >= z0 && (pz < zlim || (top && pz == n2));
-            Raw<double>::st(Ro, mine ? w : kOffPastBox, pz * pl, r3[RS(4)]);
-            Raw<double>::st(Ro, mine ? w : kOffPastBox, pz * pl + co, b4[RS(4)]);
+            const int zo = mine ? pz * pl : 0;  // (see kOffPastBox)
+            Raw<double>::st(Ro, mine ? w : kOffPastBox, zo, r3[RS(4)]);
+            Raw<double>::st(Ro, mine ? w : kOffPastBox, zo + co, b4[RS(4)]);
         }
         if constexpr (RES) {  // the residual of plane q-5
             const int pz = q - 5;
-            const bool mine = own && pz >= z0 && pz < zlim && (perz || pz > 0);
+            const bool here = pz >= z0 && pz < zlim && (perz || pz > 0), mine = own && here;
+            const int zo = here ? pz * pl : 0;
             const bool m0 = mine && !(ISA(5, 0) ? fixA : fixB), m1 = mine && !(ISA(5, 1) ? fixA : fixB);
             const double s0 = ((b4[RS(5)] + t5r.x) + (t5r.d + t5r.u)) + (b4[RS(6)] + b4[RS(4)]);
             const double s1 = ((r3[RS(5)] + t5b.x) + (t5b.d + t5b.u)) + (r3[RS(6)] + r3[RS(4)]);
             const double v0 = f0[RS(5)] - (s0 - 6.0 * r3[RS(5)]) * ih2;
             const double v1 = f1[RS(5)] - (s1 - 6.0 * b4[RS(5)]) * ih2;
             if constexpr (KIND == 1) {
-                Raw<double>::st(Rr, m0 ? v : kOffPastBox, pz * pl, v0);
-                Raw<double>::st(Rr, m1 ? v : kOffPastBox, pz * pl + co, v1);
+                Raw<double>::st(Rr, m0 ? v : kOffPastBox, zo, v0);
+                Raw<double>::st(Rr, m1 ? v : kOffPastBox, zo + co, v1);
             } else {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {  // (without branches: 0 adds nothing)

@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         }
         if constexpr (ADD) {
             const bool mine = q - 4 >= z0 && q - 4 < zlim;
-            const int zd = (q - 3) * A.GH * 8;
+            const int zd = mine ? (q - 3) * A.GH * 8 : 0;
             a0[PH & 3] = Raw<double>::ld(Ra, !mine ? kOffPastBox : (PH & 1) ? aB : aA, zd);
             a1[PH & 3] = Raw<double>::ld(Ra, !mine ? kOffPastBox : (PH & 1) ? aA : aB, zd + A.cs * 8);
         }
@@ -444,13 +444,13 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
         {  // plane q-4 is final
             const int p = q - 4;
             const bool mine = p >= z0 && p < zlim;
-            const int zo = (p + 1) * pl;
+            const int zo = mine ? (p + 1) * pl : 0;  // (see kOffPastBox)
             const int vr = (PH & 1) ? vB : vA, vb = (PH & 1) ? vA : vB;
             if constexpr (!ADD) {  // (stores past the box are dropped)
                 Raw<T>::st(Ro, own && mine ? vr : kOffPastBox, zo, r3[RS(4)]);
                 Raw<T>::st(Ro, own && mine ? vb : kOffPastBox, zo + co, b4[RS(4)]);
             } else {
-                const int cd = A.cs * 8, zd = (p + 1) * A.GH * 8;
+                const int cd = A.cs * 8, zd = mine ? (p + 1) * A.GH * 8 : 0;
                 const double x0 = a0[PH & 3] + (double)r3[RS(4)], x1 = a1[PH & 3] + (double)b4[RS(4)];
                 const int ar = (PH & 1) ? aB : aA, ab = (PH & 1) ? aA : aB;
                 Raw<double>::st(Ra, mine ? ar : kOffPastBox, zd, x0);
@@ -665,12 +665,13 @@ __global__ void __launch_bounds__(kDirThreads, 4)
             if constexpr (MODE != 0) nk[c] = near(bK + 2 * (1 - c) + s1, isA);
         }
         const bool mine = q >= z0 && q < zlim;
+        const int zn = mine ? q * pl + pl : 0;  // (see kOffPastBox)
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const bool isA = ((c + PH) & 1) == 0;
             pv[c][PH] = (double)ev[c][PH] + bs * po[c][PH];
             lds[(bP + 2 * c + s0) * NT + tid] = pv[c][PH];
-            Raw<double>::st(Rn, mine ? (isA ? wA : wB) : kOffPastBox, q * pl + pl + c * co, pv[c][PH]);
+            Raw<double>::st(Rn, mine ? (isA ? wA : wB) : kOffPastBox, zn + c * co, pv[c][PH]);
             if constexpr (MODE != 0) {
                 lds[(bK + 2 * c + s0) * NT + tid] = be[c][PH];
                 double lo = be[1 - c][P1], hi = be[c][PH];
@@ -680,6 +681,7 @@ __global__ void __launch_bounds__(kDirThreads, 4)
             }
         }
         const bool mine1 = q - 1 >= z0 && q - 1 < zlim;
+        const int zq = mine1 ? q * pl : 0;
         const double kin = MODE ? harm(be[0][P1], be[1][P1]) : 1.0;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -700,7 +702,7 @@ __global__ void __launch_bounds__(kDirThreads, 4)
             }
             sb = sb + dg;
             const double qv = (su - sb * v) * ih2;
-            Raw<double>::st(Rq, mine1 ? (isA ? wA : wB) : kOffPastBox, q * pl + c * co, qv);
+            Raw<double>::st(Rq, mine1 ? (isA ? wA : wB) : kOffPastBox, zq + c * co, qv);
             pq.dot(own && mine1 ? v : 0.0, own && mine1 ? qv : 0.0);
         }
     };
