@@ -1536,6 +1536,7 @@ void hier_vcycle_from_zero(bxmg_ctx ctx, Hier* H, const bxmg_solve_params& P) {
     R.zero_top = true;
     if (!R.streams(0)) HIPCHK(launch_zero<double>(R.s, H->u64[0]->p, L0.nelem));
     vcycle<double>(R, 0);
+    if (ctx->prof.n) HIPCHK(hipStreamSynchronize(R.s));
     ctx->prof.harvest();
 }
 
