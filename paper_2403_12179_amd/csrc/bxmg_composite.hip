@@ -42,6 +42,7 @@
 // that every coarse cell a ghost or an interpolation reads is a domain cell.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -507,16 +508,19 @@ static unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) /
 struct Comp {
     bxmg_ctx ctx = nullptr;
     // the layout this state was built for: domain, boundaries, fine boxes
-    // (the coarse boxes only matter to the loads and stores of a solve)
+    // (the coarse boxes only matter to the loads and stores of a solve), and
+    // the context's launch shapes, which its hierarchy was built with
     Box dom{};
     int bc[3] = {0, 0, 0};
     std::vector<Box> fine;
     double h0 = 0.0;
+    std::array<int, 5> shape{};
+    static std::array<int, 5> shape_of(bxmg_ctx c) { return {c->zc, c->zc_planes, c->res, c->ly_cap, c->merge}; }
     bool fits(const bxmg_ba_s* cba, const bxmg_ba_s* fba, double h) const {
         auto same = [](const Box& a, const Box& b) {
             return std::memcmp(a.lo, b.lo, sizeof a.lo) == 0 && std::memcmp(a.hi, b.hi, sizeof a.hi) == 0;
         };
-        return h == h0 && same(dom, cba->dom) && std::memcmp(bc, cba->bc, sizeof bc) == 0 &&
+        return h == h0 && shape == shape_of(ctx) && same(dom, cba->dom) && std::memcmp(bc, cba->bc, sizeof bc) == 0 &&
                std::equal(fine.begin(), fine.end(), fba->boxes.begin(), fba->boxes.end(), same);
     }
     bxmg_boxarray one = nullptr;                                           // one box over the coarse domain
@@ -608,6 +612,7 @@ static std::unique_ptr<Comp> build(bxmg_ctx ctx, const bxmg_ba_s* cba, const bxm
     std::memcpy(c->bc, cba->bc, sizeof c->bc);
     c->fine = fba->boxes;
     c->h0 = h0;
+    c->shape = Comp::shape_of(ctx);
     const Box& D = cba->dom;
     const int lohi[6] = {D.lo[0], D.lo[1], D.lo[2], D.hi[0], D.hi[1], D.hi[2]};
     if (bxmg_define_boxarray_list(D.lo, D.hi, cba->bc, 1, lohi, &c->one) != BXMG_OK)
@@ -781,8 +786,8 @@ static std::unique_ptr<Comp> build(bxmg_ctx ctx, const bxmg_ba_s* cba, const bxm
     return c;
 }
 
-// The last layout used.  It is recognised by its boxes, not by the BoxArray
-// handles: a solve on other handles of the same layout would else spend 65 ms
+// The last layout used.  It is recognised by what it was built from, not by
+// the BoxArray handles: a solve on other handles of the same layout would else spend 65 ms
 // (256^3 + 256^3 cells) building lists, maps and the hierarchy, against 19 ms
 // of kernels (88 -> 19 ms per solve).
 struct Cache {
