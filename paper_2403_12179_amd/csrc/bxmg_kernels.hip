@@ -414,22 +414,47 @@ __global__ void __launch_bounds__(kBlock) k_fill_fab(T* __restrict__ data, const
 
 // ParallelCopy: region tags between two MultiFabs (destination box dbox,
 // source box sbox, source cell = dst cell + soff), components
-// [scomp, scomp+n) into [dcomp, dcomp+n).
-// Bound by the latency of hint, tag, boxes and value, one after the other:
-// kCopyCells = 4 per thread, kBlock apart, with all their loads in flight before
-// the first store, and each XCD takes one contiguous run of the regions (208 x 176
-// x 240 cells, 64^3 boxes into 32^3 ones with ghosts: 68 -> 52 us).  Ghost
-// fills (k_fill_fab) keep one cell: theirs are bound by the lines that their
-// short rows touch, and small ones by a block's own latency (4 cells make a
-// 48^3 fill 4.4 -> 6.7 us and a 256^3 one in 512 boxes 101 -> 125 us).
-template <class T, int kCopyCells>
+// [scomp, scomp+n) into [dcomp, dcomp+n).  One cell per thread.
+template <class T>
 __global__ void __launch_bounds__(kBlock) k_copy_fab(T* __restrict__ dst, const FBox* __restrict__ dboxes,
                                                     const T* __restrict__ src, const FBox* __restrict__ sboxes,
                                                     const Tag* __restrict__ tags, int ntags, long long ncells,
                                                     int dcomp, int scomp, int ncomp, const int* __restrict__ hints) {
-    const unsigned nb = gridDim.x;  // a multiple of 8 with more than one cell
-    const long long c0 = kCopyCells == 1 ? blockIdx.x
-                                         : (long long)((blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3)) * kCopyCells;
+    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    auto cell = [&](const Tag& t) {
+        int x, y, z;
+        tag_xyz(t, g - t.prefix, x, y, z);
+        const int di = t.dlo[0] + x, dj = t.dlo[1] + y, dk = t.dlo[2] + z;
+        const FBox sb = sboxes[t.sbox], db = dboxes[t.dbox];
+        const long long s0 = fab_idx(sb, di + t.soff[0], dj + t.soff[1], dk + t.soff[2]), d0 = fab_idx(db, di, dj, dk);
+        for (int n = 0; n < ncomp; ++n) dst[d0 + (dcomp + n) * db.cs] = src[s0 + (scomp + n) * sb.cs];
+    };
+    if (hints && hints[blockIdx.x] == hints[blockIdx.x + 1]) {
+        const Tag t = tags[hints[blockIdx.x]];
+        if (g < ncells) cell(t);
+        return;
+    }
+    if (g >= ncells) return;
+    const int b = blockIdx.x;
+    cell(tags[find_tag(tags, hints ? hints[b] : 0, hints ? hints[b + 1] : ntags - 1, g)]);
+}
+
+// The same for large copies of few values per cell (launch_copy_fab).  They
+// are bound by the latency of hint, tag, boxes and value, one after the other:
+// so kCopyCells per thread, kBlock apart, with all their loads in flight before
+// the first store, and each XCD takes one contiguous run of the regions (208 x
+// 176 x 240 cells, 64^3 boxes into 32^3 ones with ghosts: 68 -> 52 us).  Ghost
+// fills (k_fill_fab) keep one cell: theirs are bound by the lines that their
+// short rows touch, and small ones by a block's own latency (4 cells make a
+// 48^3 fill 4.4 -> 6.7 us and a 256^3 one in 512 boxes 101 -> 125 us).
+template <class T, int kCopyCells>
+__global__ void __launch_bounds__(kBlock) k_copy_fab_cells(T* __restrict__ dst, const FBox* __restrict__ dboxes,
+                                                          const T* __restrict__ src, const FBox* __restrict__ sboxes,
+                                                          const Tag* __restrict__ tags, int ntags, long long ncells,
+                                                          int dcomp, int scomp, int ncomp,
+                                                          const int* __restrict__ hints) {
+    const unsigned nb = gridDim.x;  // a multiple of 8
+    const long long c0 = (long long)((blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3)) * kCopyCells;
     long long s0[kCopyCells], d0[kCopyCells], scs[kCopyCells], dcs[kCopyCells];
     bool on[kCopyCells];
     auto place = [&](int q, long long g, const Tag& t) {
@@ -2418,26 +2443,39 @@ hipError_t launch_fill_rb(hipStream_t s, void* data, bool f32, const GhostCopy* 
     return hipGetLastError();
 }
 
-// Up to this many cells (a few rounds of blocks over the chip) one cell per
-// thread has the shorter chain: 64^3 4.1 us against 4.9, 96^3 5.5 against 6.8,
-// 128^3 10.3 against 10.5; 160^3 18.7 against 15.8.
-constexpr long long kCopyOne = 1LL << 21;
+// Cells per thread of a copy.  Timed on 230 draws of 0.4 to 50 million cells
+// (boxes of 16 to 64 cells into others, 0 to 3 ghosts, 1 to 8 components, both
+// types), the time with one cell per thread over that with several:
+//                                          2 cells         4 cells
+//   up to 2^21 cells                       0.80 .. 1.36    0.73 .. 1.28
+//   up to 2^23, a cell of at most 8 B      1.12 .. 1.45    1.00 .. 1.59
+//   beyond,     a cell of at most 8 B      1.08 .. 1.47    1.11 .. 1.54
+//   beyond 2^21, a cell of 9 to 24 B       0.98 .. 1.65    0.93 .. 1.35
+//   beyond 2^21, more                      0.85 .. 1.25    0.80 .. 1.13
+// Few cells do not fill the chip with several per thread; a cell of many
+// values has several loads in flight by itself.
+static int copy_cells(long long ncells, size_t cell_bytes) {
+    if (ncells <= 1LL << 21 || cell_bytes > 24) return 1;
+    return ncells > 1LL << 23 && cell_bytes <= 8 ? 4 : 2;
+}
 hipError_t launch_copy_fab(hipStream_t s, bool f32, void* dst, const FBox* dboxes, const void* src,
                            const FBox* sboxes, const Tag* tags, int ntags, long long ncells, int dcomp, int scomp,
                            int ncomp, const int* hints) {
     if (ncells <= 0) return hipSuccess;
-    const bool four = ncells > kCopyOne;
-    const long long per = 8LL * kBlock * 4;
-    const dim3 G(four ? (unsigned)((ncells + per - 1) / per * 8) : nblk(ncells)), B(kBlock);
-#define BXMG_COPY(T, KC)                                                                                          \
-    hipLaunchKernelGGL((k_copy_fab<T, KC>), G, B, 0, s, (T*)dst, dboxes, (const T*)src, sboxes, tags, ntags, ncells, \
-                       dcomp, scomp, ncomp, hints)
+    const int kc = copy_cells(ncells, (size_t)ncomp * (f32 ? 4 : 8));
+    const long long per = 8LL * kBlock * kc;
+    const dim3 G(kc > 1 ? (unsigned)((ncells + per - 1) / per * 8) : nblk(ncells)), B(kBlock);
+#define BXMG_COPY(T, ...)                                                                                          \
+    hipLaunchKernelGGL((__VA_ARGS__), G, B, 0, s, (T*)dst, dboxes, (const T*)src, sboxes, tags, ntags, ncells, dcomp, \
+                       scomp, ncomp, hints)
     if (f32) {
-        if (four) BXMG_COPY(float, 4);
-        else BXMG_COPY(float, 1);
+        if (kc == 4) BXMG_COPY(float, k_copy_fab_cells<float, 4>);
+        else if (kc == 2) BXMG_COPY(float, k_copy_fab_cells<float, 2>);
+        else BXMG_COPY(float, k_copy_fab<float>);
     } else {
-        if (four) BXMG_COPY(double, 4);
-        else BXMG_COPY(double, 1);
+        if (kc == 4) BXMG_COPY(double, k_copy_fab_cells<double, 4>);
+        else if (kc == 2) BXMG_COPY(double, k_copy_fab_cells<double, 2>);
+        else BXMG_COPY(double, k_copy_fab<double>);
     }
 #undef BXMG_COPY
     return hipGetLastError();
