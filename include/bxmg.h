@@ -331,12 +331,13 @@ bxmg_status bxmg_autotune(bxmg_ctx ctx, const bxmg_solve_params* params, bxmg_mu
 /* ---------------------------------------------------------- profiling --- */
 /* Kernel timing with HIP events recorded on the context's stream around
  * every launch of one stage on the finest level (level 0) during solves:
- *   0 red-black Gauss-Seidel (a colour, or on a streamed level two sweeps
- *   with the residual and restriction, or with the prolongation and the
- *   norms, which are then no stages of their own), 1 convergence residual +
- *   norms, 2 residual + restriction, 3 prolongation + correction,
- *   4 ghost fills of the solution, 5 the fused coarse cycle (whichever
- *   level it starts at); -1 switches timing off (default).
+ *   0 red-black Gauss-Seidel (a colour, or where the level is streamed two
+ *   sweeps with the residual and restriction, or with the prolongation and
+ *   the norms), 1 convergence residual + norms, 2 residual + restriction,
+ *   3 prolongation + correction, 4 ghost fills of the solution, 5 the fused
+ *   coarse cycle (whichever level it starts at); -1 switches timing off
+ *   (default).  While 1, 2 or 3 is timed, level 0 is not streamed, so that
+ *   they are launches of their own (the results are the same bits).
  * Times accumulate until read; the events add a few microseconds per timed
  * launch to the stream. */
 bxmg_status bxmg_profile_stage(bxmg_ctx ctx, int32_t stage);

@@ -453,6 +453,8 @@ static CoarseCycle<T> coarse_desc(Hier* H, int nu1, int nu2, int prolong, double
 
 namespace {
 
+enum { kStageGS = 0, kStageResid = 1, kStageRestrict = 2, kStageProlong = 3, kStageFill = 4, kStageCoarse = 5 };
+
 struct Run {
     Hier* H;
     hipStream_t s;
@@ -474,8 +476,12 @@ struct Run {
     double* stream_add = nullptr;  // ... or add the FP32 result to this instead of storing it
     int streamed = 0;
     bool zero_top = false;  // the V-cycle starts from level 0 = 0
-    // whether level l runs the streaming smoother (two sweeps each way)
-    bool streams(size_t l) const { return H->L[l]->stream && nu1 == 2 && nu2 == 2; }
+    // whether level l runs the streaming smoother (two sweeps each way); not
+    // level 0 while a stage is timed that the smoother takes in
+    bool streams(size_t l) const {
+        const bool timed = l == 0 && prof && prof->stage >= kStageResid && prof->stage <= kStageProlong;
+        return H->L[l]->stream && nu1 == 2 && nu2 == 2 && !timed;
+    }
     Grid grid(const Grid& g) const {
         Grid r = g;
         r.active = active;
@@ -485,8 +491,6 @@ struct Run {
     void pre(size_t l, int stage) { if (prof && prof->stage == stage && l == 0) prof->mark(s); }
     void post(size_t l, int stage) { if (prof && prof->stage == stage && l == 0) prof->mark(s); }
 };
-
-enum { kStageGS = 0, kStageResid = 1, kStageRestrict = 2, kStageProlong = 3, kStageFill = 4, kStageCoarse = 5 };
 
 template <class T>
 void fill(Run& R, size_t l, T* data, const GhostList& g) {
