@@ -188,8 +188,6 @@ static void upload_tiles(const TileSet& t, DevBuf<Tile>& buf, int& n) {
 // coefficient in FP32 only, as its FP64 form would not fit the registers.
 static void plan_streams(Hier* H, long long& max_tiles) {
     const size_t nl = H->L.size();
-    H->a64.resize(nl);
-    H->a32.resize(nl);
     const size_t end = H->coarse_start >= 0 ? (size_t)H->coarse_start : nl - 1;
     const bool f32 = H->precision == 1;
     for (size_t l = 0; l < end && (!H->var || f32); ++l) {
@@ -210,19 +208,63 @@ static void plan_streams(Hier* H, long long& max_tiles) {
                 ok = ok && P.nt > 0;
                 max_tiles = std::max<long long>(max_tiles, P.blocks);
             }
-        if (!ok) continue;
-        L.stream = true;
-        if (f32) {
-            H->a32[l] = std::make_unique<DevBuf<float>>();
-            H->a32[l]->alloc(L.nelem);
-            HIPCHK(hipMemset(H->a32[l]->p, 0, L.nelem * 4));
-        } else {
-            H->a64[l] = std::make_unique<DevBuf<double>>();
-            H->a64[l]->alloc(L.nelem);
-            HIPCHK(hipMemset(H->a64[l]->p, 0, L.nelem * 8));
-        }
-        H->bytes += (f32 ? 4 : 8) * (size_t)L.nelem;
+        L.stream = ok;
     }
+}
+
+// The streamed levels' second arrays, after everything that a solve cannot do
+// without: a level whose array finds no room runs one launch per half-sweep.
+static void alloc_streams(Hier* H) {
+    const size_t nl = H->L.size();
+    H->a64.resize(nl);
+    H->a32.resize(nl);
+    for (size_t l = 0; l < nl; ++l) {
+        Level& L = *H->L[l];
+        if (!L.stream) continue;
+        try {
+            if (H->precision == 1) {
+                H->a32[l] = std::make_unique<DevBuf<float>>();
+                H->a32[l]->alloc(L.nelem);
+                HIPCHK(hipMemset(H->a32[l]->p, 0, L.nelem * 4));
+            } else {
+                H->a64[l] = std::make_unique<DevBuf<double>>();
+                H->a64[l]->alloc(L.nelem);
+                HIPCHK(hipMemset(H->a64[l]->p, 0, L.nelem * 8));
+            }
+            H->bytes += (H->precision == 1 ? 4 : 8) * (size_t)L.nelem;
+        } catch (HipError& e) {
+            if (e.e != hipErrorOutOfMemory) throw;
+            (void)hipGetLastError();
+            H->a32[l].reset();
+            H->a64[l].reset();
+            L.stream = false;
+        }
+    }
+}
+
+// Allocates what a solve cannot do without once the hierarchy stands; without
+// room for it the streamed levels give their second arrays up.
+template <class F>
+static void alloc_needed(Hier* H, F alloc) {
+    try {
+        alloc();
+        return;
+    } catch (HipError& e) {
+        if (e.e != hipErrorOutOfMemory) throw;
+        (void)hipGetLastError();
+        bool room = false;
+        for (size_t l = 0; l < H->L.size(); ++l) {
+            Level& L = *H->L[l];
+            if (!L.stream) continue;
+            room = true;
+            L.stream = false;
+            H->a32[l].reset();
+            H->a64[l].reset();
+            H->bytes -= (H->precision == 1 ? 4 : 8) * (size_t)L.nelem;
+        }
+        if (!room) throw;
+    }
+    alloc();
 }
 
 // merge: coarse levels run on execution_boxes (solves); the stage calls keep
@@ -358,6 +400,7 @@ static std::unique_ptr<Hier> build_hier(const bxmg_ba_s* ba, int precision, bool
     HIPCHK(hipMemset(H->state.p, 0, sizeof(SolveState)));
     H->guess_nz.alloc(1);
     H->iters.alloc(1);
+    alloc_streams(H.get());
     return H;
 }
 
@@ -1146,15 +1189,17 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
     const long long n = L0.nelem;
     Hier::Krylov& K = H->kr;
     if (!K.r.p) {
-        K.r.alloc(n);
-        K.q.alloc(n);
-        K.p[0].alloc(n);
-        K.p[1].alloc(n);
         if (L0.boxes.size() == 1 && L0.boxes[0].cells() == L0.dom.cells() && L0.push && L0.res)
             K.dir = plan_direction(L0.rb[0], H->per);
-        K.part.alloc(4 * (size_t)std::max(std::max(L0.ntcol, K.dir.blocks), 1));
-        K.sums.alloc(3);
-        K.sc.alloc(1);
+        alloc_needed(H, [&] {
+            K.q.alloc(n);
+            K.p[0].alloc(n);
+            K.p[1].alloc(n);
+            K.part.alloc(4 * (size_t)std::max(std::max(L0.ntcol, K.dir.blocks), 1));
+            K.sums.alloc(3);
+            K.sc.alloc(1);
+            K.r.alloc(n);  // last: its presence says that all of them are there
+        });
         HIPCHK(hipMemsetAsync(K.sc.p, 0, sizeof(KrylovScalars), R.s));
         // ghosts of r are never written, q is read before its first write
         // (a restart's dot pass discards z.q): both start at zero
@@ -1170,8 +1215,10 @@ static void krylov_iterate(Run& R, Hier* H, const bxmg_solve_params& P, bxmg_ctx
         // the FP64 V-cycle works in level 0's own arrays: the iterate and the
         // right-hand side move out for the solve
         if (!K.x.p) {
-            K.x.alloc(n);
-            K.f.alloc(n);
+            alloc_needed(H, [&] {
+                K.f.alloc(n);
+                K.x.alloc(n);
+            });
             H->bytes += 16 * (size_t)n;
         }
         HIPCHK(hipMemcpyAsync(K.x.p, u, n * sizeof(double), hipMemcpyDeviceToDevice, R.s));

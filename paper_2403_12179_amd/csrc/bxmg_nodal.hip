@@ -1008,7 +1008,6 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
     for (size_t q = 0; q < end; ++q) {
         H->pre[q] = plan_nd_sweep(H->L[q], H->L[q + 1], q > 0, 1, false);
         H->post[q] = plan_nd_sweep(H->L[q], H->L[q + 1], false, q > 0 ? 0 : 2, true);
-        if (H->pre[q].nt) H->a[q].alloc(H->L[q].alloc);
         np = std::max(np, H->post[q].blocks);
     }
     for (const NLev& l : H->L) np = std::max(np, plane_blocks(l, true, plane_depth(l, true, kKZr)));
@@ -1017,6 +1016,17 @@ static NHier* get(bxmg_ctx ctx, const bxmg_ba_s* ba, double h0) {
     H->bq.alloc(B.alloc);
     H->fn.alloc(3);
     H->iters.alloc(1);
+    // last: a level whose second array finds no room is not streamed
+    for (size_t q = 0; q < end; ++q) {
+        if (!H->pre[q].nt) continue;
+        try {
+            H->a[q].alloc(H->L[q].alloc);
+        } catch (HipError& e) {
+            if (e.e != hipErrorOutOfMemory) throw;
+            (void)hipGetLastError();
+            H->pre[q].nt = 0;
+        }
+    }
     if (C.h.size() >= 4) C.h.erase(C.h.begin());
     C.h.push_back(std::move(H));
     return C.h.back().get();
