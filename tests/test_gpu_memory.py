@@ -26,10 +26,17 @@ def free():
 
 
 def fill_but(room):
+    """Tensors that leave the device `room` bytes: all it gives (its runtime
+    hands memory back that it had kept) beside a tensor of that size."""
     import torch
-    full = []  # (one allocation may leave more than was asked for)
-    while free() > room + (8 << 20):
-        full.append(torch.empty(free() - room, dtype=torch.uint8, device="cuda"))
+    kept, full, size = torch.empty(room, dtype=torch.uint8, device="cuda"), [], free()
+    while size >= 4 << 20:
+        try:
+            full.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        except torch.OutOfMemoryError:
+            size //= 2
+    del kept
+    torch.cuda.empty_cache()
     return full
 
 
