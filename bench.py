@@ -86,16 +86,18 @@ GS_KERNEL = "k_sweep<double>"
 GS_MATCH = "k_sweep<double"
 COPY_BYTES = 1 << 30
 
-# Bytes per fine cell that a V(2,2) cycle of one launch per half-sweep moves at
-# least, FP64 (s = 8 B), per level l with N_l cells: 8 half-sweeps x 1.5 s N_l +
-# residual/restriction (2 + 1/8) s N_l + zeroing the coarse guess s N_l / 8 +
-# prolongation (2 + 1/8) s N_l = 16.375 s N_l; sum over levels 8/7 N_0; plus the
-# level-0 convergence residual 2 s N_0.  The streaming smoother moves fewer (a
-# launch reads u and f, reads or writes an eighth of them for the coarse level,
-# writes u); the model stays, so that effective GB/s compare across versions.
-BYTES_PER_CELL_CYCLE = 8.0 * (16.375 * 8.0 / 7.0 + 2.0)
-GS_BYTES_PER_CELL = 3.125 * 8.0
-# ... and one colour of a level that is not streamed (buffer addressing off):
+# Bytes per fine cell that a streamed V(2,2) cycle moves at least, FP64 (s = 8
+# B): a launch reads one colour of u (none from zero) and f, writes u, and reads
+# or writes an eighth of an array for the coarse level.  Level 0: twice 2.625 s;
+# a level below, of 1/8, 1/64, ... the cells: from zero 2.125 s, then 2.625 s.
+GS_BYTES_PER_CELL = 2.625 * 8.0
+STREAMED_BYTES_PER_CELL_CYCLE = 8.0 * (2 * 2.625 + (2.125 + 2.625) / 7.0)
+# ... and a cycle of one launch per half-sweep (buffer addressing off), per level
+# l with N_l cells: 8 half-sweeps x 1.5 s N_l + residual/restriction (2 + 1/8) s
+# N_l + zeroing the coarse guess s N_l / 8 + prolongation (2 + 1/8) s N_l = 16.375
+# s N_l; sum over levels 8/7 N_0; plus the level-0 convergence residual 2 s N_0.
+HALF_SWEEP_BYTES_PER_CELL_CYCLE = 8.0 * (16.375 * 8.0 / 7.0 + 2.0)
+# one colour of a level in the latter:
 # read the other colour and this colour's rhs, write this colour
 HALF_BYTES_PER_CELL = 1.5 * 8.0
 
@@ -1055,6 +1057,7 @@ def main():
         value = N ** 3 * mean_cycles / (ms_per_step / 1000.0)
         gs_avg_ms = gs_ms.value / max(launches.value, 1)
         gs_bytes = (GS_BYTES_PER_CELL if r else HALF_BYTES_PER_CELL) * N ** 3
+        cycle_bytes = STREAMED_BYTES_PER_CELL_CYCLE if r else HALF_SWEEP_BYTES_PER_CELL_CYCLE
         achieved = gs_bytes / (gs_avg_ms / 1000.0) / 1e9
         key = shape_key(z, r, ly)
         traffic = traffic_from_counters(key)
@@ -1074,8 +1077,8 @@ def main():
             "config": {"workload": "poisson_dirichlet_256c_512x32c_fp64_vcycle22_tol1e-10", "domain": [N, N, N],
                        "boxes": len(ba), "box": [MAX_BOX] * 3, "nghost": 1, "levels": res.levels,
                        "cycles_per_solve": mean_cycles, "rhs": "uniform[-1,1] seed 2"},
-            "vcycle_effective_GBps": BYTES_PER_CELL_CYCLE * N ** 3 * mean_cycles / (ms_per_step / 1000.0) / 1e9,
-            "vcycle_model_bytes_per_cell": BYTES_PER_CELL_CYCLE,
+            "vcycle_effective_GBps": cycle_bytes * N ** 3 * mean_cycles / (ms_per_step / 1000.0) / 1e9,
+            "vcycle_model_bytes_per_cell": cycle_bytes,
             "solves_per_s": 1000.0 / ms_per_step,
             "autotuned_launch_shape": tuned,
             "final_rel_resid_inf": res.rel_resid_inf,

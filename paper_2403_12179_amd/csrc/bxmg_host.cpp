@@ -185,7 +185,7 @@ static void upload_tiles(const TileSet& t, DevBuf<Tile>& buf, int& n) {
 
 // Levels the streaming smoother takes: one box, 32-bit offsets, above the
 // coarse cycle (below it the levels run in one workgroup); with a variable
-// coefficient in FP32 only, as its FP64 form would not fit the registers.
+// coefficient in FP32 only (the FP64 form would leave one wave a SIMD).
 static void plan_streams(Hier* H, long long& max_tiles) {
     const size_t nl = H->L.size();
     const size_t end = H->coarse_start >= 0 ? (size_t)H->coarse_start : nl - 1;

@@ -1,5 +1,6 @@
-// Streaming smoother: two red-black sweeps of a one-box, constant-coefficient
-// level in one pass over its data, with the residual that follows them.
+// Streaming smoother: two red-black sweeps of a one-box level in one pass over
+// its data, with the residual that follows them or the prolongation before
+// them; the coefficient constant, or in FP32 a cell beta or face arrays.
 //
 // One half-sweep per launch moves 1.5 arrays per half-sweep, 6 for the two
 // sweeps of a V(2,2) cycle and 2 more for the residual after them.  Here a
@@ -15,8 +16,9 @@
 // Every stage's z neighbours and own cells are in the thread's registers
 // (its column's last few planes); of its x and y neighbours one is the
 // thread's own other cell and three come from LDS, written there one step
-// earlier by the stage before (one barrier per step).  So u and f are read
-// once and u written once.  A block recomputes a halo around its own columns
+// earlier by the stage before (one barrier per step).  So f and one colour of
+// u are read once (the other's old values only beside Dirichlet faces, where a
+// ghost holds them) and u written once.  A block recomputes a halo around its own columns
 // (one layer per stage), reading u of one array and writing another: blocks
 // need nothing of each other.  The arithmetic of a cell, and the order of
 // its sums, are those of the one-colour kernel, so the results are bitwise
@@ -30,13 +32,14 @@
 // Measured on the 256^3 FP64 Dirichlet level 0: two sweeps, residual and
 // restriction 160 us, against 4 x 50 + 66 us one launch each; two sweeps after
 // the coarse levels with the interpolation and the norms 217, against 58 + 4 x
-// 50 + 66.  The arrays alone take 52 to 66 us at the copy rate; loads, stores,
+// 50 + 66.  The arrays alone (352 MB: half of u, f, u out, an eighth for the
+// coarse level) take 75 us at the 4.67 TB/s of a large copy; loads, stores,
 // LDS traffic (18 to 26 reads and 6 writes of a value per thread and step) and
 // FP64 issue (85 to 110 instructions) overlap only in part, as a block's waves
 // run the same phase of a step together.  The 256^3 solve went from 8.78 to
-// 5.56 ms, the 192^3 heat step from 4.49 to 2.60 ms.  Adding an FP32
+// 5.57 ms, the 192^3 heat step from 4.49 to 2.61 ms.  Adding an FP32
 // correction to the FP64 iterate (kSweepAdd) takes 455 us over the 52 million
-// cells of 64 problems, 240 of which are its bytes at the copy rate.
+// cells of 64 problems, 250 of which are its bytes at the copy rate.
 //
 // With a coefficient (FP32) a thread has the 9 faces of its pair formed once
 // per plane and kept in 60 registers: a half-sweep launch forms 6 harmonic
@@ -45,8 +48,11 @@
 // halo: 512^3, cell beta, sweeps from zero with residual and restriction 1380
 // us against 4 x 396 + 615, sweeps after the coarse levels 1255 against 256 + 4
 // x 396; 256^3 with face arrays 160 and 180 us against 4 x 60 + 97 and 85 + 4 x
-// 60.  The 512^3 preconditioned solve went from 164 to 112 ms (with its
-// direction pass below), the 128^3 mixed one from 6.8 to 5.2.
+// 60.  With the direction pass below and the fused coarse cycle the 512^3
+// preconditioned solve went from 158 to 113 ms and the 128^3 mixed one from 6.7
+// to 5.2 (both versions in turn on one card).  In FP64 the same form takes 340
+// registers a thread before and 298 after the coarse levels: one wave a SIMD
+// in blocks of 256 threads, and 205 spilled in blocks of 512.  It is not built.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -569,7 +575,7 @@ __global__ void __launch_bounds__(NT) k_sweep(SweepArgs A0, const SweepArgs* __r
 // read (minus the own cell beyond a Dirichlet face, own beta there) nor
 // written.  Same operations per cell as k_kr_axpy and k_kr_apply.
 // Bound by its bytes (36 a cell with e in FP32) and, with MODE 1, by 9 FP64
-// divisions a pair: 512^3, FP32 e, MODE 1 1180 us, 950 of them its bytes at the
+// divisions a pair: 512^3, FP32 e, MODE 1 1180 us, 1030 of them its bytes at the
 // copy rate; the two launches took 715 + 1415, the second with 12 divisions a
 // pair and 6 more FP64 loads a cell.
 constexpr int kDirThreads = 512;
@@ -793,7 +799,9 @@ template hipError_t launch_kr_direction<double>(hipStream_t, const SweepPlan&, c
 // most 1024 columns is priced as (rounds of blocks over the CUs) x (steps of a
 // block) x (time of a step) and the cheapest taken.  A step's time in clocks
 // is linear in the waves on a CU (fitted to timings of every split of levels
-// of 32^3 to 128^3: the plans are within 10 % of the best one there).
+// of 32^3 to 128^3: the plans are within 10 % of the best one there).  It knows
+// neither bytes nor interpolation, so the price of large levels is too low (at
+// 256^3 about 92 us a launch, for 160 and 217); their splits were not timed.
 SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode, int cus, int ntmax) {
     SweepPlan best;
     const bool res = kind == kSweepRestrict || kind == kSweepNorm;
