@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace bxmg {
 
@@ -262,6 +263,10 @@ struct SweepPlan {
     int threads = 0, blocks = 0;
     SweepArgs args{};
 };
+// The sizes of the pieces, multiples of unit, that cells (a multiple of it) can
+// be cut into evenly, the last piece smaller: largest first, each once.  sparse:
+// beyond 16 pieces only every eighth more are tried.
+std::vector<int> piece_sizes(int cells, int unit, bool sparse = false);
 // The blocks of a level of n cells (storage and coarse fields of args unset),
 // for cus compute units, at most ntmax threads each.  mode: as in launch_sweep.
 SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode = 0, int cus = 256,

@@ -464,14 +464,12 @@ static NSweep plan_nd_sweep(const NLev& L, const NLev& C, bool zero, int kind, b
     if (L.alloc * 8 > 0x7fffffffLL) return best;
     const int halo = (kind ? 5 : 4) - (zero ? 1 : 0), lead = ((halo + 1) & ~1) + 5, nm = L.n[0] / 2;
     double cost = 1e30;
-    auto split = [](int cells, int pieces, int unit) { return (cells / unit + pieces - 1) / pieces * unit; };
-    for (int px = 1; px <= nm; ++px) {
-        const int XM = split(nm, px, 1);
-        if (XM < 4 && px > 1) break;
+    const std::vector<int> ys = piece_sizes(L.n[1], 2), zs = piece_sizes(L.n[2], 2, true);
+    for (int XM : piece_sizes(nm, 1)) {
+        if (XM < 4 && XM < nm) break;
         const int hm = XM == nm ? 0 : (halo + 1) / 2, RM = XM == nm ? nm + (L.per[0] ? 0 : 1) : XM + 2 * hm;
         if (RM > 768) continue;
-        for (int py = 1; py <= L.n[1] / 2; ++py) {
-            const int TY = split(L.n[1], py, 2);
+        for (int TY : ys) {
             const bool span = TY == L.n[1];
             const int hy = span ? 0 : halo, RY = span ? TY + (L.per[1] ? 0 : 1) : TY + 2 * hy;
             const int cols = std::max(RM * RY, post ? (RM + 1) * (RY / 2 + 3) : 0);
@@ -479,8 +477,8 @@ static NSweep plan_nd_sweep(const NLev& L, const NLev& C, bool zero, int kind, b
             const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : 768;
             const int nbx = (nm + XM - 1) / XM, nby = (L.n[1] + TY - 1) / TY;
             const int fit = nt == 256 ? 3 : 1;
-            for (int pz = 1; pz <= L.n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
-                const int ZC = split(L.n[2], pz, 2), nbz = (L.n[2] + ZC - 1) / ZC;
+            for (int ZC : zs) {
+                const int nbz = (L.n[2] + ZC - 1) / ZC;
                 const long long blocks = (long long)nbx * nby * nbz, per_cu = (blocks + 255) / 256;
                 const int waves = (int)std::min<long long>(per_cu, fit) * ((cols + 63) / 64);
                 const double c = (double)((per_cu + fit - 1) / fit) * (ZC + lead) * (550.0 + 115.0 * waves) +
@@ -494,7 +492,6 @@ static NSweep plan_nd_sweep(const NLev& L, const NLev& C, bool zero, int kind, b
                     best.XM = XM; best.TY = TY; best.ZC = ZC;
                     best.nbx = nbx; best.nby = nby; best.nbz = nbz;
                 }
-                if (ZC == 2) break;
             }
         }
     }

@@ -57,6 +57,7 @@
 #include <type_traits>
 
 #include <algorithm>
+#include <vector>
 
 #include "bxmg_device.h"
 
@@ -730,6 +731,16 @@ __global__ void __launch_bounds__(kDirThreads, 4)
     if (tid == 0) store_sums(partials, blk, pq, Sum2{});
 }
 
+std::vector<int> piece_sizes(int cells, int unit, bool sparse) {
+    const int u = cells / unit;
+    std::vector<int> out;
+    for (int p = 1; p <= u; p += sparse && p >= 16 ? p / 8 : 1) {
+        const int size = (u + p - 1) / p * unit;
+        if (out.empty() || out.back() != size) out.push_back(size);
+    }
+    return out;
+}
+
 // The blocks of k_kr_direction: the split with the fewest columns and planes
 // read per cell that still gives every CU two rounds of two blocks.
 SweepPlan plan_direction(const RBox& B, const int per[3]) {
@@ -741,17 +752,17 @@ SweepPlan plan_direction(const RBox& B, const int per[3]) {
     }
     const int nm = n[0] / 2;
     double cost = 1e30;
-    auto split = [](int cells, int pieces, int unit) { return (cells / unit + pieces - 1) / pieces * unit; };
-    for (int px = 1; px <= nm; ++px) {
-        const int XM = split(nm, px, 1), hm = XM == nm ? 0 : 1, RM = XM + 2 * hm;
-        if (XM < 8 && px > 1) break;
+    const std::vector<int> ys = piece_sizes(n[1], 1), zs = piece_sizes(n[2], 2, true);
+    for (int XM : piece_sizes(nm, 1)) {
+        const int hm = XM == nm ? 0 : 1, RM = XM + 2 * hm;
+        if (XM < 8 && XM < nm) break;
         if (RM > kDirThreads) continue;
-        for (int py = 1; py <= n[1]; ++py) {
-            const int TY = split(n[1], py, 1), hy = TY == n[1] ? 0 : 1, cols = RM * (TY + 2 * hy);
+        for (int TY : ys) {
+            const int hy = TY == n[1] ? 0 : 1, cols = RM * (TY + 2 * hy);
             if (cols > kDirThreads) continue;
             const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
-            for (int pz = 1; pz <= n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
-                const int ZC = split(n[2], pz, 2), nbz = (n[2] + ZC - 1) / ZC;
+            for (int ZC : zs) {
+                const int nbz = (n[2] + ZC - 1) / ZC;
                 const long long blocks = (long long)nbx * nby * nbz, rounds = (blocks + 511) / 512;
                 const double c = (double)rounds * (ZC + 4) * (1.0 + (cols + 63) / 64) + 1e-3 * (double)blocks;
                 if (c < cost) {
@@ -764,7 +775,6 @@ SweepPlan plan_direction(const RBox& B, const int per[3]) {
                     A.XM = XM; A.TY = TY; A.ZC = ZC;
                     A.nbx = nbx; A.nby = nby; A.nbz = nbz;
                 }
-                if (ZC == 2) break;
             }
         }
     }
@@ -797,11 +807,13 @@ template hipError_t launch_kr_direction<double>(hipStream_t, const SweepPlan&, c
 
 // Blocks of a level: every split of its rows and planes into blocks of at
 // most 1024 columns is priced as (rounds of blocks over the CUs) x (steps of a
-// block) x (time of a step) and the cheapest taken.  A step's time in clocks
-// is linear in the waves on a CU (fitted to timings of every split of levels
-// of 32^3 to 128^3: the plans are within 10 % of the best one there).  It knows
-// neither bytes nor interpolation, so the price of large levels is too low (at
-// 256^3 about 92 us a launch, for 160 and 217); their splits were not timed.
+// block) x (time of a step) and the cheapest taken.  A hierarchy is planned on
+// its first solve, so each size of a piece is priced once: 0.4 ms for the levels
+// of 512^3, 52 with every number of pieces (256^3: 0.2 and 11).  A step's time in
+// clocks is linear in the waves on a CU (fitted to timings of every split of
+// levels of 32^3 to 128^3: the plans are within 10 % of the best one there).  It
+// knows neither bytes nor interpolation, so the price of large levels is too low
+// (at 256^3 about 92 us a launch, for 160 and 217); their splits were not timed.
 SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool f32, int mode, int cus, int ntmax) {
     SweepPlan best;
     const bool res = kind == kSweepRestrict || kind == kSweepNorm;
@@ -812,18 +824,13 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
     // thread: at most 12 waves, 8 where those would spill)
     ntmax = std::min(ntmax, f32 && mode == 0 ? 1024 : mode == 2 && kind != kSweepRestrict ? 512 : 768);
     double cost = 1e30;
-    auto split = [](int cells, int pieces, int unit) {  // the size of equal pieces, a multiple of unit
-        const int u = cells / unit, q = (u + pieces - 1) / pieces;
-        return q * unit;
-    };
-    for (int px = 1; px <= nm; ++px) {
-        const int XM = split(nm, px, 1);
-        if (XM < 4 && px > 1) break;
+    const std::vector<int> ys = piece_sizes(n[1], 2), zs = piece_sizes(n[2], 2, true);
+    for (int XM : piece_sizes(nm, 1)) {
         const bool wx = XM == nm;
+        if (XM < 4 && !wx) break;
         const int hm = wx ? 0 : (halo + 1) / 2, RM = XM + 2 * hm;
         if (RM > ntmax) continue;
-        for (int py = 1; py <= n[1] / 2; ++py) {
-            const int TY = split(n[1], py, 2);
+        for (int TY : ys) {
             const bool wy = TY == n[1];
             const int hy = wy ? 0 : halo, RY = TY + 2 * hy;
             // (after the coarse levels a block also needs a thread per coarse column)
@@ -832,8 +839,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
             const int nt = cols <= 256 ? 256 : cols <= 512 ? 512 : cols <= 768 ? 768 : 1024;
             const int nbx = (nm + XM - 1) / XM, nby = (n[1] + TY - 1) / TY;
             const int fit = mode ? (nt == 256 ? 3 : 1) : nt == 256 ? 5 : nt == 512 ? 2 : 1;  // blocks a CU holds (registers)
-            for (int pz = 1; pz <= n[2] / 2; pz = pz < 16 ? pz + 1 : pz + pz / 8) {
-                const int ZC = split(n[2], pz, 2);
+            for (int ZC : zs) {
                 const int nbz = (n[2] + ZC - 1) / ZC;
                 const long long blocks = (long long)nbx * nby * nbz;
                 const long long per_cu = (blocks + cus - 1) / cus;
@@ -851,9 +857,7 @@ SweepPlan plan_sweep(const int n[3], const int per[3], int kind, bool zero, bool
                     A.XM = XM; A.TY = TY; A.ZC = ZC;
                     A.nbx = nbx; A.nby = nby; A.nbz = nbz;
                 }
-                if (ZC == 2) break;
             }
-            if (TY == 2) break;
         }
     }
     for (int d = 0; d < 3; ++d) { best.args.n[d] = n[d]; best.args.per[d] = per[d]; }
